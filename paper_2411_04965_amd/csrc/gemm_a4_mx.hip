@@ -62,8 +62,8 @@ __device__ __forceinline__ u32 gx_pack_bf16(float lo, float hi) {
   return r;
 }
 
-// OUT: 0 = bf16 rows through the LDS transpose (N % 8 == 0), 1 = 4 outputs per store (N % 4 == 0),
-// 2 = one output per store (any N).  ACC: also write the integer accumulators (tests).
+// OUT: 0 = bf16 rows through the LDS transpose, 1 = float32, 4 outputs per store (N % 4 == 0), 2 = float32, one
+// output per store (any N).  ACC: also write the integer accumulators (tests).
 // FP4: the activations are E2M1 codes with one E8M0 scale per token and 32 channels (eq. 8-9)
 // instead of E3M2 codes of INT4 levels: 2 KB instead of 3 KB per block, the same instruction in its
 // scaled form with the block scales as the column operand's scale (`xsc`, 128 bytes per block in
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(GX_THREADS, 1) void gemm_a4_mx_kernel(
     const unsigned char* __restrict__ A, const float* __restrict__ scale,
     const unsigned char* __restrict__ xsc, int M, int KB,
     const unsigned char* __restrict__ Wp, const float* __restrict__ alpha_p, int N, void* __restrict__ Y,
-    int y_bf16, int32_t* __restrict__ acc_out, int MT, int NTB,
+    int32_t* __restrict__ acc_out, int MT, int NTB,
     const unsigned char* __restrict__ Wp2 = nullptr, const float* __restrict__ alpha2_p = nullptr) {
   extern __shared__ __align__(16) unsigned char gx_smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(GX_THREADS, 1) void gemm_a4_mx_kernel(
       // 4 lh + r % 4, token m = 32 b + l32 of the wave tile
       const float alpha2 = alpha2_p[0];
       const int nw = (n0 >> 1) + wn * (WN / 2);                // first H column of this wave
-      if (OUT == 0) {
+      {
         constexpr int TB_ROW = WN + 32;                      // 64 bfloat16 per token + padding
         unsigned char* tbuf = gx_smem + GX_TB + wave * (32 * (WN * 2 + 32));
         constexpr int LANES_PER_ROW = WN / 16;               // 8 lanes cover one token's 128 bytes
@@ -469,35 +469,20 @@ __global__ __launch_bounds__(GX_THREADS, 1) void gemm_a4_mx_kernel(
           for (int i = 0; i < NPASS; ++i) {
             const int row = b * 32 + i * ROWS_PER_PASS;
             const v4i v = *reinterpret_cast<const v4i*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
-            if (interior || (row < m_left && 0 < n_left)) *reinterpret_cast<v4i*>(ywave + (size_t)row * N + lane_off) = v;
+            if (interior || (row < m_left && n_left >= 8)) *reinterpret_cast<v4i_align2*>(ywave + (size_t)row * N + lane_off) = v;
+          }
+          if (!interior && (N & 7)) {                        // uniform
+#pragma unroll 1
+            for (int i = 0; i < NPASS; ++i) {
+              const int row = b * 32 + i * ROWS_PER_PASS;
+              const v4i v = *reinterpret_cast<const v4i*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
+              if (row < m_left && 0 < n_left && n_left < 8) bl_store_tail8(ywave + (size_t)row * N + lane_off, v, n_left);
+            }
           }
           __builtin_amdgcn_sched_barrier(0);
         }
-      } else {
-#pragma unroll
-        for (int b = 0; b < TM; ++b) {
-          const int m = m0 + wm * WM + b * 32 + l32;
-          const float d = dsc[b];
-#pragma unroll
-          for (int a = 0; a < TN / 2; ++a) {
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-              const int n = nw + a * 32 + 8 * q4 + 4 * lh;
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const float g = (acc[a][b][4 * q4 + r] * d) * alpha;
-                const float u = (acc[a + 2][b][4 * q4 + r] * d) * alpha2;
-                const float rl = fmaxf(g, 0.0f);
-                const float rr2 = rl * rl;
-                if (m < M && n + r < N) ((uint16_t*)Y)[(size_t)m * N + n + r] = bl_f32_to_bf16_rne(u * rr2);
-              }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
       }
-    } else
-    if (OUT == 0) {
+    } else if (OUT == 0) {
       constexpr int TB_ROW = WN * 2 + 32;
       unsigned char* tbuf = gx_smem + GX_TB + wave * (32 * TB_ROW);
       static_assert(4 * 32 * TB_ROW <= GX_TB_BYTES, "transpose space");
@@ -534,13 +519,21 @@ __global__ __launch_bounds__(GX_THREADS, 1) void gemm_a4_mx_kernel(
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < NPASS; ++i)
-            *reinterpret_cast<v4i*>(ywave + (size_t)(b * 32 + i * ROWS_PER_PASS) * N + lane_off) = v[i];
+            *reinterpret_cast<v4i_align2*>(ywave + (size_t)(b * 32 + i * ROWS_PER_PASS) * N + lane_off) = v[i];
         } else {
 #pragma unroll
           for (int i = 0; i < NPASS; ++i) {
             const int row = b * 32 + i * ROWS_PER_PASS;
             const v4i v = *reinterpret_cast<const v4i*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
-            if (row < m_left && 0 < n_left) *reinterpret_cast<v4i*>(ywave + (size_t)row * N + lane_off) = v;
+            if (row < m_left && n_left >= 8) *reinterpret_cast<v4i_align2*>(ywave + (size_t)row * N + lane_off) = v;
+          }
+          if (N & 7) {                                       // uniform
+#pragma unroll 1
+            for (int i = 0; i < NPASS; ++i) {
+              const int row = b * 32 + i * ROWS_PER_PASS;
+              const v4i v = *reinterpret_cast<const v4i*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
+              if (row < m_left && 0 < n_left && n_left < 8) bl_store_tail8(ywave + (size_t)row * N + lane_off, v, n_left);
+            }
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -560,24 +553,11 @@ __global__ __launch_bounds__(GX_THREADS, 1) void gemm_a4_mx_kernel(
 #pragma unroll
             for (int r = 0; r < 4; ++r) fv[r] = (acc[a][b][4 * q4 + r] * d) * alpha;
             if (OUT == 1) {
-              if (m < M && n < N) {
-                if (y_bf16) {
-                  uint2 p;
-                  p.x = gx_pack_bf16(fv[0], fv[1]);
-                  p.y = gx_pack_bf16(fv[2], fv[3]);
-                  *reinterpret_cast<uint2*>((uint16_t*)Y + o) = p;
-                } else {
-                  *reinterpret_cast<float4*>((float*)Y + o) = make_float4(fv[0], fv[1], fv[2], fv[3]);
-                }
-              }
+              if (m < M && n < N) *reinterpret_cast<float4*>((float*)Y + o) = make_float4(fv[0], fv[1], fv[2], fv[3]);
             } else {
 #pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                if (m < M && n + r < N) {
-                  if (y_bf16) ((uint16_t*)Y)[o + r] = bl_f32_to_bf16_rne(fv[r]);
-                  else ((float*)Y)[o + r] = fv[r];
-                }
-              }
+              for (int r = 0; r < 4; ++r)
+                if (m < M && n + r < N) ((float*)Y)[o + r] = fv[r];
             }
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -613,13 +593,12 @@ __global__ __launch_bounds__(GX_THREADS, 1) void gemm_a4_mx_kernel(
 
 template <int OUT, bool ACC, bool FP4, bool W2>
 static int gx_go(const void* q, const float* scale, const uint8_t* xsc, int M, int KB, const void* Wp,
-                 const float* alpha, int N, void* Y, int y_bf16, int32_t* acc_out, int MT, int NTB,
-                 hipStream_t s) {
+                 const float* alpha, int N, void* Y, int32_t* acc_out, int MT, int NTB, hipStream_t s) {
   BL_SET_MAX_LDS_ONCE((gemm_a4_mx_kernel<OUT, ACC, FP4, W2>), GX_LDS);
   const int grid = min(MT * NTB, bl_num_cus());      // persistent blocks, one per CU (all of its LDS)
   gemm_a4_mx_kernel<OUT, ACC, FP4, W2><<<(unsigned)grid, GX_THREADS, GX_LDS, s>>>(
       (const unsigned char*)q, scale, (const unsigned char*)xsc, M, KB, (const unsigned char*)Wp, alpha, N, Y,
-      y_bf16, acc_out, MT, NTB);
+      acc_out, MT, NTB);
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
 }
@@ -629,11 +608,10 @@ int bl_launch_gemm_a4_mx(const void* q, const float* scale, int64_t M, int64_t K
                          hipStream_t s) {
   const int KB = (int)(bl_round_up(K, BL_KPAD) / 128);
   const int MT = (int)((M + GX_BM - 1) / GX_BM), NTB = (int)((N + GX_BN - 1) / GX_BN);
-  const int out = (ydt == BL_BF16 && (N & 7) == 0) ? 0 : ((N & 3) == 0 ? 1 : 2);
-  const int yb = ydt == BL_BF16 ? 1 : 0;
+  const int out = ydt == BL_BF16 ? 0 : ((N & 3) == 0 ? 1 : 2);
 #define GX_CALL(OUT, ACC) \
-  (w2 ? gx_go<OUT, ACC, false, true>(q, scale, nullptr, (int)M, KB, Wp, alpha, (int)N, Y, yb, acc_out, MT, NTB, s) \
-      : gx_go<OUT, ACC, false, false>(q, scale, nullptr, (int)M, KB, Wp, alpha, (int)N, Y, yb, acc_out, MT, NTB, s))
+  (w2 ? gx_go<OUT, ACC, false, true>(q, scale, nullptr, (int)M, KB, Wp, alpha, (int)N, Y, acc_out, MT, NTB, s) \
+      : gx_go<OUT, ACC, false, false>(q, scale, nullptr, (int)M, KB, Wp, alpha, (int)N, Y, acc_out, MT, NTB, s))
   if (acc_out) return out == 0 ? GX_CALL(0, true) : out == 1 ? GX_CALL(1, true) : GX_CALL(2, true);
   return out == 0 ? GX_CALL(0, false) : out == 1 ? GX_CALL(1, false) : GX_CALL(2, false);
 #undef GX_CALL
@@ -641,13 +619,13 @@ int bl_launch_gemm_a4_mx(const void* q, const float* scale, int64_t M, int64_t K
 
 // Gate and up projection with the ReLU^2 GLU in the epilogue: H[M, N] bfloat16 from INT4 activations in the
 // MX6 form and two weight matrices [N, K] in the same block-float layout.
-template <int OUT, bool W2>
+template <bool W2>
 static int gx_go_glu(const void* q, const float* scale, int M, int KB, const void* Wg, const float* ag, const void* Wu,
                      const float* au, int N, void* H, int MT, int NTB, hipStream_t s) {
-  BL_SET_MAX_LDS_ONCE((gemm_a4_mx_kernel<OUT, false, false, W2, true>), GX_LDS);
+  BL_SET_MAX_LDS_ONCE((gemm_a4_mx_kernel<0, false, false, W2, true>), GX_LDS);
   const int grid = min(MT * NTB, bl_num_cus());
-  gemm_a4_mx_kernel<OUT, false, false, W2, true><<<(unsigned)grid, GX_THREADS, GX_LDS, s>>>(
-      (const unsigned char*)q, scale, nullptr, M, KB, (const unsigned char*)Wg, ag, N, H, 1, nullptr, MT, NTB,
+  gemm_a4_mx_kernel<0, false, false, W2, true><<<(unsigned)grid, GX_THREADS, GX_LDS, s>>>(
+      (const unsigned char*)q, scale, nullptr, M, KB, (const unsigned char*)Wg, ag, N, H, nullptr, MT, NTB,
       (const unsigned char*)Wu, au);
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
@@ -657,11 +635,8 @@ int bl_launch_gemm_a4_mx_glu(const void* q, const float* scale, int64_t M, int64
                              const void* Wu, const float* au, bool w2, int64_t N, void* H, hipStream_t s) {
   const int KB = (int)(bl_round_up(K, BL_KPAD) / 128);
   const int MT = (int)((M + GX_BM - 1) / GX_BM), NTB = (int)((N + GX_BN / 2 - 1) / (GX_BN / 2));
-  const bool rows = (N & 7) == 0;
-  if (w2) return rows ? gx_go_glu<0, true>(q, scale, (int)M, KB, Wg, ag, Wu, au, (int)N, H, MT, NTB, s)
-                      : gx_go_glu<2, true>(q, scale, (int)M, KB, Wg, ag, Wu, au, (int)N, H, MT, NTB, s);
-  return rows ? gx_go_glu<0, false>(q, scale, (int)M, KB, Wg, ag, Wu, au, (int)N, H, MT, NTB, s)
-              : gx_go_glu<2, false>(q, scale, (int)M, KB, Wg, ag, Wu, au, (int)N, H, MT, NTB, s);
+  return w2 ? gx_go_glu<true>(q, scale, (int)M, KB, Wg, ag, Wu, au, (int)N, H, MT, NTB, s)
+            : gx_go_glu<false>(q, scale, (int)M, KB, Wg, ag, Wu, au, (int)N, H, MT, NTB, s);
 }
 
 // FP4 activations (E2M1 codes and E8M0 block scales in the MX form) x BL_W_MX4 weights.
@@ -669,11 +644,10 @@ int bl_launch_gemm_fp4_mx(const void* q, const uint8_t* xscale, int64_t M, int64
                           const float* alpha, int64_t N, void* Y, bl_dtype ydt, hipStream_t s) {
   const int KB = (int)(bl_round_up(K, BL_KPAD) / 128);
   const int MT = (int)((M + GX_BM - 1) / GX_BM), NTB = (int)((N + GX_BN - 1) / GX_BN);
-  const int out = (ydt == BL_BF16 && (N & 7) == 0) ? 0 : ((N & 3) == 0 ? 1 : 2);
-  const int yb = ydt == BL_BF16 ? 1 : 0;
+  const int out = ydt == BL_BF16 ? 0 : ((N & 3) == 0 ? 1 : 2);
 #define GX_CALL4(OUT) \
-  (w2 ? gx_go<OUT, false, true, true>(q, nullptr, xscale, (int)M, KB, Wp, alpha, (int)N, Y, yb, nullptr, MT, NTB, s) \
-      : gx_go<OUT, false, true, false>(q, nullptr, xscale, (int)M, KB, Wp, alpha, (int)N, Y, yb, nullptr, MT, NTB, s))
+  (w2 ? gx_go<OUT, false, true, true>(q, nullptr, xscale, (int)M, KB, Wp, alpha, (int)N, Y, nullptr, MT, NTB, s) \
+      : gx_go<OUT, false, true, false>(q, nullptr, xscale, (int)M, KB, Wp, alpha, (int)N, Y, nullptr, MT, NTB, s))
   return out == 0 ? GX_CALL4(0) : out == 1 ? GX_CALL4(1) : GX_CALL4(2);
 #undef GX_CALL4
 }

@@ -57,13 +57,13 @@ __device__ __forceinline__ u32 gp_pack_bf16(float lo, float hi) {
   return r;
 }
 
-// OUT: 0 = bf16 rows through the LDS transpose (N % 8 == 0), 1 = 4 outputs per store (N % 4 == 0),
-// 2 = one output per store (any N).  ACC: also write the int32 accumulators (tests).
+// OUT: 0 = bf16 rows through the LDS transpose, 1 = float32, 4 outputs per store (N % 4 == 0), 2 = float32, one
+// output per store (any N).  ACC: also write the int32 accumulators (tests).
 template <int BM, int BN, bool A4, int OUT, bool ACC>
 __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
     const unsigned char* __restrict__ A, const float* __restrict__ scale, int M, int Kp,
     const unsigned char* __restrict__ Wp, const float* __restrict__ alpha_p, int N, void* __restrict__ Y,
-    int y_bf16, int32_t* __restrict__ acc_out, int MT, int NTB) {
+    int32_t* __restrict__ acc_out, int MT, int NTB) {
   constexpr int WM = BM / 2, WN = BN / 2;        // wave tile
   constexpr int TM = WM / 32, TN = WN / 32;      // 32x32 MFMA tiles per wave
   constexpr int PA = A4 ? 4 : 8;                 // 16-byte pieces per activation row per stage
@@ -449,13 +449,21 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
           __builtin_amdgcn_sched_barrier(0);               // (keeps the reads from being paired off with the stores)
 #pragma unroll
           for (int i = 0; i < NPASS; ++i)
-            *reinterpret_cast<v4i*>(ywave + (size_t)(b * 32 + i * ROWS_PER_PASS) * N + lane_off) = v[i];
+            *reinterpret_cast<v4i_align2*>(ywave + (size_t)(b * 32 + i * ROWS_PER_PASS) * N + lane_off) = v[i];
         } else {
 #pragma unroll
           for (int i = 0; i < NPASS; ++i) {
             const int row = b * 32 + i * ROWS_PER_PASS;
-            const uint4 v = *reinterpret_cast<const uint4*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
-            if (row < m_left && 0 < n_left) *reinterpret_cast<uint4*>(ywave + (size_t)row * N + lane_off) = v;
+            const v4i v = *reinterpret_cast<const v4i*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
+            if (row < m_left && n_left >= 8) *reinterpret_cast<v4i_align2*>(ywave + (size_t)row * N + lane_off) = v;
+          }
+          if (N & 7) {                                       // uniform
+#pragma unroll 1
+            for (int i = 0; i < NPASS; ++i) {
+              const int row = b * 32 + i * ROWS_PER_PASS;
+              const v4i v = *reinterpret_cast<const v4i*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
+              if (row < m_left && 0 < n_left && n_left < 8) bl_store_tail8(ywave + (size_t)row * N + lane_off, v, n_left);
+            }
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -475,24 +483,11 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
 #pragma unroll
             for (int r = 0; r < 4; ++r) fv[r] = ((float)acc[a][b][4 * g + r] * d) * alpha;
             if (OUT == 1) {
-              if (m < M && n < N) {
-                if (y_bf16) {
-                  uint2 p;
-                  p.x = gp_pack_bf16(fv[0], fv[1]);
-                  p.y = gp_pack_bf16(fv[2], fv[3]);
-                  *reinterpret_cast<uint2*>((uint16_t*)Y + o) = p;
-                } else {
-                  *reinterpret_cast<float4*>((float*)Y + o) = make_float4(fv[0], fv[1], fv[2], fv[3]);
-                }
-              }
+              if (m < M && n < N) *reinterpret_cast<float4*>((float*)Y + o) = make_float4(fv[0], fv[1], fv[2], fv[3]);
             } else {
 #pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                if (m < M && n + r < N) {
-                  if (y_bf16) ((uint16_t*)Y)[o + r] = bl_f32_to_bf16_rne(fv[r]);
-                  else ((float*)Y)[o + r] = fv[r];
-                }
-              }
+              for (int r = 0; r < 4; ++r)
+                if (m < M && n + r < N) ((float*)Y)[o + r] = fv[r];
             }
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -536,14 +531,14 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
 
 template <int BM, int BN, bool A4, int OUT, bool ACC>
 static int gp_go(const void* q, const float* scale, int M, int Kp, const void* Wp, const float* alpha, int N,
-                 void* Y, int y_bf16, int32_t* acc_out, int MT, int NTB, hipStream_t s) {
+                 void* Y, int32_t* acc_out, int MT, int NTB, hipStream_t s) {
   constexpr int smem = GpSmem<BM, BN>::total;
   BL_SET_MAX_LDS_ONCE((gemm_prefill_kernel<BM, BN, A4, OUT, ACC>), smem);
   // persistent blocks: one per CU for the large tile (128 KB of LDS, 512 registers per lane)
   const int per_cu = (BM == 256) ? 1 : 2;
   const int grid = min(MT * NTB, bl_num_cus() * per_cu);
   gemm_prefill_kernel<BM, BN, A4, OUT, ACC><<<(unsigned)grid, GP_THREADS, smem, s>>>(
-      (const unsigned char*)q, scale, M, Kp, (const unsigned char*)Wp, alpha, N, Y, y_bf16, acc_out, MT, NTB);
+      (const unsigned char*)q, scale, M, Kp, (const unsigned char*)Wp, alpha, N, Y, acc_out, MT, NTB);
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
 }
@@ -553,9 +548,8 @@ static int gp_launch(const void* q, const float* scale, int M, int Kp, const voi
                      const float* alpha, int N, void* Y, bl_dtype ydt, int32_t* acc_out,
                      hipStream_t s) {
   const int MT = (M + BM - 1) / BM, NTB = (N + BN - 1) / BN;
-  const int out = (ydt == BL_BF16 && (N & 7) == 0) ? 0 : ((N & 3) == 0 ? 1 : 2);
-  const int yb = ydt == BL_BF16 ? 1 : 0;
-#define GP_CALL(OUT, ACC) gp_go<BM, BN, A4, OUT, ACC>(q, scale, M, Kp, Wp, alpha, N, Y, yb, acc_out, MT, NTB, s)
+  const int out = ydt == BL_BF16 ? 0 : ((N & 3) == 0 ? 1 : 2);
+#define GP_CALL(OUT, ACC) gp_go<BM, BN, A4, OUT, ACC>(q, scale, M, Kp, Wp, alpha, N, Y, acc_out, MT, NTB, s)
   if (acc_out) return out == 0 ? GP_CALL(0, true) : out == 1 ? GP_CALL(1, true) : GP_CALL(2, true);
   return out == 0 ? GP_CALL(0, false) : out == 1 ? GP_CALL(1, false) : GP_CALL(2, false);
 #undef GP_CALL
