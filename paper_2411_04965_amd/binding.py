@@ -94,8 +94,13 @@ def _check(fn, status):
         raise BitlinearError(fn, status)
 
 
+# torch.cuda.current_stream() builds a Stream object: 2.7 us of the 8.1 us that a one-token linear took on the host.
+# The raw handle of the same stream takes 0.1 us.
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dt(t):
