@@ -504,7 +504,7 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
           for (int g = 0; g < 4; ++g) {
             const int n = n0 + wn * WN + a * 32 + 8 * g + 4 * lh;
             const size_t o = (size_t)m * N + n;
-            if (OUT != 2) {
+            if ((N & 3) == 0) {                            // (other rows: a quad may run past its end, and is not aligned)
               if (m < M && n < N)
                 *reinterpret_cast<int4*>(acc_out + o) =
                     make_int4(acc[a][b][4 * g] >> SHIFT, acc[a][b][4 * g + 1] >> SHIFT,

@@ -34,3 +34,46 @@ def test_rows_of_any_length(M, N, K):
     p, a = pack(W)
     ref8 = O.bitlinear_a8_sparse(X, W, K // 2, EPS, "bf16")["y"]
     assert np.array_equal(host(B.bitlinear_a8_sparse(Xd, K // 2, p, a, N, EPS)), ref8)
+
+
+def product(X, W, mode, topk=0):
+    """The product stage on codes from the library's own quantizers (which have their own tests), in plain torch: integer
+    sums are below 2^24 and so exact in float32."""
+    M, K = X.shape
+    p, a = B.pack_ternary(W)
+    qa = B.quantize_act(X, mode, topk=topk)
+    acc = B.unpack_act(qa["q"], mode, M, K).float() @ B.unpack_ternary(p, W.shape[0], K).float().T
+    return acc, (acc * qa["scale"][:, None]) * a
+
+
+# (tokens, outputs, channels) that reach each tile of the many-token GEMMs on 256 CUs, with ragged edges, one K step (fewer
+# than K groups), odd and even numbers of steps: 64 x 64, 64 x 128 with one and two K groups, 128 x 128, 256 x 256
+TILES = [(65, 63, 200), (191, 1021, 257), (130, 516, 700), (449, 3211, 1025), (833, 2045, 300), (641, 4091, 520), (1153, 2052, 777),
+         (4090, 4091, 300), (4097, 4100, 520), (2900, 6141, 256)]
+
+
+@pytest.mark.parametrize("M,N,K", TILES)
+def test_tiles(M, N, K):
+    """Every tile and number format, bfloat16 and float32 outputs and accumulators, bit for bit."""
+    print("[case] tiles M=%d N=%d K=%d" % (M, N, K), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    X = torch.randn((M, K), generator=g, device="cuda").to(BF16)
+    W = 0.02 * torch.randn((N, K), generator=g, device="cuda")
+    Wu = 0.02 * torch.randn((N, K), generator=g, device="cuda")
+    acc8, y8 = product(X, W, B.BL_ACT_TOPK_INT8_ABSMAX, K // 2)
+    acc4, y4 = product(X, W, B.BL_ACT_INT4_ABSMEAN)
+    u4 = product(X, Wu, B.BL_ACT_INT4_ABSMEAN)[1]
+    p, a = B.pack_ternary(W)
+    assert torch.equal(B.bitlinear_a8_sparse(X, K // 2, p, a, N), y8.to(BF16))
+    y, acc = B.bitlinear_a8_sparse(X, K // 2, p, a, N, y_dtype=torch.float32, want_acc=True)
+    assert torch.equal(y, y8) and torch.equal(acc, acc8.int())
+    assert torch.equal(B.bitlinear_a4(X, p, a, N), y4.to(BF16))
+    y, acc = B.bitlinear_a4(X, p, a, N, want_acc=True)
+    assert torch.equal(y, y4.to(BF16)) and torch.equal(acc, acc4.int())
+    p, a = B.pack_ternary(W, layout=B.BL_W_MX2)
+    pu, au = B.pack_ternary(Wu, layout=B.BL_W_MX2)
+    assert torch.equal(B.bitlinear_a4(X, p, a, N, layout=B.BL_W_MX2), y4.to(BF16))
+    y, acc = B.bitlinear_a4(X, p, a, N, layout=B.BL_W_MX2, y_dtype=torch.float32, want_acc=True)
+    assert torch.equal(y, y4) and torch.equal(acc, acc4.int())
+    h = B.bitlinear_a4_gate_up(X, p, a, pu, au, N, layout=B.BL_W_MX2, want=("H",))["H"]
+    assert torch.equal(h, (u4 * y4.clamp_min(0.0).square()).to(BF16))
