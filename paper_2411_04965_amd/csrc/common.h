@@ -53,6 +53,11 @@ __device__ __forceinline__ uint16_t bl_f32_to_bf16_rne(float f) {
   u32 lsb = (u >> 16) & 1u;
   return (uint16_t)((u + 0x7FFFu + lsb) >> 16);   // finite inputs only
 }
+__device__ __forceinline__ u32 bl_pack_bf16(float lo, float hi) {
+  u32 r;
+  asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(lo), "v"(hi));
+  return r;
+}
 
 // 16-byte stores to output rows of any length: the hardware takes global stores at any 2-byte alignment, so only
 // a row's last piece (rows of a length that is no multiple of 8) goes by elements.  (Stores of one bfloat16 each bound
@@ -148,6 +153,15 @@ int bl_launch_gemm_decode(const void* q, const float* scale, bl_act_mode mode, i
                           int64_t K, const void* Wp, const float* alpha, int64_t N, void* Y,
                           bl_dtype ydt, int32_t* acc_out, void* ws, hipStream_t s);
 size_t bl_gemm_decode_ws_bytes(int64_t M, int64_t N, int64_t K);
+// smaller tiles for a few hundred to a few thousand tokens (gemm_mid.hip)
+bool bl_gemm_mid_ok(int64_t M, int64_t N);
+int bl_launch_gemm_mid(const void* q, const float* scale, bl_act_mode mode, int64_t M, int64_t K, const void* Wp,
+                       const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);
+bool bl_gemm_mid_mx_ok(int64_t M, int64_t n_cols);
+int bl_launch_gemm_mid_mx(const void* q, const float* scale, int64_t M, int64_t K, const void* Wp, const float* alpha,
+                          int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);
+int bl_launch_gemm_mid_mx_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,
+                              const void* Wu, const float* au, int64_t N, void* H, hipStream_t s);
 bool bl_gemv_a4_fused_ok(int64_t M, int64_t N, int64_t K);
 int bl_launch_up_gated(const void* X, int64_t M, int64_t K, float eps, const void* Wr, const float* alpha,
                        int64_t N, const void* G, bl_dtype gdt, void* H, hipStream_t s);

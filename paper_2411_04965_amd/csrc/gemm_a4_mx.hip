@@ -56,12 +56,6 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v6i __attribute__((ext_vector_type(6)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ u32 gx_pack_bf16(float lo, float hi) {
-  u32 r;
-  asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(lo), "v"(hi));
-  return r;
-}
-
 // OUT: 0 = bf16 rows through the LDS transpose, 1 = float32, 4 outputs per store (N % 4 == 0), 2 = float32, one
 // output per store (any N).  ACC: also write the integer accumulators (tests).
 // FP4: the activations are E2M1 codes with one E8M0 scale per token and 32 channels (eq. 8-9)
@@ -459,8 +453,8 @@ __global__ __launch_bounds__(GX_THREADS, 1) void gemm_a4_mx_kernel(
                 hv[r] = u * rr2;
               }
               uint2 p;
-              p.x = gx_pack_bf16(hv[0], hv[1]);
-              p.y = gx_pack_bf16(hv[2], hv[3]);
+              p.x = bl_pack_bf16(hv[0], hv[1]);
+              p.y = bl_pack_bf16(hv[2], hv[3]);
               *reinterpret_cast<uint2*>(tbuf + l32 * TB_ROW + (a * 32 + 8 * q4 + 4 * lh) * 2) = p;
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -505,8 +499,8 @@ __global__ __launch_bounds__(GX_THREADS, 1) void gemm_a4_mx_kernel(
 #pragma unroll
             for (int r = 0; r < 4; ++r) fv[r] = (acc[a][b][4 * q4 + r] * d) * alpha;
             uint2 p;
-            p.x = gx_pack_bf16(fv[0], fv[1]);
-            p.y = gx_pack_bf16(fv[2], fv[3]);
+            p.x = bl_pack_bf16(fv[0], fv[1]);
+            p.y = bl_pack_bf16(fv[2], fv[3]);
             *reinterpret_cast<uint2*>(tbuf + l32 * TB_ROW + (a * 32 + 8 * q4 + 4 * lh) * 2) = p;
           }
           __builtin_amdgcn_sched_barrier(0);

@@ -9,6 +9,8 @@
 // two and is folded exactly into the per-token scale in the epilogue.
 // |1024 * acc| <= 8 * K * 1024 < 2^31 for K <= 32768.
 //
+// For problems with enough 256 x 256 tiles; the others take gemm_mid.hip.
+//
 // Structure.  Persistent blocks (one per CU) walk the tile list.  Block = 4 waves, tile
 // BM x BN, each wave (BM/2) x (BN/2) as 32x32 MFMA tiles; the MFMA's row operand is the weight
 // fragment and its column operand the token fragment, so a lane ends up with groups of 4
@@ -49,12 +51,6 @@ __device__ __forceinline__ int gp_lds_off(int row, int chunk) {
   // 16 lanes of a 16-byte access must fall into distinct 16-byte slots of a 256-byte window:
   // two rows per window, so the row's parity picks the half and (row / 2) % 8 permutes the chunks
   return row * GP_BK + ((chunk ^ ((row >> 1) & 7)) << 4);
-}
-
-__device__ __forceinline__ u32 gp_pack_bf16(float lo, float hi) {
-  u32 r;
-  asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(lo), "v"(hi));
-  return r;
 }
 
 // OUT: 0 = bf16 rows through the LDS transpose, 1 = float32, 4 outputs per store (N % 4 == 0), 2 = float32, one
@@ -192,7 +188,7 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
   // GP_PIN_OUT uses the results (they cannot be computed later).
 #define GP_PIN_IN(x) asm volatile("" : "+v"(x))
 #define GP_PIN_OUT(x, y) asm volatile("" ::"v"(x), "v"(y))
-  static_assert(TM == TN && (TN == 2 || TN == 4), "the interleaving below assumes a square wave tile");
+  static_assert(TM == 4 && TN == 4, "the interleaving below assumes a 128 x 128 wave tile");
   constexpr int ROWS = 2 * TN;                   // MFMA rows (one weight fragment each) per half step
   static_assert(NWR_A == ROWS && NWR_B == ROWS, "one A write and one B write per MFMA row");
   constexpr int A_EVERY = ROWS / LA, B_EVERY = ROWS / LB;
@@ -299,21 +295,20 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
 #pragma unroll
             for (int b = 0; b < TM; ++b) {
               GP_MFMA(acc[a][b], wF[sub][a], xF[sub][b]);
-              // slots behind MFMA b of this row (4 per row; a 2-MFMA row takes two at a time)
-              const int s0 = (TM == 4) ? b : 2 * b, s1 = (TM == 4) ? b : 2 * b + 1;
-              if (s0 == 0) {
+              // slots behind MFMA b of this row (4 per row)
+              if (b == 0) {
                 xS[sub][a] = read_x(stage, 2 + sub, a);
                 wS[sub][a] = read_w(stage, 2 + sub, a);
               }
-              if (s0 <= 1 && 1 <= s1) {
+              if (b == 1) {
                 if (hrow > 0) store_b(st_other, hrow - 1, cw_prev);
               }
-              if (s0 <= 2 && 2 <= s1) {
+              if (b == 2) {
                 GP_PIN_IN(w);
                 cw.x = (w << 6) & MB; cw.y = (w << 4) & MB;
                 GP_PIN_OUT(cw.x, cw.y);
               }
-              if (s0 <= 3 && 3 <= s1) {
+              if (b == 3) {
                 GP_PIN_IN(w);
                 cw.z = (w << 2) & MB; cw.w = w & MB;
                 GP_PIN_OUT(cw.z, cw.w);
@@ -347,26 +342,25 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
 #pragma unroll
             for (int b = 0; b < TM; ++b) {
               GP_MFMA(acc[a][b], wS[sub][a], xS[sub][b]);
-              const int s0 = (TM == 4) ? b : 2 * b, s1 = (TM == 4) ? b : 2 * b + 1;
-              if (s0 == 0) {
+              if (b == 0) {
                 xF[sub][a] = read_x(stage ^ 1, sub, a);
                 wF[sub][a] = read_w(stage ^ 1, sub, a);
               }
-              if (s0 <= 1 && 1 <= s1) {
+              if (b == 1) {
                 if (A4) {
                   if (hrow > 0) store_a(st_own, hrow - 1, cx_prev);
                 } else {                          // INT8: a plain copy, nothing to wait for
                   store_a(st_own, hrow, make_uint4(a_reg[hrow].x, a_reg[hrow].y, a_reg[hrow].z, a_reg[hrow].w));
                 }
               }
-              if (s0 <= 2 && 2 <= s1) {
+              if (b == 2) {
                 if (A4) {
                   GP_PIN_IN(x0);
                   cx.x = (x0 << 4) & MA; cx.y = x0 & MA;
                   GP_PIN_OUT(cx.x, cx.y);
                 }
               }
-              if (s0 <= 3 && 3 <= s1) {
+              if (b == 3) {
                 if (A4) {
                   GP_PIN_IN(x1);
                   cx.z = (x1 << 4) & MA; cx.w = x1 & MA;
@@ -430,8 +424,8 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
 #pragma unroll
             for (int r = 0; r < 4; ++r) fv[r] = ((float)acc[a][b][4 * g + r] * d) * alpha;
             uint2 p;
-            p.x = gp_pack_bf16(fv[0], fv[1]);
-            p.y = gp_pack_bf16(fv[2], fv[3]);
+            p.x = bl_pack_bf16(fv[0], fv[1]);
+            p.y = bl_pack_bf16(fv[2], fv[3]);
             *reinterpret_cast<uint2*>(tbuf + l32 * TB_ROW + (a * 32 + 8 * g + 4 * lh) * 2) = p;
           }
           // keep the scheduler from reading many accumulators ahead of their use: the next
@@ -534,9 +528,8 @@ static int gp_go(const void* q, const float* scale, int M, int Kp, const void* W
                  void* Y, int32_t* acc_out, int MT, int NTB, hipStream_t s) {
   constexpr int smem = GpSmem<BM, BN>::total;
   BL_SET_MAX_LDS_ONCE((gemm_prefill_kernel<BM, BN, A4, OUT, ACC>), smem);
-  // persistent blocks: one per CU for the large tile (128 KB of LDS, 512 registers per lane)
-  const int per_cu = (BM == 256) ? 1 : 2;
-  const int grid = min(MT * NTB, bl_num_cus() * per_cu);
+  // persistent blocks: one per CU (128 KB of LDS, 512 registers per lane)
+  const int grid = min(MT * NTB, bl_num_cus());
   gemm_prefill_kernel<BM, BN, A4, OUT, ACC><<<(unsigned)grid, GP_THREADS, smem, s>>>(
       (const unsigned char*)q, scale, M, Kp, (const unsigned char*)Wp, alpha, N, Y, acc_out, MT, NTB);
   BL_HIP_CHECK_LAUNCH();
@@ -560,12 +553,6 @@ int bl_launch_gemm_prefill(const void* q, const float* scale, bl_act_mode mode, 
                            bl_dtype ydt, int32_t* acc_out, hipStream_t s) {
   const int Kp = (int)bl_round_up(K, BL_KPAD);
   const bool a4 = mode == BL_ACT_INT4_ABSMEAN;
-  // Large problems take 256 x 256 tiles; small ones 128 x 128 so that the grid still covers the chip.
-  const bool big = (M >= 1024 && N >= 1024);
-  if (a4) {
-    if (big) return gp_launch<256, 256, true>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s);
-    return gp_launch<128, 128, true>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s);
-  }
-  if (big) return gp_launch<256, 256, false>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s);
-  return gp_launch<128, 128, false>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s);
+  if (a4) return gp_launch<256, 256, true>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s);
+  return gp_launch<256, 256, false>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s);
 }
