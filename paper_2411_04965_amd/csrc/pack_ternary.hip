@@ -3,6 +3,10 @@
 // Two kernels: a float64 partial-sum reduction of |W|, then ternarise + pack.  Every block of
 // the second kernel re-adds the partial sums in one fixed order, so alpha is identical in all
 // blocks and from run to run.
+//
+// Both are bound by reading W (float32 9600 x 3200: 123 MB, 24 us at the 5.1 TB/s of a plain copy).  So loads are
+// 16 bytes per lane and several are in flight, and the ternary code of a weight is a comparison, not the division of
+// eq. 2 (pt_ternary_bits).
 #include "common.h"
 
 #define PT_THREADS 256
@@ -14,15 +18,45 @@ template <> __device__ __forceinline__ float pt_load<uint16_t>(const uint16_t* p
   return bl_bf16_to_f32(p[i]);
 }
 
+// Four consecutive elements at a multiple of their size.
+__device__ __forceinline__ void pt_load4(const float* p, int64_t i, float (&v)[4]) {
+  const float4 x = *reinterpret_cast<const float4*>(p + i);
+  v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+}
+__device__ __forceinline__ void pt_load4(const uint16_t* p, int64_t i, float (&v)[4]) {
+  const uint2 x = *reinterpret_cast<const uint2*>(p + i);
+  v[0] = __uint_as_float(x.x << 16); v[1] = __uint_as_float(x.x & 0xFFFF0000u);
+  v[2] = __uint_as_float(x.y << 16); v[3] = __uint_as_float(x.y & 0xFFFF0000u);
+}
+
+// One load of an element per turn, as the loop was, kept too little in flight: 9600 x 3200 38 us alone.
 template <typename T>
 __global__ __launch_bounds__(PT_THREADS) void abs_sum_partial_kernel(const T* __restrict__ W,
                                                                      int64_t n,
                                                                      double* __restrict__ partial) {
   __shared__ double red[PT_THREADS / BL_WAVE];
-  double acc = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * PT_THREADS + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * PT_THREADS)
-    acc += (double)fabsf(pt_load<T>(W, i));
+  const int64_t step = (int64_t)gridDim.x * PT_THREADS, first = (int64_t)blockIdx.x * PT_THREADS + threadIdx.x;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  const int64_t n4 = n >> 2;                // (W is 16-byte aligned: checked at the entry point)
+  constexpr int U = 4;
+  int64_t i = first;
+  for (; i + (U - 1) * step < n4; i += U * step) {
+    float v[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) pt_load4(W, 4 * (i + u * step), v[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] += (double)fabsf(v[u][e]);
+  }
+  for (; i < n4; i += step) {
+    float v[4];
+    pt_load4(W, 4 * i, v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] += (double)fabsf(v[e]);
+  }
+  for (int64_t j = 4 * n4 + first; j < n; j += step) a[0] += (double)fabsf(pt_load<T>(W, j));
+  double acc = (a[0] + a[1]) + (a[2] + a[3]);
   acc = bl_wave_sum_f64(acc);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
@@ -34,15 +68,17 @@ __global__ __launch_bounds__(PT_THREADS) void abs_sum_partial_kernel(const T* __
 }
 
 // alpha from the partial sums, same order in every block.
+template <int THREADS = PT_THREADS>
 __device__ __forceinline__ float pt_alpha(const double* __restrict__ partial, int n_partial,
                                           int64_t n_elem, double* red) {
   double acc = 0.0;
-  for (int i = threadIdx.x; i < n_partial; i += PT_THREADS) acc += partial[i];
+  if (THREADS == PT_THREADS || threadIdx.x < PT_THREADS)     // (the same order in every layout's kernel)
+    for (int i = threadIdx.x; i < n_partial; i += PT_THREADS) acc += partial[i];
   acc = bl_wave_sum_f64(acc);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
   double s = 0.0;
-  for (int w = 0; w < PT_THREADS / BL_WAVE; ++w) s += red[w];
+  for (int w = 0; w < THREADS / BL_WAVE; ++w) s += red[w];
   return (float)(s / (double)n_elem);
 }
 
@@ -52,61 +88,128 @@ __device__ __forceinline__ u32 pt_code(float w, float t) {
   int c = (int)r;                          // -1, 0, 1
   return (u32)c & 3u;                      // two's complement 2-bit: 00, 01, 11
 }
+// The same code by comparison.  The rounded quotient is 0 unless |w| / t, rounded to float32, exceeds 0.5, that is
+// unless |w| > t/2 + t 2^-25 (a quotient nearer to 0.5 rounds to 0.5, whose mantissa is even).  t/2 is a float32 here,
+// and the next float32 above it exceeds it by at least t 2^-24: for a float32 |w| the condition is |w| > t/2.
+// Wants a finite t, which says that every weight is finite, and t/2 free of rounding (t well above the subnormals).
+__device__ __forceinline__ u32 pt_ternary_bits(float w, float half) {
+  const u32 u = __float_as_uint(w);
+  return (u & 0x7FFFFFFFu) > __float_as_uint(half) ? 1u | ((u >> 30) & 2u) : 0u;
+}
+__device__ __forceinline__ bool pt_compare_ok(float t) { return t >= 0x1p-100f && t <= 0x1p100f; }
 
-// One thread per 32-bit word of the tiled GEMM layout: output channel n, 16 input channels.
-template <typename T>
-__global__ __launch_bounds__(PT_THREADS) void ternarize_pack_gemm_kernel(
-    const T* __restrict__ W, int64_t N, int64_t K, int64_t Kp, float eps,
-    const double* __restrict__ partial, int n_partial, u32* __restrict__ out,
-    float* __restrict__ alpha_out, int64_t n_words) {
-  __shared__ double red[PT_THREADS / BL_WAVE];
-  const float alpha = pt_alpha(partial, n_partial, N * K, red);
-  if (blockIdx.x == 0 && threadIdx.x == 0) alpha_out[0] = alpha;
-  const float t = alpha + eps;
-  const int64_t w = (int64_t)blockIdx.x * PT_THREADS + threadIdx.x;
-  if (w >= n_words) return;
-  const int64_t tile = w >> 8;              // 256 words per 1 KB tile
-  const int in_tile = (int)(w & 255);
-  const int word_t = in_tile & 3;
-  const int i = (in_tile >> 2) & 15;
-  const int g = in_tile >> 6;
-  const int64_t k_tiles = Kp / 256;
-  const int64_t nt = tile / k_tiles, kt = tile % k_tiles;
-  const int64_t n = nt * 16 + i;
-  const int64_t k0 = kt * 256 + g * 64 + word_t * 16;
-  u32 word = 0;
-  if (n < N) {
-#pragma unroll
-    for (int f = 0; f < 16; ++f) {
-      const int64_t k = k0 + 4 * (f & 3) + (f >> 2);
-      if (k < K) word |= pt_code(pt_load<T>(W, n * K + k), t) << (2 * f);
-    }
+// body(code): code(w) is the ternary code of a weight.
+template <typename Body>
+__device__ __forceinline__ void pt_with_code(float t, Body body) {
+  if (pt_compare_ok(t)) {
+    const float half = 0.5f * t;
+    body([=](float w) { return pt_ternary_bits(w, half); });
+  } else {
+    body([=](float w) { return pt_code(w, t); });
   }
-  out[w] = word;
 }
 
-// One thread per 32-bit word of the input-channel-major layout (column blocks of 512 outputs,
-// 128 bytes per channel and block): channel k, 16 outputs.  Consecutive threads take
-// consecutive k so that reads of W are coalesced.
+// Tiled GEMM layout: a wave ternarises 4 output rows x 256 input channels (a quarter of a tile), 4 rows of 4 consecutive
+// channels per lane, so that a wave reads whole rows of 1 KB.  Channel c of a word sits in field 4 (c % 4) + c / 4: the four
+// lanes of a word hold disjoint fields, which two exchanges inside the quad put together; lane q of the quad then
+// stores the word of row q (64-byte runs).  One thread per word with 16 loads of 4 bytes, 64 bytes apart between lanes,
+// as it was: 9600 x 3200 99 us.
 template <typename T>
-__global__ __launch_bounds__(PT_THREADS) void ternarize_pack_kmajor_kernel(
-    const T* __restrict__ W, int64_t N, int64_t K, int64_t Np, float eps,
+__global__ __launch_bounds__(PT_THREADS) void ternarize_pack_gemm_kernel(
+    const T* __restrict__ W, int64_t N, int64_t K, int64_t Kp, float eps, int vec,
     const double* __restrict__ partial, int n_partial, u32* __restrict__ out,
-    float* __restrict__ alpha_out, int64_t n_words) {
+    float* __restrict__ alpha_out, int64_t n_tiles) {
   __shared__ double red[PT_THREADS / BL_WAVE];
   const float alpha = pt_alpha(partial, n_partial, N * K, red);
   if (blockIdx.x == 0 && threadIdx.x == 0) alpha_out[0] = alpha;
   const float t = alpha + eps;
-  const int64_t id = (int64_t)blockIdx.x * PT_THREADS + threadIdx.x;
-  if (id >= n_words) return;
-  const int64_t k = id % K, d = id / K;
-  u32 word = 0;
+  const int lane = threadIdx.x & 63, i0 = (threadIdx.x >> 6) * 4;   // rows i0 ... i0 + 3 of the tile
+  const int q = lane & 3, g = lane >> 4, wt = (lane >> 2) & 3;
+  const int64_t k_tiles = Kp / 256;
+  pt_with_code(t, [&](auto code) {
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+      const int64_t nt = tile / k_tiles, kt = tile - nt * k_tiles;
+      const int64_t n0 = nt * 16 + i0, k = kt * 256 + 4 * lane;
+      float v[4][4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[r][e] = 0.0f;       // (code 0 either way)
+        if (n0 + r < N) {
+          if (vec) {
+            if (k < K) pt_load4(W, (n0 + r) * K + k, v[r]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (k + e < K) v[r][e] = pt_load<T>(W, (n0 + r) * K + k + e);
+          }
+        }
+      }
+      u32 mine = 0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        u32 w = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool pad = !(n0 + r < N && k + e < K);
+          w |= (pad ? 0u : code(v[r][e])) << (2 * (4 * e + q));
+        }
+        w |= (u32)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xF, 0xF, true);   // quad_perm [1, 0, 3, 2]
+        w |= (u32)__builtin_amdgcn_mov_dpp((int)w, 0x4E, 0xF, 0xF, true);   // quad_perm [2, 3, 0, 1]
+        if (r == q) mine = w;
+      }
+      out[tile * 256 + (g * 16 + i0 + q) * 4 + wt] = mine;
+    }
+  });
+}
+
+// Input-channel-major layout (column blocks of 512 outputs, 128 bytes per channel and block): a workgroup takes 64
+// channels of one column block, a thread 4 of the channels and the 16 outputs of a word (16 loads of 16 bytes in flight, 256-byte
+// runs of a row of W per 16 lanes); the words meet in LDS and leave as one run of 8 KB.  One thread per word and
+// each word stored where it falls, 128 bytes apart between lanes, as it was: 9600 x 3200 46 us.
+#define PT_KM_THREADS 512
+template <typename T>
+__global__ __launch_bounds__(PT_KM_THREADS) void ternarize_pack_kmajor_kernel(
+    const T* __restrict__ W, int64_t N, int64_t K, float eps, int vec,
+    const double* __restrict__ partial, int n_partial, u32* __restrict__ out,
+    float* __restrict__ alpha_out, int64_t k_blocks) {
+  __shared__ double red[PT_KM_THREADS / BL_WAVE];
+  __shared__ u32 words[64 * 33];
+  const int64_t cb = blockIdx.x / k_blocks, k0 = (blockIdx.x - cb * k_blocks) * 64;
+  const int c4 = (threadIdx.x & 15) * 4, d = threadIdx.x >> 4;          // channels k0 + c4 ... + 3, word d of 32
+  const int64_t k = k0 + c4, n0 = cb * 512 + d * 16;
+  float v[16][4];
 #pragma unroll
   for (int f = 0; f < 16; ++f) {
-    const int64_t n = d * 16 + f;
-    if (n < N) word |= pt_code(pt_load<T>(W, n * K + k), t) << (2 * f);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[f][e] = 0.0f;
+    if (n0 + f < N) {
+      if (vec) {
+        if (k < K) pt_load4(W, (n0 + f) * K + k, v[f]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (k + e < K) v[f][e] = pt_load<T>(W, (n0 + f) * K + k + e);
+      }
+    }
   }
-  out[((d >> 5) * K + k) * 32 + (d & 31)] = word;
+  const float alpha = pt_alpha<PT_KM_THREADS>(partial, n_partial, N * K, red);
+  if (blockIdx.x == 0 && threadIdx.x == 0) alpha_out[0] = alpha;
+  pt_with_code(alpha + eps, [&](auto code) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      u32 word = 0;
+#pragma unroll
+      for (int f = 0; f < 16; ++f)
+        if (n0 + f < N) word |= code(v[f][e]) << (2 * f);
+      words[(c4 + e) * 33 + d] = word;
+    }
+  });
+  __syncthreads();
+  u32* dst = out + (cb * K + k0) * 32;
+#pragma unroll
+  for (int i = threadIdx.x; i < 64 * 32; i += PT_KM_THREADS)
+    if (k0 + (i >> 5) < K) dst[i] = words[(i >> 5) * 33 + (i & 31)];
 }
 
 // One thread per 32-bit word of the block-float GEMM layout: blocks of 32 outputs x 128 input
@@ -131,16 +234,17 @@ __global__ __launch_bounds__(PT_THREADS) void ternarize_pack_mx4_kernel(
   const int64_t n = (blk / KB) * 32 + r;
   const int64_t k0 = (blk % KB) * 128 + 32 * (p ^ ((r >> 2) & 3)) + 8 * j;
   u32 word = 0;
-  if (n < N) {
+  pt_with_code(t, [&](auto code) {
+    if (n >= N) return;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int64_t k = k0 + i;
       if (k < K) {
-        const u32 c = pt_code(pt_load<T>(W, n * K + k), t);        // 00, 01, 11
+        const u32 c = code(pt_load<T>(W, n * K + k));        // 00, 01, 11
         word |= (((c & 2u) << 2) | ((c & 1u) << 1)) << (4 * i);    // sign to bit 3, magnitude 1.0 = 010
       }
     }
-  }
+  });
   out[w] = word;
 }
 
@@ -167,19 +271,20 @@ __global__ __launch_bounds__(PT_THREADS) void ternarize_pack_mx2_kernel(
   const int64_t n = (blk / KB) * 32 + r;
   const int64_t k0 = (blk % KB) * 128 + 32 * (p ^ ((r >> 3) & 3)) + 16 * h;
   u32 word = 0;
-  if (n < N) {
+  pt_with_code(t, [&](auto code) {
+    if (n >= N) return;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       if (k0 + j < K) {
-        const u32 c = pt_code(pt_load<T>(W, n * K + k0 + j), t);            // 00, 01, 11
+        const u32 c = code(pt_load<T>(W, n * K + k0 + j));            // 00, 01, 11
         word |= (((c & 2u) << 2) | ((c & 1u) << 1)) << (4 * j);
       }
       if (k0 + 8 + j < K) {
-        const u32 c = pt_code(pt_load<T>(W, n * K + k0 + 8 + j), t);
+        const u32 c = code(pt_load<T>(W, n * K + k0 + 8 + j));
         word |= (((c & 2u) << 1) | (c & 1u)) << (4 * j);
       }
     }
-  }
+  });
   out[w] = word;
 }
 
@@ -198,9 +303,11 @@ __global__ __launch_bounds__(PT_THREADS) void ternarize_pack_rows_kernel(
   if (w >= n_words) return;
   const int64_t wpr = Kp / 16, n = w / wpr, k0 = (w % wpr) * 16;
   u32 word = 0;
+  pt_with_code(t, [&](auto code) {
 #pragma unroll
-  for (int f = 0; f < 16; ++f)
-    if (k0 + f < K) word |= pt_code(pt_load<T>(W, n * K + k0 + f), t) << (2 * f);
+    for (int f = 0; f < 16; ++f)
+      if (k0 + f < K) word |= code(pt_load<T>(W, n * K + k0 + f)) << (2 * f);
+  });
   out[w] = word;
 }
 
@@ -262,6 +369,7 @@ static int pt_run(const T* W, int64_t N, int64_t K, float eps, bl_w_layout layou
   const int64_t n = N * K;
   const int np = pt_num_partials(n);
   double* partial = (double*)ws;
+  const int vec = K % 4 == 0 ? 1 : 0;              // rows of whole, aligned groups of four
   abs_sum_partial_kernel<T><<<np, PT_THREADS, 0, s>>>(W, n, partial);
   BL_HIP_CHECK_LAUNCH();
   if (layout == BL_W_MX4) {
@@ -283,17 +391,16 @@ static int pt_run(const T* W, int64_t N, int64_t K, float eps, bl_w_layout layou
     ternarize_pack_rows_kernel<T><<<(unsigned)blocks, PT_THREADS, 0, s>>>(
         W, N, K, Kp, eps, partial, np, (u32*)out, alpha, n_words);
   } else if (layout == BL_W_GEMM) {
-    const int64_t Kp = bl_round_up(K, BL_KPAD), Np = bl_round_up(N, 16);
-    const int64_t n_words = Np * Kp / 16;
-    const int64_t blocks = (n_words + PT_THREADS - 1) / PT_THREADS;
+    const int64_t Kp = bl_round_up(K, BL_KPAD);
+    const int64_t n_tiles = bl_round_up(N, 16) / 16 * (Kp / 256);
+    // (8 workgroups per CU: each adds the partial sums once for all its tiles)
+    const int64_t blocks = n_tiles < 8 * (int64_t)bl_num_cus() ? n_tiles : 8 * (int64_t)bl_num_cus();
     ternarize_pack_gemm_kernel<T><<<(unsigned)blocks, PT_THREADS, 0, s>>>(
-        W, N, K, Kp, eps, partial, np, (u32*)out, alpha, n_words);
+        W, N, K, Kp, eps, vec, partial, np, (u32*)out, alpha, n_tiles);
   } else {
-    const int64_t Np = bl_round_up(N, 512);
-    const int64_t n_words = K * (Np / 16);
-    const int64_t blocks = (n_words + PT_THREADS - 1) / PT_THREADS;
-    ternarize_pack_kmajor_kernel<T><<<(unsigned)blocks, PT_THREADS, 0, s>>>(
-        W, N, K, Np, eps, partial, np, (u32*)out, alpha, n_words);
+    const int64_t k_blocks = (K + 63) / 64, blocks = bl_round_up(N, 512) / 512 * k_blocks;
+    ternarize_pack_kmajor_kernel<T><<<(unsigned)blocks, PT_KM_THREADS, 0, s>>>(
+        W, N, K, eps, vec, partial, np, (u32*)out, alpha, k_blocks);
   }
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
