@@ -183,7 +183,7 @@ extern "C" int quantize_heads(const void* X, bl_dtype x_dtype, int64_t T, int64_
   // the kernels take 4 or 16 heads per workgroup: bound the grid by the smaller
   if (!bl_grid_ok((T * H + 3) / 4)) return BL_ESHAPE;
   if (!bl_aligned16(X) || !bl_aligned16(q_out)) return BL_EALIGN;
-  return bl_launch_quantize_heads(X, x_dtype, T * H, D, bits, eps, q_out, scale_out, (hipStream_t)stream);
+  return bl_launch_quantize_heads(X, x_dtype, T * H, 0, D, bits, eps, q_out, scale_out, (hipStream_t)stream);
 }
 
 extern "C" int dequantize_heads(const void* q, const float* scale, int64_t T, int64_t H, int64_t D, int bits,
@@ -195,7 +195,7 @@ extern "C" int dequantize_heads(const void* q, const float* scale, int64_t T, in
   const int64_t lim = (int64_t)1 << 40;
   if (T > lim / H || T * H > lim / D) return BL_ESHAPE;
   if (!bl_aligned16(out)) return BL_EALIGN;
-  return bl_launch_dequantize_heads(q, scale, T * H, D, bits, out, out_dtype, (hipStream_t)stream);
+  return bl_launch_dequantize_heads(q, scale, T * H, 0, D, bits, out, out_dtype, (hipStream_t)stream);
 }
 
 // The 3-bit key / value cache with the first token's heads at 4 bits (Table 3): byte offset of the
@@ -226,19 +226,9 @@ extern "C" int kv_cache_append(const void* X, bl_dtype x_dtype, int64_t T, int64
   int rc = kv_check(T, H, D, pos0);
   if (rc) return rc;
   if (!bl_aligned16(X) || !bl_aligned16(cache)) return BL_EALIGN;
-  const size_t esz = x_dtype == BL_BF16 ? 2 : 4;
-  const unsigned char* x = (const unsigned char*)X;
-  unsigned char* c = (unsigned char*)cache;
-  int64_t t = 0;
-  if (pos0 == 0) {                                         // the sequence's first token: 4 bits
-    rc = bl_launch_quantize_heads(x, x_dtype, H, D, 4, eps, c, scales, (hipStream_t)stream);
-    if (rc) return rc;
-    t = 1;
-  }
-  if (t < T)
-    rc = bl_launch_quantize_heads(x + (size_t)t * H * D * esz, x_dtype, (T - t) * H, D, 3, eps,
-                                  c + kv_token_offset(pos0 + t, H, D), scales + (pos0 + t) * H, (hipStream_t)stream);
-  return rc;
+  // the sequence's first token has 4 bits
+  return bl_launch_quantize_heads(X, x_dtype, T * H, pos0 == 0 ? H : 0, D, 3, eps,
+                                  (unsigned char*)cache + kv_token_offset(pos0, H, D), scales + pos0 * H, (hipStream_t)stream);
 }
 
 extern "C" int kv_cache_read(const void* cache, const float* scales, int64_t pos0, int64_t T, int64_t H, int64_t D,
@@ -248,19 +238,8 @@ extern "C" int kv_cache_read(const void* cache, const float* scales, int64_t pos
   int rc = kv_check(T, H, D, pos0);
   if (rc) return rc;
   if (!bl_aligned16(out)) return BL_EALIGN;
-  const size_t esz = out_dtype == BL_BF16 ? 2 : 4;
-  const unsigned char* c = (const unsigned char*)cache;
-  unsigned char* o = (unsigned char*)out;
-  int64_t t = 0;
-  if (pos0 == 0) {
-    rc = bl_launch_dequantize_heads(c, scales, H, D, 4, o, out_dtype, (hipStream_t)stream);
-    if (rc) return rc;
-    t = 1;
-  }
-  if (t < T)
-    rc = bl_launch_dequantize_heads(c + kv_token_offset(pos0 + t, H, D), scales + (pos0 + t) * H, (T - t) * H, D, 3,
-                                    o + (size_t)t * H * D * esz, out_dtype, (hipStream_t)stream);
-  return rc;
+  return bl_launch_dequantize_heads((const unsigned char*)cache + kv_token_offset(pos0, H, D), scales + pos0 * H, T * H,
+                                    pos0 == 0 ? H : 0, D, 3, out, out_dtype, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------- ReLU^2 GLU (eq. 5)

@@ -4,6 +4,10 @@
 //   gamma = max |x| over the head,  q = RoundClip(Q_b / (gamma + eps) * x, -Q_b, Q_b),
 //   Q_b = 2^(bits-1) - 1,  code = q + 2^(bits-1),  scale = gamma / Q_b.
 // HBM bound: 2 D bytes in (bfloat16), D bits / 8 bytes and one float out per head.
+//
+// In the key / value cache the first token's heads have 4 bits and all others 3.  The kernels take the number n4 of
+// leading heads with 4 bits, so that one launch serves both widths: a launch of its own for the one token cost
+// 1.5 (append) to 1.8 us (read), a sixth of what 4096 tokens of 32 x 128 take (10 us).
 #include "common.h"
 
 #define QH_THREADS 256
@@ -57,7 +61,7 @@ __device__ __forceinline__ u32 qh_codes8(const float (&x)[8], float s) {
 // (3 bits: D % 32 == 0, so that the lanes of a quad fill whole words).
 template <typename RawT, int BITS>
 __global__ __launch_bounds__(QH_THREADS) void quant_heads_row_kernel(
-    const RawT* __restrict__ X, int64_t n_heads, int D, float eps, unsigned char* __restrict__ q_out,
+    const RawT* __restrict__ X, int64_t n_heads, int64_t n4, int D, float eps, unsigned char* __restrict__ q_out,
     float* __restrict__ scale_out) {
   const int64_t head = (int64_t)blockIdx.x * (QH_THREADS / 16) + (threadIdx.x >> 4);
   if (head >= n_heads) return;                            // whole rows leave together
@@ -72,27 +76,45 @@ __global__ __launch_bounds__(QH_THREADS) void quant_heads_row_kernel(
   for (int e = 0; e < 8; ++e) mx = max(mx, __float_as_uint(x[e]) & 0x7FFFFFFFu);
   mx = qh_row_max_dpp(mx);
   const float gamma = __uint_as_float(mx);
-  constexpr float QB = (float)((1 << (BITS - 1)) - 1);
-  const float s = QB / (gamma + eps);
-  if (j == 0) scale_out[head] = gamma / QB;
-  const u32 v = qh_codes8<BITS>(x, s);
-  if (BITS == 4) {
+  if (BITS == 4 || head < n4) {                           // (the same for a whole row of lanes)
+    const float s = 7.0f / (gamma + eps);
+    if (j == 0) scale_out[head] = gamma / 7.0f;
+    const u32 v = qh_codes8<4>(x, s);
     if (have) reinterpret_cast<u32*>(q_out + head * (D / 2))[j] = v;
   } else {
+    const float s = 3.0f / (gamma + eps);
+    if (j == 0) scale_out[head] = gamma / 3.0f;
+    const u32 v = qh_codes8<3>(x, s);
     // four lanes hold 4 x 24 bits = three words: lane jq of the quad builds word jq from its own
     // value and its right neighbour's
     const u32 nxt = (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x39, 0xF, 0xF, false);   // quad_perm [1,2,3,0]
     const int jq = j & 3;
     const u32 word = (v >> (8 * jq)) | (nxt << (24 - 8 * jq));
-    if (have && jq < 3) reinterpret_cast<u32*>(q_out + head * (3 * D / 8) + (j >> 2) * 12)[jq] = word;
+    if (have && jq < 3) reinterpret_cast<u32*>(q_out + n4 * (D / 2) + (head - n4) * (3 * D / 8) + (j >> 2) * 12)[jq] = word;
   }
 }
 
 // Any D % 8 == 0 up to BL_MAX_K: one wave per head, groups of 8 channels strided over the lanes,
 // the head read twice (statistics, coding), the codes written byte by byte.
 template <typename RawT, int BITS>
+__device__ __forceinline__ void qh_code_head(const RawT* x, int D, float gamma, float eps, unsigned char* out, float* scale_out) {
+  const int lane = threadIdx.x & 63;
+  constexpr float QB = (float)((1 << (BITS - 1)) - 1);
+  const float s = QB / (gamma + eps);
+  if (lane == 0) scale_out[0] = gamma / QB;
+  for (int g = lane; g < D / 8; g += 64) {
+    float v8[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v8[e] = qh_to_f32<RawT>(x[8 * g + e]);
+    const u32 v = qh_codes8<BITS>(v8, s);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) out[BITS * g + b] = (unsigned char)(v >> (8 * b));
+  }
+}
+
+template <typename RawT, int BITS>
 __global__ __launch_bounds__(QH_THREADS) void quant_heads_wave_kernel(
-    const RawT* __restrict__ X, int64_t n_heads, int D, float eps, unsigned char* __restrict__ q_out,
+    const RawT* __restrict__ X, int64_t n_heads, int64_t n4, int D, float eps, unsigned char* __restrict__ q_out,
     float* __restrict__ scale_out) {
   const int64_t head = (int64_t)blockIdx.x * (QH_THREADS / 64) + (threadIdx.x >> 6);
   if (head >= n_heads) return;                            // (no barriers in this kernel)
@@ -104,21 +126,12 @@ __global__ __launch_bounds__(QH_THREADS) void quant_heads_wave_kernel(
     for (int e = 0; e < 8; ++e) mx = max(mx, __float_as_uint(qh_to_f32<RawT>(x[8 * g + e])) & 0x7FFFFFFFu);
   mx = bl_wave_max_u32(mx);
   const float gamma = __uint_as_float(mx);
-  constexpr float QB = (float)((1 << (BITS - 1)) - 1);
-  const float s = QB / (gamma + eps);
-  if (lane == 0) scale_out[head] = gamma / QB;
-  unsigned char* out = q_out + head * (BITS * D / 8);
-  for (int g = lane; g < D / 8; g += 64) {
-    float v8[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v8[e] = qh_to_f32<RawT>(x[8 * g + e]);
-    const u32 v = qh_codes8<BITS>(v8, s);
-#pragma unroll
-    for (int b = 0; b < BITS; ++b) out[BITS * g + b] = (unsigned char)(v >> (8 * b));
-  }
+  if (BITS == 4 || head < n4) qh_code_head<RawT, 4>(x, D, gamma, eps, q_out + head * (D / 2), scale_out + head);
+  else qh_code_head<RawT, 3>(x, D, gamma, eps, q_out + n4 * (D / 2) + (head - n4) * (3 * D / 8), scale_out + head);
 }
 
-int bl_launch_quantize_heads(const void* X, bl_dtype dt, int64_t n_heads, int64_t D64, int bits, float eps,
+// bits = 4: all heads at 4 bits; bits = 3: the first n4 heads at 4 bits (packed before the others), the rest at 3
+int bl_launch_quantize_heads(const void* X, bl_dtype dt, int64_t n_heads, int64_t n4, int64_t D64, int bits, float eps,
                              void* q, float* scale, hipStream_t s) {
   const int D = (int)D64;
   const bool rows = D <= 128 && (bits == 4 || D % 32 == 0);
@@ -127,11 +140,11 @@ int bl_launch_quantize_heads(const void* X, bl_dtype dt, int64_t n_heads, int64_
 #define QH_GO(KERN)                                                                                          \
   do {                                                                                                       \
     if (dt == BL_BF16) {                                                                                     \
-      if (bits == 4) KERN<uint16_t, 4><<<grid, QH_THREADS, 0, s>>>((const uint16_t*)X, n_heads, D, eps, (unsigned char*)q, scale); \
-      else KERN<uint16_t, 3><<<grid, QH_THREADS, 0, s>>>((const uint16_t*)X, n_heads, D, eps, (unsigned char*)q, scale);           \
+      if (bits == 4) KERN<uint16_t, 4><<<grid, QH_THREADS, 0, s>>>((const uint16_t*)X, n_heads, n4, D, eps, (unsigned char*)q, scale); \
+      else KERN<uint16_t, 3><<<grid, QH_THREADS, 0, s>>>((const uint16_t*)X, n_heads, n4, D, eps, (unsigned char*)q, scale);           \
     } else {                                                                                                 \
-      if (bits == 4) KERN<u32, 4><<<grid, QH_THREADS, 0, s>>>((const u32*)X, n_heads, D, eps, (unsigned char*)q, scale);           \
-      else KERN<u32, 3><<<grid, QH_THREADS, 0, s>>>((const u32*)X, n_heads, D, eps, (unsigned char*)q, scale);                     \
+      if (bits == 4) KERN<u32, 4><<<grid, QH_THREADS, 0, s>>>((const u32*)X, n_heads, n4, D, eps, (unsigned char*)q, scale);           \
+      else KERN<u32, 3><<<grid, QH_THREADS, 0, s>>>((const u32*)X, n_heads, n4, D, eps, (unsigned char*)q, scale);                     \
     }                                                                                                        \
   } while (0)
   if (rows) QH_GO(quant_heads_row_kernel);
@@ -146,19 +159,21 @@ int bl_launch_quantize_heads(const void* X, bl_dtype dt, int64_t n_heads, int64_
 // One thread per group of 8 channels: BITS bytes in, 8 values out.
 template <typename OutT, int BITS>
 __global__ __launch_bounds__(QH_THREADS) void dequant_heads_kernel(
-    const unsigned char* __restrict__ q, const float* __restrict__ scale, int64_t n_groups, int gph,
+    const unsigned char* __restrict__ q, const float* __restrict__ scale, int64_t n_groups, int64_t n4, int gph,
     OutT* __restrict__ out) {
   const int64_t g = (int64_t)blockIdx.x * QH_THREADS + threadIdx.x;
   if (g >= n_groups) return;
   const float d = scale[g / gph];                          // gph = groups of 8 channels per head
-  const unsigned char* p = q + g * BITS;
-  u32 v = 0;
-#pragma unroll
-  for (int b = 0; b < BITS; ++b) v |= (u32)p[b] << (8 * b);
-  constexpr int OFF = 1 << (BITS - 1);
+  const int64_t g4 = BITS == 4 ? n_groups : n4 * gph;      // groups at 4 bits
+  const int bits = g < g4 ? 4 : 3;
+  const unsigned char* p = q + (g < g4 ? 4 * g : 3 * g + g4);
+  u32 v = (u32)p[0] | ((u32)p[1] << 8) | ((u32)p[2] << 16);
+  if (g < g4) v |= (u32)p[3] << 24;
+  const u32 mask = (1u << bits) - 1u;
+  const int off = 1 << (bits - 1);
   float x[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) x[j] = (float)((int)((v >> (BITS * j)) & ((1u << BITS) - 1u)) - OFF) * d;
+  for (int j = 0; j < 8; ++j) x[j] = (float)((int)((v >> (bits * j)) & mask) - off) * d;
   if (sizeof(OutT) == 2) {
     uint4 w;
     w.x = (u32)bl_f32_to_bf16_rne(x[0]) | ((u32)bl_f32_to_bf16_rne(x[1]) << 16);
@@ -172,13 +187,13 @@ __global__ __launch_bounds__(QH_THREADS) void dequant_heads_kernel(
   }
 }
 
-int bl_launch_dequantize_heads(const void* q, const float* scale, int64_t n_heads, int64_t D, int bits, void* out,
+int bl_launch_dequantize_heads(const void* q, const float* scale, int64_t n_heads, int64_t n4, int64_t D, int bits, void* out,
                                bl_dtype odt, hipStream_t s) {
   const int64_t n_groups = n_heads * (D / 8);
   const int64_t blocks = (n_groups + QH_THREADS - 1) / QH_THREADS;
   if (!bl_grid_ok(blocks)) return BL_ESHAPE;
   const int gph = (int)(D / 8);
-#define QH_DQ(T, B) dequant_heads_kernel<T, B><<<(unsigned)blocks, QH_THREADS, 0, s>>>((const unsigned char*)q, scale, n_groups, gph, (T*)out)
+#define QH_DQ(T, B) dequant_heads_kernel<T, B><<<(unsigned)blocks, QH_THREADS, 0, s>>>((const unsigned char*)q, scale, n_groups, n4, gph, (T*)out)
   if (odt == BL_BF16) { if (bits == 4) QH_DQ(uint16_t, 4); else QH_DQ(uint16_t, 3); }
   else { if (bits == 4) QH_DQ(float, 4); else QH_DQ(float, 3); }
 #undef QH_DQ

@@ -44,3 +44,20 @@ def test_topk_float32_rows(K):
             for k in ("q", "rowsum"):
                 assert torch.equal(a[k], b[k])
             assert torch.equal(a["scale"].view(torch.int32), b["scale"].view(torch.int32))
+
+
+@pytest.mark.parametrize("T,H,D", [(1, 3, 32), (5, 7, 96), (3, 5, 160)])
+def test_kv_cache_widths(T, H, D):
+    """The cache's two code widths in one launch: heads in rows of 16 lanes (D <= 128) and one per wave (wider), head
+    counts that split a workgroup, the first token alone and with others, reads from position 0 and from 1."""
+    print("[case] kv widths T=%d H=%d D=%d" % (T, H, D), flush=True)
+    X = S.heavy(T, H * D, S.seed_for(8, T + H + D)).reshape(T, H, D)
+    raw, d = O.kv_cache_pack(X, EPS)
+    vals = O.kv_cache_unpack(raw, d, T, H, D)
+    cache, scales = B.kv_cache_new(T, H, D, "cuda")
+    B.kv_cache_append(dev(X.reshape(T, H * D)).reshape(T, H, D), 0, cache, scales, EPS)
+    assert np.array_equal(cache.cpu().numpy(), raw)
+    assert np.array_equal(host(scales), d)
+    for pos0 in range(min(T, 2)):
+        out = B.kv_cache_read(cache, scales, pos0, T - pos0, H, D, torch.float32)
+        assert np.array_equal(host(out), vals[pos0:])
