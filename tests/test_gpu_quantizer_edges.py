@@ -6,7 +6,7 @@ import torch
 from oracle import bitnet_a48 as O
 from paper_2411_04965_amd import binding as B
 from paper_2411_04965_amd import synth as S
-from tests.gpu_util import EPS, decode_int8, dev, host
+from tests.gpu_util import EPS, decode_fp4, decode_fp4_mx, decode_int8, dev, host
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +61,49 @@ def test_kv_cache_widths(T, H, D):
     for pos0 in range(min(T, 2)):
         out = B.kv_cache_read(cache, scales, pos0, T - pos0, H, D, torch.float32)
         assert np.array_equal(host(out), vals[pos0:])
+
+
+@pytest.mark.parametrize("be", [1, 2, 3, 4, 100, 127, 200, 253, 254])
+def test_fp4_every_bfloat16(be):
+    """Every bfloat16 value of the 17 binades up to a block's maximum, both signs, under every mantissa of that maximum:
+    codes and scales bit for bit, at both ends of the exponent range and inside it."""
+    print("[case] fp4 values be=%d" % be, flush=True)
+    top = be * 128 + np.arange(128)                         # bit patterns of the maxima
+    vals = np.arange(max(0, (be - 16) * 128), be * 128 + 128)
+    blocks = []
+    for t in top:
+        v = vals[vals <= t]
+        v = np.concatenate([v, v | 0x8000])
+        v = np.concatenate([v, np.zeros(-len(v) % 31, v.dtype)]).reshape(-1, 31)
+        blocks.append(np.concatenate([np.full((len(v), 1), t | (0x8000 if t & 1 else 0)), v], axis=1))
+    bits = np.concatenate(blocks).astype(np.uint32)
+    bits = bits[:len(bits) // 96 * 96].reshape(-1, 96 * 32)  # rows of 96 blocks
+    x = (bits << 16).view(np.float32)
+    M, K = x.shape
+    c_ref, e_ref = O.quant_fp4(x)
+    r = B.quantize_act(dev(x, torch.bfloat16), B.BL_ACT_FP4_E2M1_B32_MX)
+    codes, e = decode_fp4_mx(host(r["q"]), host(r["scale"]), M, K)
+    assert np.array_equal(e, e_ref + 127)
+    assert np.array_equal(codes, c_ref)
+
+
+@pytest.mark.parametrize("M,K", [(1, 8), (2, 24), (3, 136), (33, 504), (35, 520), (65, 1000), (31, 3200)])
+def test_fp4_mx_edges(M, K):
+    """Row pairs and wave edges, zero blocks; infinities and NaN give what the kernel for row-major codes gives."""
+    print("[case] fp4 mx M=%d K=%d" % (M, K), flush=True)
+    Kp = (K + 255) // 256 * 256
+    x = S.snap_bf16(S.heavy(M, K, S.seed_for(8, M + K)))
+    x[M // 2, :min(K, 64)] = 0.0
+    pad = np.zeros((M, Kp), np.float32)
+    pad[:, :K] = x
+    c_ref, e_ref = O.quant_fp4(pad)
+    r = B.quantize_act(dev(x, torch.bfloat16), B.BL_ACT_FP4_E2M1_B32_MX)
+    codes, e = decode_fp4_mx(host(r["q"]), host(r["scale"]), M, Kp)
+    assert np.array_equal(e, e_ref + 127) and np.array_equal(codes, c_ref)
+    x[0, ::5] = np.inf
+    x[M - 1, 1::7] = np.nan
+    r = B.quantize_act(dev(x, torch.bfloat16), B.BL_ACT_FP4_E2M1_B32_MX)
+    codes, e = decode_fp4_mx(host(r["q"]), host(r["scale"]), M, Kp)
+    r = B.quantize_act(dev(x, torch.bfloat16), B.BL_ACT_FP4_E2M1_B32)
+    assert np.array_equal(e, host(r["scale"]).reshape(M, Kp // 32))
+    assert np.array_equal(codes, decode_fp4(host(r["q"]), M, Kp))
