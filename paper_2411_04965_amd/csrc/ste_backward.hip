@@ -131,6 +131,10 @@ __global__ __launch_bounds__(256) void ste_transpose_kernel(const void* __restri
 }
 
 // ---------------------------------------------------------------- the contraction
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t sb_rsrc(const uint16_t* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, 0x7FFFFFFF, 0x00027000);
+}
+
 // C[r][c] = mul * sum_j A[r][j] B[c][j]; A [R][lda], B [Cn][ldb] bfloat16, J % 64 == 0 (the callers pad the
 // contraction with zeros), lda % 8 == 0, ldb % 8 == 0.  Rows past the end re-read the last row and their
 // outputs are not stored.  A workgroup of four waves (2 x 2) owns a tile
@@ -139,7 +143,15 @@ __global__ __launch_bounds__(256) void ste_transpose_kernel(const void* __restri
 // 64 contraction indices per step, two LDS stages, the next step's operands in registers while the current
 // one is multiplied.  A row of a stage is 128 bytes whose 16-byte piece p sits at p ^ ((row / 2) % 8): the
 // 16 rows that one phase of a fragment read touches then cover the 16 slots of a 256-byte bank window.
-template <typename OutT, int TM, int TN>
+//
+// Bound by the matrix cores as far as the four waves keep them fed (1.38 PFLOP/s at 8192^3; 1.03 with flat addresses and all of a
+// sub-step's loads ahead of its MFMAs): with 256 x 256 tiles a wave is alone on its SIMD, so everything
+// else has to be issued in the shadow of its MFMAs (32 cycles each).  Hence one MFMA at a time between an LDS read,
+// an LDS write and a request; operands by buffer loads (a uniform step offset and one 32-bit offset per piece: flat
+// addresses took about ten vector instructions per piece); the barrier before the last sub-step, which reads the next step's
+// first fragments, so that a step starts without waiting for LDS.
+// WIDE: rows so long that 32-bit offsets inside a tile do not reach (flat addresses instead).
+template <typename OutT, int TM, int TN, bool WIDE>
 __global__ __launch_bounds__(SB_THREADS) void ste_gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                                  const uint16_t* __restrict__ B, int64_t ldb, int R,
                                                                  int Cn, int J, const float* __restrict__ mul_p,
@@ -157,22 +169,21 @@ __global__ __launch_bounds__(SB_THREADS) void ste_gemm_nt_kernel(const uint16_t*
   const int prow = tid >> 3, pp = tid & 7;
   // rows prow + 32 i: (row / 2) % 8 does not depend on i, so one LDS offset serves all pieces of a thread
   const int lds_off = prow * 128 + ((pp ^ ((prow >> 1) & 7)) << 4);
-  // (addresses are formed per load: 16 + 16 row pointers would take the registers the fragments need)
-  v4i ra[PA], rb[PB];                     // (a first-class vector type: the arrays then stay in registers)
-  auto load = [&](int j0) {
-    const int64_t col = j0 + 8 * pp;
+  // (offsets from the tile's first row, clamped to the last row: under 2^31 by the host's rule on lda, ldb)
+  const __amdgpu_buffer_rsrc_t rsrc_a = sb_rsrc(A + (int64_t)r0 * lda), rsrc_b = sb_rsrc(B + (int64_t)c0 * ldb);
+  constexpr int P = PA + PB, PER = (P + 2) / 3;
+  auto row_of = [&](int i) { return i < PA ? min(prow + 32 * i, R - 1 - r0) : min(prow + 32 * (i - PA), Cn - 1 - c0); };
+  u32 off[P];
 #pragma unroll
-    for (int i = 0; i < PA; ++i) ra[i] = *reinterpret_cast<const v4i*>(A + (int64_t)min(r0 + prow + 32 * i, R - 1) * lda + col);
-#pragma unroll
-    for (int i = 0; i < PB; ++i) rb[i] = *reinterpret_cast<const v4i*>(B + (int64_t)min(c0 + prow + 32 * i, Cn - 1) * ldb + col);
+  for (int i = 0; i < P; ++i) off[i] = 16 * pp + 2 * (u32)row_of(i) * (u32)(i < PA ? lda : ldb);
+  v4i reg[P];                             // (a first-class vector type: the array then stays in registers)
+  auto load = [&](int i, int s) {
+    if constexpr (WIDE)
+      reg[i] = *reinterpret_cast<const v4i*>((i < PA ? A + (r0 + row_of(i)) * lda : B + (c0 + row_of(i)) * ldb) + (int64_t)s * SB_BK + 8 * pp);
+    else
+      reg[i] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(i < PA ? rsrc_a : rsrc_b, (int)off[i], s * (SB_BK * 2), 0));
   };
-  auto stage_store = [&](int st) {
-    unsigned char* sa = sb_lds + st * STAGE + lds_off;
-#pragma unroll
-    for (int i = 0; i < PA; ++i) *reinterpret_cast<v4i*>(sa + i * 32 * 128) = ra[i];
-#pragma unroll
-    for (int i = 0; i < PB; ++i) *reinterpret_cast<v4i*>(sa + BM * 128 + i * 32 * 128) = rb[i];
-  };
+  auto stage_store = [&](int st, int i) { *reinterpret_cast<v4i*>(sb_lds + st * STAGE + lds_off + i * 32 * 128) = reg[i]; };
 
   v16f acc[TM][TN];
 #pragma unroll
@@ -187,58 +198,61 @@ __global__ __launch_bounds__(SB_THREADS) void ste_gemm_nt_kernel(const uint16_t*
   const int fsw = (li >> 1) & 7;
   const int fa_off = (wr + li) * 128, fb_off = BM * 128 + (wc + li) * 128;
   const int steps = (J + SB_BK - 1) / SB_BK;
-  // Pipeline: the operands of step s + 2 are requested during step s and written to LDS during step s + 1,
-  // a quarter of the pieces in each of the four sub-steps (A pieces in sub-steps 0, 1, B pieces in 2, 3): every
-  // load has a whole step to arrive, and neither the requests nor the LDS writes come as a burst (a wave that
+  // Pipeline: the operands of step s + 2 are requested during step s and written to LDS during step s + 1, a third of
+  // the pieces in each of the first three sub-steps: every load has a whole step to arrive, and neither the
+  // requests nor the LDS writes come as a burst (a wave that
   // issues many loads back to back stalls on them, and it is the only wave of its SIMD).  A piece's register
-  // is written to LDS and at once refilled by the next request, so one register set serves.  No branch in the
+  // is written to LDS and at once refilled by the next request, so one register set serves.  The barrier comes before
+  // the last sub-step: the next stage is whole then, and every read of the own one has been waited for.  No branch in the
   // loop (past the last step the requests re-read the last step's pieces and the LDS writes fill a stage that
-  // nobody reads any more), so that the compiler can count the loads in flight.
-  load(0);
-  stage_store(0);
-  load(min(1, steps - 1) * SB_BK);
+  // nobody multiplies any more), so that the compiler can count the loads in flight.
+  v8bf fa[2][TM], fb[2][TN];
+  auto fragments = [&](int set, int st, int ks) {
+    const unsigned char* p = sb_lds + st * STAGE + (((2 * ks + kg) ^ fsw) << 4);
+#pragma unroll
+    for (int a = 0; a < TM; ++a) fa[set][a] = *reinterpret_cast<const v8bf*>(p + fa_off + a * 32 * 128);
+#pragma unroll
+    for (int b = 0; b < TN; ++b) fb[set][b] = *reinterpret_cast<const v8bf*>(p + fb_off + b * 32 * 128);
+  };
+#pragma unroll
+  for (int i = 0; i < P; ++i) load(i, 0);
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    stage_store(0, i);
+    load(i, min(1, steps - 1));
+  }
   __syncthreads();
+  fragments(0, 0, 0);
   for (int s = 0; s < steps; ++s) {
     const int cur = s & 1;
-    const unsigned char* st = sb_lds + cur * STAGE;
-    unsigned char* sn = sb_lds + (cur ^ 1) * STAGE + lds_off;               // stage of step s + 1
-    const int64_t coln = min(s + 2, steps - 1) * SB_BK + 8 * pp;           // column of step s + 2
-    v8bf fa[2][TM], fb[2][TN];
-#pragma unroll
-    for (int a = 0; a < TM; ++a) fa[0][a] = *reinterpret_cast<const v8bf*>(st + fa_off + a * 32 * 128 + ((kg ^ fsw) << 4));
-#pragma unroll
-    for (int b = 0; b < TN; ++b) fb[0][b] = *reinterpret_cast<const v8bf*>(st + fb_off + b * 32 * 128 + ((kg ^ fsw) << 4));
+    const int s2 = min(s + 2, steps - 1);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      if (ks < 2) {
+      if (ks == 3) __syncthreads();
+      __builtin_amdgcn_sched_barrier(0);
+      if (ks < 3) fragments((ks + 1) & 1, cur, ks + 1);
+      else fragments(0, cur ^ 1, 0);
 #pragma unroll
-        for (int i = ks * (PA / 2); i < (ks + 1) * (PA / 2); ++i) {
-          *reinterpret_cast<v4i*>(sn + i * 32 * 128) = ra[i];
-          ra[i] = *reinterpret_cast<const v4i*>(A + (int64_t)min(r0 + prow + 32 * i, R - 1) * lda + coln);
-        }
-      } else {
-#pragma unroll
-        for (int i = (ks - 2) * (PB / 2); i < (ks - 1) * (PB / 2); ++i) {
-          *reinterpret_cast<v4i*>(sn + BM * 128 + i * 32 * 128) = rb[i];
-          rb[i] = *reinterpret_cast<const v4i*>(B + (int64_t)min(c0 + prow + 32 * i, Cn - 1) * ldb + coln);
-        }
+      for (int i = ks * PER; i < (ks + 1) * PER && i < P; ++i) {
+        stage_store(cur ^ 1, i);
+        load(i, s2);
       }
-      if (ks + 1 < 4) {                                                     // fragments one sub-step ahead
-        const int poff = ((2 * (ks + 1) + kg) ^ fsw) << 4;
-#pragma unroll
-        for (int a = 0; a < TM; ++a) fa[(ks + 1) & 1][a] = *reinterpret_cast<const v8bf*>(st + fa_off + a * 32 * 128 + poff);
-#pragma unroll
-        for (int b = 0; b < TN; ++b) fb[(ks + 1) & 1][b] = *reinterpret_cast<const v8bf*>(st + fb_off + b * 32 * 128 + poff);
-      }
-      __builtin_amdgcn_sched_barrier(0);                                   // (all of that stays ahead of the MFMAs)
 #pragma unroll
       for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b)
           acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][a], fb[ks & 1][b], acc[a][b], 0, 0, 0);
+      // one MFMA, then what fits into its shadow
+#pragma unroll
+      for (int k = 0; k < TM * TN; ++k) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);   // LDS write
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
+        __builtin_amdgcn_sched_group_barrier(0x006, 2, 0);   // arithmetic
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
   }
 
   // D of a 32 x 32 MFMA tile: lane (li, kg) holds column li, rows 8 (v / 4) + 4 kg + v % 4
@@ -266,27 +280,40 @@ size_t bl_ste_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   return (size_t)(K * Nc + N * Mc + K * Mc + (N % 64 ? M * Nc : 0)) * 2;
 }
 
-template <typename OutT, int TM, int TN>
+template <typename OutT, int TM, int TN, bool WIDE>
 static int sb_gemm_go(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int64_t R, int64_t Cn, int64_t J,
                       const float* mul, OutT* C, int64_t ldc, hipStream_t s) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   constexpr size_t smem = 2 * (size_t)(BM + BN) * 128;
   const int64_t RT = (R + BM - 1) / BM, CT = (Cn + BN - 1) / BN;
   if (!bl_grid_ok(RT * CT)) return BL_ESHAPE;
-  BL_SET_MAX_LDS_ONCE((ste_gemm_nt_kernel<OutT, TM, TN>), smem);
-  ste_gemm_nt_kernel<OutT, TM, TN><<<(unsigned)(RT * CT), SB_THREADS, smem, s>>>(A, lda, B, ldb, (int)R, (int)Cn, (int)J,
-                                                                                mul, C, ldc, (int)RT, (int)CT);
+  BL_SET_MAX_LDS_ONCE((ste_gemm_nt_kernel<OutT, TM, TN, WIDE>), smem);
+  ste_gemm_nt_kernel<OutT, TM, TN, WIDE><<<(unsigned)(RT * CT), SB_THREADS, smem, s>>>(
+      A, lda, B, ldb, (int)R, (int)Cn, (int)J, mul, C, ldc, (int)RT, (int)CT);
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
 }
 
-// 256 x 256 tiles where they fill the chip at least twice, else 128 x 128.
+// Tiles by turns of the chip (tiles over CUs, rounded up): a step of 64 indices takes 1.55 us on a 256 x 256 tile and 0.47 on
+// a 128 x 128 tile with every CU busy, so the large tile is taken where the small one needs 3.3 times the turns.  Outputs
+// (contraction) 4096 x 3200 (9600): 230 us against 280 of small tiles, 9600 x 3200 (4096): 218 / 255, 4096 x 4096 (12288): 296 / 388,
+// 8192 x 8192 (8192): 798 / 951, 1.38 PFLOP/s; on the other side 5460 x 2048 (2048): 56 / 51, 2048 x 2048 (5460): 111 / 49.
+// Below one turn a tile's steps are bound by the latency of its loads, so tiles get smaller as long as they still fill
+// no more than one turn: 256 x 2048 (5000): 64 x 64 28.0 us, 64 x 128 30.7, 128 x 128 38.5; 1024 x 2048 (4800): 35.5, 32.5, 39.0.
 template <typename OutT>
 static int sb_gemm(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int64_t R, int64_t Cn, int64_t J,
                    const float* mul, OutT* C, int64_t ldc, hipStream_t s) {
-  if (((R + 255) / 256) * ((Cn + 255) / 256) >= 2 * (int64_t)bl_num_cus())
-    return sb_gemm_go<OutT, 4, 4>(A, lda, B, ldb, R, Cn, J, mul, C, ldc, s);
-  return sb_gemm_go<OutT, 2, 2>(A, lda, B, ldb, R, Cn, J, mul, C, ldc, s);
+#define SB_GO(TM, TN, WIDE) sb_gemm_go<OutT, TM, TN, WIDE>(A, lda, B, ldb, R, Cn, J, mul, C, ldc, s)
+  // 256 rows of 2^22 - 64 elements: every offset inside a tile stays below 2^31
+  if (max(lda, ldb) > ((int64_t)1 << 22) - SB_BK) return SB_GO(2, 2, true);
+  const int64_t cus = bl_num_cus();
+  auto tiles = [&](int bm, int bn) { return ((R + bm - 1) / bm) * ((Cn + bn - 1) / bn); };
+  auto turns = [&](int bm, int bn) { return (tiles(bm, bn) + cus - 1) / cus; };
+  if (33 * turns(256, 256) <= 10 * turns(128, 128)) return SB_GO(4, 4, false);
+  if (tiles(64, 64) <= cus) return SB_GO(1, 1, false);
+  if (tiles(64, 128) <= cus) return SB_GO(1, 2, false);
+  return SB_GO(2, 2, false);
+#undef SB_GO
 }
 
 // q: INT4 nibble codes [M][Kp / 2] (a4 = true) or INT8 codes [M][Kp]; Wk: BL_W_KMAJOR.
