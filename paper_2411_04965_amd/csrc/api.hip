@@ -522,8 +522,7 @@ extern "C" int bitlinear_a4_gate_up(const void* X, bl_dtype x_dtype, int64_t M, 
     if (rc) return rc;
     return bl_launch_gemv_stream_glu_codes(codes, (const float*)scales, M, K, W_gate, alpha_gate, W_up, alpha_up, N, H, s);
   }
-  // 17 to 64 tokens, 2-bit tile weights, only H wanted: both products and eq. 5 in one launch of the
-  // kernel that keeps the tokens' codes in LDS
+  // 17 to 64 tokens, 2-bit tile weights, only H wanted: both products and eq. 5 in one launch
   if (layout == BL_W_GEMM && H && !G && !U && bl_gemm_decode_glu_ok(M, N, K)) {
     rc = bl_launch_quantize(X, x_dtype, M, K, mode, 0, eps, codes, scales, nullptr, nullptr, s);
     if (rc) return rc;

@@ -153,7 +153,7 @@ int bl_launch_gemm_decode(const void* q, const float* scale, bl_act_mode mode, i
                           int64_t K, const void* Wp, const float* alpha, int64_t N, void* Y,
                           bl_dtype ydt, int32_t* acc_out, void* ws, hipStream_t s);
 size_t bl_gemm_decode_ws_bytes(int64_t M, int64_t N, int64_t K);
-// smaller tiles for a few hundred to a few thousand tokens (gemm_mid.hip)
+// smaller tiles for 33 to a few thousand tokens (gemm_mid.hip)
 bool bl_gemm_mid_ok(int64_t M, int64_t N);
 int bl_launch_gemm_mid(const void* q, const float* scale, bl_act_mode mode, int64_t M, int64_t K, const void* Wp,
                        const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);
@@ -161,6 +161,8 @@ bool bl_gemm_mid_mx_ok(int64_t M, int64_t n_cols);
 int bl_launch_gemm_mid_mx(const void* q, const float* scale, int64_t M, int64_t K, const void* Wp, const float* alpha,
                           int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);
 int bl_launch_gemm_mid_mx_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,
+                              const void* Wu, const float* au, int64_t N, void* H, hipStream_t s);
+int bl_launch_gemm_mid_a4_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,
                               const void* Wu, const float* au, int64_t N, void* H, hipStream_t s);
 bool bl_gemv_a4_fused_ok(int64_t M, int64_t N, int64_t K);
 int bl_launch_up_gated(const void* X, int64_t M, int64_t K, float eps, const void* Wr, const float* alpha,

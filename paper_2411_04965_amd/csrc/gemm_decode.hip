@@ -626,10 +626,10 @@ __global__ __launch_bounds__(GD_THREADS) void gemm_decode_rows_kernel(
   }
 }
 
-// 17 to 64 tokens.  The tokens' codes are the larger stream here (a block of 16 outputs reads 4 KB
-// of weights per 1024 channels but 32 to 64 KB of codes), and split-K partial sums cost as much
+// 17 to 32 tokens.  The tokens' codes are the larger stream here (a block of 16 outputs reads 4 KB
+// of weights per 1024 channels but 32 KB of codes), and split-K partial sums cost as much
 // again.  So the codes stay put: one block of 16 waves per CU keeps the codes of all tokens for its
-// slice of K in LDS (up to 128 KB: all of K for INT4 codes at 4096 channels) and streams the weight
+// slice of K in LDS (up to 128 KB: all of K for INT4 codes at 8192 channels) and streams the weight
 // tiles of its NWT output tiles past them.  The output tiles go in groups of up to GR_G to the
 // waves, so that one expansion of a token fragment (nibbles to bytes) serves GR_G matrix
 // instructions; wave u works on group u / KS and on part u % KS of the slice.  The parts are added
@@ -879,7 +879,8 @@ __global__ __launch_bounds__(GD_THREADS) void decode_reduce_kernel(
 
 // Kernel choice.  Up to 16 tokens (one MFMA tile of tokens) with enough output tiles to fill the
 // chip: one 16-output tile per block, no split of K, one launch.  Up to 16 tokens and few outputs:
-// 64 outputs per block and K split until the grid is large.  More tokens: codes resident in LDS.
+// 64 outputs per block and K split until the grid is large.  17 to 32 tokens: codes resident in LDS.  More: gemm_mid.hip, which
+// needs no workspace (the split still sizes one there, so that calls are accepted and refused by one rule).
 static bool gd_single_tile(int M, int N) { return M <= 16 && (N + 15) / 16 >= 128; }
 // resident kernel: tiles of K per slice so that 16 * MT rows of codes fit
 static int gr_slice_tiles(int MT, bool a4) { return GR_X_BYTES / (MT * 16) / (a4 ? 128 : 256); }
@@ -936,20 +937,19 @@ static int gd_run(const void* q, const float* scale, int M, int Kp, const void* 
   return S > 1 ? gd_reduce(S, M, N, A4 ? 10 : 6, scale, alpha, Y, ybf, acc_out, ws, s) : BL_OK;
 }
 
-template <int MT, bool A4>
+template <bool A4>
 static int gr_run(const void* q, const float* scale, int M, int Kp, const void* Wp,
                   const float* alpha, int N, void* Y, bl_dtype ydt, int32_t* acc_out, void* ws,
                   hipStream_t s) {
+  constexpr int MT = 2;
   const int KT = Kp >> 8, NT16 = (N + 15) / 16;
   const int S = gd_pick_split(M, N, KT, A4);
   if (S > 1 && !ws) return BL_EWORKSPACE;
   const int L = (KT + S - 1) / S;                        // tiles of the longest slice
   // output tiles per block: as few as still give at most one block per CU (one block takes most
   // of a CU's LDS), at most one per wave
-  // (64 tokens: at most 12, so that the partial tiles and the sums fit the LDS together)
-  const int nwt_max = MT == 4 ? 12 : GR_WAVES;
   int NWT = 1;
-  while (NWT < nwt_max && ((NT16 + NWT - 1) / NWT) * S > bl_num_cus()) ++NWT;
+  while (NWT < GR_WAVES && ((NT16 + NWT - 1) / NWT) * S > bl_num_cus()) ++NWT;
   const int NBn = (NT16 + NWT - 1) / NWT;
   const int NG = (NWT + GR_G - 1) / GR_G;                // groups of output tiles, one per wave
   // parts of the slice per group: every part gets at least one tile; at most 8 working waves (two
@@ -957,24 +957,23 @@ static int gr_run(const void* q, const float* scale, int M, int Kp, const void* 
   const int KS = max(1, min(max(1, 8 / NG), KT / S));
   const size_t smem = max((size_t)MT * 16 * ((size_t)L * (A4 ? 128 : 256) + 16),
                           (size_t)NG * KS * GR_G * MT * 1024 + (size_t)MT * 16 * (NWT * 16 + 4) * sizeof(int32_t));
-  auto kern = gemm_decode_resident_kernel<MT, A4>;
   // (the limit is raised once, to the most a launch can ask for: the codes' space plus row padding, or
   // eight waves' partial tiles plus the block's sums)
   BL_SET_MAX_LDS_ONCE((gemm_decode_resident_kernel<MT, A4>), GR_LDS_MAX);
   if (smem > GR_LDS_MAX) return BL_ESHAPE;
   const int ybf = ydt == BL_BF16 ? 1 : 0;
-  kern<<<(unsigned)(NBn * S), GR_THREADS, smem, s>>>((const unsigned char*)q, scale, M, Kp,
-                                                     (const unsigned char*)Wp, alpha, N, Y, ybf,
-                                                     acc_out, (int32_t*)ws, NBn, S, NWT, KS, nullptr, nullptr);
+  gemm_decode_resident_kernel<MT, A4><<<(unsigned)(NBn * S), GR_THREADS, smem, s>>>(
+      (const unsigned char*)q, scale, M, Kp, (const unsigned char*)Wp, alpha, N, Y, ybf, acc_out, (int32_t*)ws, NBn, S, NWT, KS,
+      nullptr, nullptr);
   BL_HIP_CHECK_LAUNCH();
   return S > 1 ? gd_reduce(S, M, N, A4 ? 10 : 6, scale, alpha, Y, ybf, acc_out, ws, s) : BL_OK;
 }
 
-// Gate and up projection of 17 to 64 tokens with eq. 5 in the same launch (INT4 codes, both matrices in
+// Gate and up projection of 17 to 32 tokens with eq. 5 in the same launch (INT4 codes, both matrices in
 // BL_W_GEMM): possible where all of K fits the LDS beside the tokens (no split across blocks).
-static bool gr_glu_plan(int M, int N, int Kp, int& MT, int& NWT, int& KS, int& NBn, size_t& smem) {
-  if (M <= 16 || M > 64) return false;
-  MT = M > 32 ? 4 : 2;
+static bool gr_glu_plan(int M, int N, int Kp, int& NWT, int& KS, int& NBn, size_t& smem) {
+  if (M <= 16 || M > 32) return false;
+  constexpr int MT = 2;
   const int KT = Kp >> 8;
   if (KT > gr_slice_tiles(MT, true)) return false;
   const int NTv = 2 * ((N + 15) / 16);                   // gate and up tiles
@@ -991,32 +990,31 @@ static bool gr_glu_plan(int M, int N, int Kp, int& MT, int& NWT, int& KS, int& N
 }
 
 bool bl_gemm_decode_glu_ok(int64_t M, int64_t N, int64_t K) {
-  int MT, NWT, KS, NBn;
+  int NWT, KS, NBn;
   size_t smem;
   if (M > 64 || N > ((int64_t)1 << 27)) return false;
-  return gr_glu_plan((int)M, (int)N, (int)bl_round_up(K, BL_KPAD), MT, NWT, KS, NBn, smem);
-}
-
-template <int MT>
-static int gr_go_glu(const void* q, const float* scale, int M, int Kp, const void* Wg, const float* ag, const void* Wu,
-                     const float* au, int N, void* H, int NWT, int KS, int NBn, size_t smem, hipStream_t s) {
-  BL_SET_MAX_LDS_ONCE((gemm_decode_resident_kernel<MT, true, true>), GR_LDS_MAX);
-  gemm_decode_resident_kernel<MT, true, true><<<(unsigned)NBn, GR_THREADS, smem, s>>>(
-      (const unsigned char*)q, scale, M, Kp, (const unsigned char*)Wg, ag, N, H, 1, nullptr, nullptr, NBn, 1, NWT, KS,
-      (const unsigned char*)Wu, au);
-  BL_HIP_CHECK_LAUNCH();
-  return BL_OK;
+  const int Kp = (int)bl_round_up(K, BL_KPAD);
+  // (33 to 64 tokens run in gemm_mid.hip, which takes any K; rows wider than this keep to the composed path, whose larger
+  // workspace their callers already pass)
+  if (M > 32) return (Kp >> 8) <= gr_slice_tiles(4, true);
+  return gr_glu_plan((int)M, (int)N, Kp, NWT, KS, NBn, smem);
 }
 
 // q: INT4 nibble codes [M][Kp / 2] with their scales; H [M, N] bfloat16.
 int bl_launch_gemm_decode_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,
                               const void* Wu, const float* au, int64_t N, void* H, hipStream_t s) {
-  int MT, NWT, KS, NBn;
+  // (more than 32 tokens: 57 x 2 x 5460 x 2048 9.5 us with the codes in LDS, 7.9 with the tiles of gemm_mid.hip)
+  if (M > 32) return bl_launch_gemm_mid_a4_glu(q, scale, M, K, Wg, ag, Wu, au, N, H, s);
+  int NWT, KS, NBn;
   size_t smem;
   const int Kp = (int)bl_round_up(K, BL_KPAD);
-  if (!gr_glu_plan((int)M, (int)N, Kp, MT, NWT, KS, NBn, smem)) return BL_EUNSUPPORTED;
-  if (MT == 2) return gr_go_glu<2>(q, scale, (int)M, Kp, Wg, ag, Wu, au, (int)N, H, NWT, KS, NBn, smem, s);
-  return gr_go_glu<4>(q, scale, (int)M, Kp, Wg, ag, Wu, au, (int)N, H, NWT, KS, NBn, smem, s);
+  if (!gr_glu_plan((int)M, (int)N, Kp, NWT, KS, NBn, smem)) return BL_EUNSUPPORTED;
+  BL_SET_MAX_LDS_ONCE((gemm_decode_resident_kernel<2, true, true>), GR_LDS_MAX);
+  gemm_decode_resident_kernel<2, true, true><<<(unsigned)NBn, GR_THREADS, smem, s>>>(
+      (const unsigned char*)q, scale, (int)M, Kp, (const unsigned char*)Wg, ag, (int)N, H, 1, nullptr, nullptr, NBn, 1, NWT, KS,
+      (const unsigned char*)Wu, au);
+  BL_HIP_CHECK_LAUNCH();
+  return BL_OK;
 }
 
 // The fused INT4 linear is used for one bfloat16 token when the one-tile-per-block kernel would be
@@ -1106,8 +1104,10 @@ int bl_launch_gemm_decode(const void* q, const float* scale, bl_act_mode mode, i
 #define GD_ARGS q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, ws, s
   if (gd_single_tile((int)M, (int)N)) return a4 ? gd_run<1, true, true>(GD_ARGS) : gd_run<1, false, true>(GD_ARGS);
   if (M <= 16) return a4 ? gd_run<1, true, false>(GD_ARGS) : gd_run<1, false, false>(GD_ARGS);
-  if (M <= 32) return a4 ? gr_run<2, true>(GD_ARGS) : gr_run<2, false>(GD_ARGS);
-  return a4 ? gr_run<4, true>(GD_ARGS) : gr_run<4, false>(GD_ARGS);
+  // (more than 32 tokens: see the head of gemm_mid.hip.  At 32 the two kernels are level -- 4096 x 4096 8.0 us against 7.9,
+  // 4096 x 11008 13.5 / 14.0 -- and below the codes' share of the traffic speaks for keeping them in LDS)
+  if (M <= 32) return a4 ? gr_run<true>(GD_ARGS) : gr_run<false>(GD_ARGS);
+  return bl_launch_gemm_mid(q, scale, mode, M, K, Wp, alpha, N, Y, ydt, acc_out, s);
 #undef GD_ARGS
 }
 

@@ -1,4 +1,4 @@
-// Prefill GEMMs of the quantized linears for a few hundred to a few thousand tokens (eq. 6 and eq. 1 of the paper):
+// GEMMs of the quantized linears for 33 to a few thousand tokens (eq. 6 and eq. 1 of the paper):
 //   acc[m, n] = sum_k q[m, k] * T[n, k],   Y[m, n] = (acc * d[m]) * alpha,
 // from INT8 or INT4 codes x BL_W_GEMM weights (int32 on v_mfma_i32_32x32x32_i8) and from E3M2 codes x BL_W_MX2
 // weights (exact integers in float32 on v_mfma_f32_32x32x64_f8f6f4).
@@ -11,7 +11,8 @@
 // and 64 KB of reads per step (about 800 cycles of 1024 of INT8 matrix work), where a tile that also expands the
 // weights into LDS moves 64 + 128 KB.  Measured, product alone (before: 256 x 256 and 128 x 128 tiles with one step of
 // prefetch): INT8 200 x 3200 x 8640 34.8 -> 12.8 us, 1000 x 4096 x 11008 45.8 -> 38.8, 2048 x 2048 x 5460 54.5 -> 22.3,
-// 2048 x 4096 x 11008 100 -> 71 (2.6 POPS); INT4 200 x 9600 x 3200 22.3 -> 10.8, gate/up of 200 x 2 x 8640 x 3200 21.6 -> 14.9.
+// 2048 x 4096 x 11008 100 -> 71 (2.6 POPS); 64 tokens (before: the kernel that keeps the codes in LDS, and a second launch for
+// the sums where K is split): INT8 64 x 4096 x 4096 12.7 -> 8.0, 64 x 4096 x 11008 17.6 -> 14.0, 57 x 2048 x 5460 12.2 -> 9.6; INT4 200 x 9600 x 3200 22.3 -> 10.8, gate/up of 200 x 2 x 8640 x 3200 21.6 -> 14.9.
 //
 // Structure.  A group of 4 waves (2 x 2) owns a tile of 64 TM x 64 TN; a wave has TM x TN MFMA tiles (row operand =
 // weights, column operand = tokens, so a lane ends up with groups of 4 consecutive outputs of one token).  One step =
@@ -71,7 +72,7 @@ __device__ __forceinline__ void gm_acc4_add(v16f& c, int q, v4i v) {   // (whole
 }
 
 // OUT: GM_ROWS = bfloat16 rows through LDS; GM_ANY = either output type by elements, and the accumulators if asked
-// for.  GLU (GM_MX, GM_ROWS, TN = 2): a tile is 64 outputs of the gate and of the up matrix, column
+// for.  GLU (GM_I4 or GM_MX, GM_ROWS, TN = 2): a tile is 64 outputs of the gate and of the up matrix, column
 // tile 0 of a wave is G and column tile 1 is U of the same 32 outputs; H = bf16(U * max(G, 0)^2).
 template <int FMT, int OUT, bool GLU, int TM, int TN, int G>
 __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
@@ -163,8 +164,8 @@ __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
     const int nt_max = ((N + 15) >> 4) - 1;
 #pragma unroll
     for (int a = 0; a < TN; ++a) {
-      const int nt = (n0 >> 4) + 2 * TN * wn + 2 * a;
-      w_base[a] = Wp + ((size_t)min(nt, nt_max) * KT + kt0) * W_STEP;
+      const int nt = GLU ? (n0 >> 5) + 2 * wn : (n0 >> 4) + 2 * TN * wn + 2 * a;
+      w_base[a] = (GLU && a ? Wp2 : Wp) + ((size_t)min(nt, nt_max) * KT + kt0) * W_STEP;
       w_off[a] = ((l32 >> 4) && nt < nt_max ? (u32)KT * 1024 : 0u) + (lh * 16 + (l32 & 15)) * 16;
     }
   }
@@ -308,8 +309,11 @@ __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
   }
 
   // ---- epilogue.  acc[a][b][r] is output n = 64 wn + 32 a + 8 (r / 4) + 4 lh + r % 4 (GLU: 32 wn + ...) of token
-  // m = 64 wm + 32 b + l32 of the tile.  float(2^shift acc) * (d / 2^shift) rounds exactly like float(acc) * d.
-  constexpr float unscale = FMT == GM_I8 ? 1.0f / 64.0f : FMT == GM_I4 ? 1.0f / 1024.0f : 1.0f;
+  // m = 64 wm + 32 b + l32 of the tile, times 2^shift in integer formats.
+  auto value = [&](const Acc& c, int i) {
+    if constexpr (MX) return c[i];
+    else return (float)(c[i] >> F::shift);
+  };
   if constexpr (G > 1) {                                   // sums of the other groups, added by group 0
     __syncthreads();
     v4i* const sp = reinterpret_cast<v4i*>(gm_smem) + tid;
@@ -331,7 +335,7 @@ __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
     const float alpha = alpha_p[0];
     float dsc[TM];
 #pragma unroll
-    for (int b = 0; b < TM; ++b) dsc[b] = scale[min(m0 + wm * 32 * TM + b * 32 + l32, M - 1)] * unscale;
+    for (int b = 0; b < TM; ++b) dsc[b] = scale[min(m0 + wm * 32 * TM + b * 32 + l32, M - 1)];
     if constexpr (OUT == GM_ROWS) {
       constexpr int TB = F::tb_row;
       constexpr int BNO = GLU ? F::bn / 2 : F::bn;                 // outputs per token of this tile
@@ -348,9 +352,9 @@ __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
             float fv[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const float g = ((float)acc[a][b][4 * q + r] * dsc[b]) * alpha;
+              const float g = (value(acc[a][b], 4 * q + r) * dsc[b]) * alpha;
               if constexpr (GLU) {
-                const float u = ((float)acc[TN - 1][b][4 * q + r] * dsc[b]) * alpha2;
+                const float u = (value(acc[TN - 1][b], 4 * q + r) * dsc[b]) * alpha2;
                 const float rl = fmaxf(g, 0.0f);
                 const float rr = rl * rl;
                 fv[r] = u * rr;
@@ -393,7 +397,7 @@ __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
             int iv[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              fv[r] = ((float)acc[a][b][4 * q + r] * dsc[b]) * alpha;
+              fv[r] = (value(acc[a][b], 4 * q + r) * dsc[b]) * alpha;
               iv[r] = MX ? (int)acc[a][b][4 * q + r] : (int)acc[a][b][4 * q + r] >> F::shift;
             }
             if (m >= M) continue;
@@ -455,7 +459,7 @@ bool bl_gemm_mid_mx_ok(int64_t M, int64_t n_cols) { return 24 * gm_turns(M, n_co
 
 // Integer codes: 64 x 64 tiles and two K groups while these fill one turn (200 x 3200 x 8640: 12.8 us, 64 x 128 tiles 17.6,
 // 128 x 128 25.9), then 64 x 128 while those do (400 x 3200 x 8640: 18.5, 128 x 128 26.8, 64 x 64 21.0), then 128 x 128
-// (600 x 4096 x 4096: 15.6 against 16.4 and more).
+// (600 x 4096 x 4096: 15.6 against 16.4 and more; never for tokens that fill only half of it).
 template <int FMT, int OUT>
 static int gm_int(const void* q, const float* scale, int64_t M, int64_t K, const void* Wp, const float* alpha, int64_t N,
                   void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s) {
@@ -463,7 +467,7 @@ static int gm_int(const void* q, const float* scale, int64_t M, int64_t K, const
   const void* Wp2 = nullptr;
   const float* alpha2 = nullptr;
   if (gm_turns(M, N, 64, 64) == 1) return GM_CALL(FMT, OUT, false, 1, 1, 2);
-  if (gm_turns(M, N, 64, 128) == 1) return GM_CALL(FMT, OUT, false, 1, 2, 2);
+  if (M <= 64 || gm_turns(M, N, 64, 128) == 1) return GM_CALL(FMT, OUT, false, 1, 2, 2);
   return GM_CALL(FMT, OUT, false, 2, 2, 1);
 }
 
@@ -500,4 +504,13 @@ int bl_launch_gemm_mid_mx_glu(const void* q, const float* scale, int64_t M, int6
   const bl_dtype ydt = BL_BF16;
   int32_t* acc_out = nullptr;
   return GM_CALL(GM_MX, GM_ROWS, true, 1, 2, 1);
+}
+
+// INT4 codes x two BL_W_GEMM matrices (33 to 64 tokens): 64 outputs of either per block, two K groups.
+int bl_launch_gemm_mid_a4_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wp, const float* alpha,
+                              const void* Wp2, const float* alpha2, int64_t N, void* Y, hipStream_t s) {
+  const int KT = (int)(bl_round_up(K, BL_KPAD) >> 8);
+  const bl_dtype ydt = BL_BF16;
+  int32_t* acc_out = nullptr;
+  return GM_CALL(GM_I4, GM_ROWS, true, 1, 2, 2);
 }

@@ -77,3 +77,29 @@ def test_tiles(M, N, K):
     assert torch.equal(y, y4) and torch.equal(acc, acc4.int())
     h = B.bitlinear_a4_gate_up(X, p, a, pu, au, N, layout=B.BL_W_MX2, want=("H",))["H"]
     assert torch.equal(h, (u4 * y4.clamp_min(0.0).square()).to(BF16))
+
+
+# both sides of 32 tokens; K of one step and of an odd number; outputs past one turn of the smallest tile and of the next one
+@pytest.mark.parametrize("M,N,K,mul", [(32, 70, 300, 1.0), (33, 70, 200, 1.0), (33, 1027, 1300, 1e-36), (57, 5460, 2048, 1.0),
+                                       (64, 16452, 520, 1.0), (63, 32901, 257, 1.0), (64, 260, 4200, 1.0)])
+def test_decode_tokens(M, N, K, mul):
+    """33 to 64 tokens in the two-bit tile layout, the gate/up front among them, bit for bit; with tiny activations too, whose
+    scales have no binades to spare."""
+    print("[case] decode tiles M=%d N=%d K=%d mul=%g" % (M, N, K, mul), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    X = (mul * torch.randn((M, K), generator=g, device="cuda")).to(BF16)
+    W = 0.02 * torch.randn((N, K), generator=g, device="cuda")
+    Wu = 0.02 * torch.randn((N, K), generator=g, device="cuda")
+    acc8, y8 = product(X, W, B.BL_ACT_TOPK_INT8_ABSMAX, K // 2)
+    acc4, y4 = product(X, W, B.BL_ACT_INT4_ABSMEAN)
+    u4 = product(X, Wu, B.BL_ACT_INT4_ABSMEAN)[1]
+    p, a = B.pack_ternary(W)
+    pu, au = B.pack_ternary(Wu)
+    assert torch.equal(B.bitlinear_a8_sparse(X, K // 2, p, a, N), y8.to(BF16))
+    y, acc = B.bitlinear_a8_sparse(X, K // 2, p, a, N, y_dtype=torch.float32, want_acc=True)
+    assert torch.equal(y, y8) and torch.equal(acc, acc8.int())
+    assert torch.equal(B.bitlinear_a4(X, p, a, N), y4.to(BF16))
+    y, acc = B.bitlinear_a4(X, p, a, N, y_dtype=torch.float32, want_acc=True)
+    assert torch.equal(y, y4) and torch.equal(acc, acc4.int())
+    h = B.bitlinear_a4_gate_up(X, p, a, pu, au, N, want=("H",))["H"]
+    assert torch.equal(h, (u4 * y4.clamp_min(0.0).square()).to(BF16))
