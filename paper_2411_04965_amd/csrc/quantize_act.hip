@@ -648,7 +648,7 @@ __global__ __launch_bounds__(QA_THREADS) void quant_topk_int8_regs_kernel(
 // Few tokens (decode): what counts is how long one token takes, not how many run at once.  Eight
 // waves per token, 11-bit keys and three bits of the threshold per pass (topk_regs.h); codes and
 // scales only (the codes are those of the kernels above bit for bit).
-template <int CPW>
+template <int CPW, bool EARLY>
 __global__ __launch_bounds__(512) void quant_topk_int8_regs8_kernel(
     const uint16_t* __restrict__ X, int K, int Kp, int topk, float eps, u32* __restrict__ q_out,
     float* __restrict__ scale_out) {
@@ -669,7 +669,7 @@ __global__ __launch_bounds__(512) void quant_topk_int8_regs8_kernel(
     raw[i][0] = v.x;
     raw[i][1] = v.y;
   }
-  qa_topk_row_regs8<CPW>(raw, nc, c_begin, topk, eps, q_out + m * (int64_t)(Kp / 4), scale_out + m, sh);
+  qa_topk_row_regs8<CPW, EARLY>(raw, nc, c_begin, topk, eps, q_out + m * (int64_t)(Kp / 4), scale_out + m, sh);
 }
 
 // The same selection with one wave per token, for many tokens of moderate width: the fixed cost of a
@@ -1109,10 +1109,12 @@ static int qa_run_topk_regs(const void* x, const void* x2, int64_t M, int K, int
   const int nb = (Kp / 256 + 3) / 4;
   if (GLU == 0 && rowsum == nullptr && M <= 256) {
     // (K % 4 == 0 and Kp <= 12288 by dispatch: at most 6 chunks of 256 channels per wave)
-    if (Kp <= 8192)
-      quant_topk_int8_regs8_kernel<4><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale);
+    if (Kp <= 4096)
+      quant_topk_int8_regs8_kernel<4, false><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale);
+    else if (Kp <= 8192)
+      quant_topk_int8_regs8_kernel<4, true><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale);
     else
-      quant_topk_int8_regs8_kernel<8><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale);
+      quant_topk_int8_regs8_kernel<8, false><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale);
   } else if (M >= 2048 && nb <= 6) {
     const unsigned grid = (unsigned)((M + QA_WAVES - 1) / QA_WAVES);
     if (nb <= 4)

@@ -6,6 +6,7 @@ import torch
 from oracle import bitnet_a48 as O
 from paper_2411_04965_amd import binding as B
 from paper_2411_04965_amd import synth as S
+from tests.test_gpu_parity import _rows_around_the_shortcut
 from tests.gpu_util import EPS, decode_fp4, decode_fp4_mx, decode_int8, dev, host
 
 pytestmark = pytest.mark.gpu
@@ -107,3 +108,19 @@ def test_fp4_mx_edges(M, K):
     r = B.quantize_act(dev(x, torch.bfloat16), B.BL_ACT_FP4_E2M1_B32)
     assert np.array_equal(e, host(r["scale"]).reshape(M, Kp // 32))
     assert np.array_equal(codes, decode_fp4(host(r["q"]), M, Kp))
+
+
+@pytest.mark.parametrize("K", [4, 260, 2048, 2052, 5460, 8192])
+def test_topk_shortcut_eight_waves(K):
+    """Eight waves per token, rows of up to 8192 channels: the shortcut for mostly-zero rows one count below, at and above its
+    boundary, and rows with no value in reach of it, bit for bit the oracle's codes."""
+    M, n_big = 33, max(1, K // 5)
+    x = _rows_around_the_shortcut(M, K, n_big, S.seed_for(8, K)) if K >= 16 else S.snap_bf16(S.heavy(M, K, 1))
+    x[5] = 0.0
+    x[6] *= 2.0 ** -126                                     # maximum within 8 binades of the smallest number
+    for topk in sorted({1, max(1, n_big - 1), n_big, min(K, n_big + 1), K // 2, K}):
+        print("[case] topk shortcut K=%d topk=%d" % (K, topk), flush=True)
+        q_ref, d_ref, _ = O.quant_topk_int8(x, topk, EPS)
+        r = B.quantize_act(dev(x, torch.bfloat16), B.BL_ACT_TOPK_INT8_ABSMAX, topk, EPS)
+        assert np.array_equal(host(r["scale"]), d_ref)
+        assert np.array_equal(decode_int8(host(r["q"]), M, K), q_ref)
