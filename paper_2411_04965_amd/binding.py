@@ -95,11 +95,13 @@ def _check(fn, status):
 
 
 # torch.cuda.current_stream() builds a Stream object: 2.7 us of the 8.1 us that a one-token linear took on the host.
-# The raw handle of the same stream takes 0.1 us.
-_raw_stream = torch._C._cuda_getCurrentRawStream
+# The raw handle of the same stream takes 0.1 us.  (A torch without GPU support lacks the call; the module still loads there.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
     return _raw_stream(torch.cuda.current_device())
 
 

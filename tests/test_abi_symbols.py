@@ -3,6 +3,8 @@ No compute call is made (no GPU needed); size queries and argument validation ru
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -54,3 +56,12 @@ def test_size_queries_and_validation(lib):
     assert lib.bitlinear_a4(16, 0, 1, 40000, 16, 0, 16, 1, 1e-5, 0, 16, 0, None, None, 0, None) == -2
     assert lib.bitlinear_a8_sparse(16, 0, 4, 64, 65, 16, 0, 16, 8, 1e-5, 16, 0, None, 16, 1 << 20, None) == -1
     assert lib.bl_status_string(-4).decode().startswith("workspace")
+
+
+def test_binding_loads_where_torch_has_no_gpu_support(lib):
+    """Sizes, constants and signatures need no device: the module loads on a torch without the raw stream call."""
+    code = ("import torch; hasattr(torch._C, '_cuda_getCurrentRawStream') and delattr(torch._C, '_cuda_getCurrentRawStream')\n"
+            "from paper_2411_04965_amd import binding\n"
+            "assert binding.lib().bl_padded_k(5460) == 5632\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
