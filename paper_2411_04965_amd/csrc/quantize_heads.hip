@@ -5,9 +5,11 @@
 //   Q_b = 2^(bits-1) - 1,  code = q + 2^(bits-1),  scale = gamma / Q_b.
 // HBM bound: 2 D bytes in (bfloat16), D bits / 8 bytes and one float out per head.
 //
-// In the key / value cache the first token's heads have 4 bits and all others 3.  The kernels take the number n4 of
+// In the key / value cache the first token's heads have 4 bits and all others 3.  The MIXED kernels take the number n4 of
 // leading heads with 4 bits, so that one launch serves both widths: a launch of its own for the one token cost
-// 1.5 (append) to 1.8 us (read), a sixth of what 4096 tokens of 32 x 128 take (10 us).
+// 1.5 (append) to 1.8 us (read), a sixth of what 4096 tokens of 32 x 128 take (10 us).  Calls of one width (later
+// tokens, the query) have kernels without that choice: 4096 x 32 x 128 bfloat16 at 3 bits appended in 8.7 us against 9.2 and
+// read in 8.9 against 10.0.
 #include "common.h"
 
 #define QH_THREADS 256
@@ -59,7 +61,7 @@ __device__ __forceinline__ u32 qh_codes8(const float (&x)[8], float s) {
 
 // One head per row of 16 lanes, lane j holding channels 8 j .. 8 j + 7: D <= 128, D % 8 == 0
 // (3 bits: D % 32 == 0, so that the lanes of a quad fill whole words).
-template <typename RawT, int BITS>
+template <typename RawT, int BITS, bool MIXED>
 __global__ __launch_bounds__(QH_THREADS) void quant_heads_row_kernel(
     const RawT* __restrict__ X, int64_t n_heads, int64_t n4, int D, float eps, unsigned char* __restrict__ q_out,
     float* __restrict__ scale_out) {
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(QH_THREADS) void quant_heads_row_kernel(
   for (int e = 0; e < 8; ++e) mx = max(mx, __float_as_uint(x[e]) & 0x7FFFFFFFu);
   mx = qh_row_max_dpp(mx);
   const float gamma = __uint_as_float(mx);
-  if (BITS == 4 || head < n4) {                           // (the same for a whole row of lanes)
+  if (BITS == 4 || (MIXED && head < n4)) {                // (the same for a whole row of lanes)
     const float s = 7.0f / (gamma + eps);
     if (j == 0) scale_out[head] = gamma / 7.0f;
     const u32 v = qh_codes8<4>(x, s);
@@ -90,7 +92,8 @@ __global__ __launch_bounds__(QH_THREADS) void quant_heads_row_kernel(
     const u32 nxt = (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x39, 0xF, 0xF, false);   // quad_perm [1,2,3,0]
     const int jq = j & 3;
     const u32 word = (v >> (8 * jq)) | (nxt << (24 - 8 * jq));
-    if (have && jq < 3) reinterpret_cast<u32*>(q_out + n4 * (D / 2) + (head - n4) * (3 * D / 8) + (j >> 2) * 12)[jq] = word;
+    unsigned char* out = MIXED ? q_out + n4 * (D / 2) + (head - n4) * (3 * D / 8) : q_out + head * (3 * D / 8);
+    if (have && jq < 3) reinterpret_cast<u32*>(out + (j >> 2) * 12)[jq] = word;
   }
 }
 
@@ -112,7 +115,7 @@ __device__ __forceinline__ void qh_code_head(const RawT* x, int D, float gamma, 
   }
 }
 
-template <typename RawT, int BITS>
+template <typename RawT, int BITS, bool MIXED>
 __global__ __launch_bounds__(QH_THREADS) void quant_heads_wave_kernel(
     const RawT* __restrict__ X, int64_t n_heads, int64_t n4, int D, float eps, unsigned char* __restrict__ q_out,
     float* __restrict__ scale_out) {
@@ -126,8 +129,9 @@ __global__ __launch_bounds__(QH_THREADS) void quant_heads_wave_kernel(
     for (int e = 0; e < 8; ++e) mx = max(mx, __float_as_uint(qh_to_f32<RawT>(x[8 * g + e])) & 0x7FFFFFFFu);
   mx = bl_wave_max_u32(mx);
   const float gamma = __uint_as_float(mx);
-  if (BITS == 4 || head < n4) qh_code_head<RawT, 4>(x, D, gamma, eps, q_out + head * (D / 2), scale_out + head);
-  else qh_code_head<RawT, 3>(x, D, gamma, eps, q_out + n4 * (D / 2) + (head - n4) * (3 * D / 8), scale_out + head);
+  if (BITS == 4 || (MIXED && head < n4)) qh_code_head<RawT, 4>(x, D, gamma, eps, q_out + head * (D / 2), scale_out + head);
+  else if (MIXED) qh_code_head<RawT, 3>(x, D, gamma, eps, q_out + n4 * (D / 2) + (head - n4) * (3 * D / 8), scale_out + head);
+  else qh_code_head<RawT, 3>(x, D, gamma, eps, q_out + head * (3 * D / 8), scale_out + head);
 }
 
 // bits = 4: all heads at 4 bits; bits = 3: the first n4 heads at 4 bits (packed before the others), the rest at 3
@@ -137,19 +141,24 @@ int bl_launch_quantize_heads(const void* X, bl_dtype dt, int64_t n_heads, int64_
   const bool rows = D <= 128 && (bits == 4 || D % 32 == 0);
   const unsigned grid = (unsigned)((n_heads + (rows ? QH_THREADS / 16 : QH_THREADS / 64) - 1) /
                                    (rows ? QH_THREADS / 16 : QH_THREADS / 64));
-#define QH_GO(KERN)                                                                                          \
-  do {                                                                                                       \
-    if (dt == BL_BF16) {                                                                                     \
-      if (bits == 4) KERN<uint16_t, 4><<<grid, QH_THREADS, 0, s>>>((const uint16_t*)X, n_heads, n4, D, eps, (unsigned char*)q, scale); \
-      else KERN<uint16_t, 3><<<grid, QH_THREADS, 0, s>>>((const uint16_t*)X, n_heads, n4, D, eps, (unsigned char*)q, scale);           \
-    } else {                                                                                                 \
-      if (bits == 4) KERN<u32, 4><<<grid, QH_THREADS, 0, s>>>((const u32*)X, n_heads, n4, D, eps, (unsigned char*)q, scale);           \
-      else KERN<u32, 3><<<grid, QH_THREADS, 0, s>>>((const u32*)X, n_heads, n4, D, eps, (unsigned char*)q, scale);                     \
-    }                                                                                                        \
+#define QH_ONE(KERN, T, BITS, MIXED) \
+  KERN<T, BITS, MIXED><<<grid, QH_THREADS, 0, s>>>((const T*)X, n_heads, n4, D, eps, (unsigned char*)q, scale)
+#define QH_GO(KERN)                                  \
+  do {                                               \
+    if (dt == BL_BF16) {                             \
+      if (bits == 4) QH_ONE(KERN, uint16_t, 4, false); \
+      else if (n4) QH_ONE(KERN, uint16_t, 3, true);  \
+      else QH_ONE(KERN, uint16_t, 3, false);         \
+    } else {                                         \
+      if (bits == 4) QH_ONE(KERN, u32, 4, false);    \
+      else if (n4) QH_ONE(KERN, u32, 3, true);       \
+      else QH_ONE(KERN, u32, 3, false);              \
+    }                                                \
   } while (0)
   if (rows) QH_GO(quant_heads_row_kernel);
   else QH_GO(quant_heads_wave_kernel);
 #undef QH_GO
+#undef QH_ONE
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
 }
@@ -157,23 +166,31 @@ int bl_launch_quantize_heads(const void* X, bl_dtype dt, int64_t n_heads, int64_
 // ---------------------------------------------------------------- reading the codes back
 // value = (code - 2^(bits-1)) * scale, one float32 multiply (bfloat16 outputs: one rounding more).
 // One thread per group of 8 channels: BITS bytes in, 8 values out.
-template <typename OutT, int BITS>
+template <int BITS>
+__device__ __forceinline__ void qh_values8(const unsigned char* p, float d, float (&x)[8]) {
+  u32 v = 0;
+#pragma unroll
+  for (int b = 0; b < BITS; ++b) v |= (u32)p[b] << (8 * b);
+  constexpr int OFF = 1 << (BITS - 1);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) x[j] = (float)((int)((v >> (BITS * j)) & ((1u << BITS) - 1u)) - OFF) * d;
+}
+
+template <typename OutT, int BITS, bool MIXED>
 __global__ __launch_bounds__(QH_THREADS) void dequant_heads_kernel(
     const unsigned char* __restrict__ q, const float* __restrict__ scale, int64_t n_groups, int64_t n4, int gph,
     OutT* __restrict__ out) {
   const int64_t g = (int64_t)blockIdx.x * QH_THREADS + threadIdx.x;
   if (g >= n_groups) return;
   const float d = scale[g / gph];                          // gph = groups of 8 channels per head
-  const int64_t g4 = BITS == 4 ? n_groups : n4 * gph;      // groups at 4 bits
-  const int bits = g < g4 ? 4 : 3;
-  const unsigned char* p = q + (g < g4 ? 4 * g : 3 * g + g4);
-  u32 v = (u32)p[0] | ((u32)p[1] << 8) | ((u32)p[2] << 16);
-  if (g < g4) v |= (u32)p[3] << 24;
-  const u32 mask = (1u << bits) - 1u;
-  const int off = 1 << (bits - 1);
   float x[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) x[j] = (float)((int)((v >> (bits * j)) & mask) - off) * d;
+  if constexpr (MIXED) {
+    const int64_t g4 = n4 * gph;                           // groups at 4 bits
+    if (g < g4) qh_values8<4>(q + 4 * g, d, x);
+    else qh_values8<3>(q + 3 * g + g4, d, x);
+  } else {
+    qh_values8<BITS>(q + BITS * g, d, x);
+  }
   if (sizeof(OutT) == 2) {
     uint4 w;
     w.x = (u32)bl_f32_to_bf16_rne(x[0]) | ((u32)bl_f32_to_bf16_rne(x[1]) << 16);
@@ -193,9 +210,9 @@ int bl_launch_dequantize_heads(const void* q, const float* scale, int64_t n_head
   const int64_t blocks = (n_groups + QH_THREADS - 1) / QH_THREADS;
   if (!bl_grid_ok(blocks)) return BL_ESHAPE;
   const int gph = (int)(D / 8);
-#define QH_DQ(T, B) dequant_heads_kernel<T, B><<<(unsigned)blocks, QH_THREADS, 0, s>>>((const unsigned char*)q, scale, n_groups, n4, gph, (T*)out)
-  if (odt == BL_BF16) { if (bits == 4) QH_DQ(uint16_t, 4); else QH_DQ(uint16_t, 3); }
-  else { if (bits == 4) QH_DQ(float, 4); else QH_DQ(float, 3); }
+#define QH_DQ(T, B, MIXED) dequant_heads_kernel<T, B, MIXED><<<(unsigned)blocks, QH_THREADS, 0, s>>>((const unsigned char*)q, scale, n_groups, n4, gph, (T*)out)
+  if (odt == BL_BF16) { if (bits == 4) QH_DQ(uint16_t, 4, false); else if (n4) QH_DQ(uint16_t, 3, true); else QH_DQ(uint16_t, 3, false); }
+  else { if (bits == 4) QH_DQ(float, 4, false); else if (n4) QH_DQ(float, 3, true); else QH_DQ(float, 3, false); }
 #undef QH_DQ
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
