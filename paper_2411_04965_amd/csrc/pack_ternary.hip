@@ -212,6 +212,29 @@ __global__ __launch_bounds__(PT_KM_THREADS) void ternarize_pack_kmajor_kernel(
     if (k0 + (i >> 5) < K) dst[i] = words[(i >> 5) * 33 + (i & 31)];
 }
 
+// The same layout, one thread per 32-bit word (channel k, 16 outputs; consecutive threads take consecutive channels, so reads
+// are coalesced and each word is stored where it falls): for matrices with too few blocks of the kernel above.
+template <typename T>
+__global__ __launch_bounds__(PT_THREADS) void ternarize_pack_kmajor_words_kernel(
+    const T* __restrict__ W, int64_t N, int64_t K, float eps, const double* __restrict__ partial, int n_partial,
+    u32* __restrict__ out, float* __restrict__ alpha_out, int64_t n_words) {
+  __shared__ double red[PT_THREADS / BL_WAVE];
+  const float alpha = pt_alpha(partial, n_partial, N * K, red);
+  if (blockIdx.x == 0 && threadIdx.x == 0) alpha_out[0] = alpha;
+  const int64_t id = (int64_t)blockIdx.x * PT_THREADS + threadIdx.x;
+  if (id >= n_words) return;
+  const int64_t k = id % K, d = id / K;
+  u32 word = 0;
+  pt_with_code(alpha + eps, [&](auto code) {
+#pragma unroll
+    for (int f = 0; f < 16; ++f) {
+      const int64_t n = d * 16 + f;
+      if (n < N) word |= code(pt_load<T>(W, n * K + k)) << (2 * f);
+    }
+  });
+  out[((d >> 5) * K + k) * 32 + (d & 31)] = word;
+}
+
 // One thread per 32-bit word of the block-float GEMM layout: blocks of 32 outputs x 128 input
 // channels (2048 bytes); inside, row r = n % 32 takes 64 bytes, its 16-byte piece p holds the
 // 32 channels of unit u = p ^ ((r / 4) % 4) as E2M1 nibbles (0 -> 0000, +1 -> 0010, -1 -> 1010),
@@ -399,8 +422,18 @@ static int pt_run(const T* W, int64_t N, int64_t K, float eps, bl_w_layout layou
         W, N, K, Kp, eps, vec, partial, np, (u32*)out, alpha, n_tiles);
   } else {
     const int64_t k_blocks = (K + 63) / 64, blocks = bl_round_up(N, 512) / 512 * k_blocks;
-    ternarize_pack_kmajor_kernel<T><<<(unsigned)blocks, PT_KM_THREADS, 0, s>>>(
-        W, N, K, eps, vec, partial, np, (u32*)out, alpha, k_blocks);
+    // One word per thread where the 64 x 512 blocks leave too much of the chip idle for their longer chains: fewer than 100 of
+    // them (1024 x 1024, 32 blocks: float32 8.6 us against 9.8, bfloat16 8.6 / 10.5; 1536 x 2048, 96: 10.7 / 11.0, 10.5 / 11.5;
+    // on the other side 2048 x 2048, 128: 13.5 / 11.8, 11.4 / 11.7), or no more than one per CU where rows are not whole groups of four
+    // (1000 x 1001, 32: 8.7 / 14.3, 8.8 / 13.6; 2048 x 4095, 256: 20.4 / 20.6, 17.1 / 20.9).
+    if (vec ? blocks < 100 : blocks <= bl_num_cus()) {
+      const int64_t n_words = K * (bl_round_up(N, 512) / 16);
+      ternarize_pack_kmajor_words_kernel<T><<<(unsigned)((n_words + PT_THREADS - 1) / PT_THREADS), PT_THREADS, 0, s>>>(
+          W, N, K, eps, partial, np, (u32*)out, alpha, n_words);
+    } else {
+      ternarize_pack_kmajor_kernel<T><<<(unsigned)blocks, PT_KM_THREADS, 0, s>>>(
+          W, N, K, eps, vec, partial, np, (u32*)out, alpha, k_blocks);
+    }
   }
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
