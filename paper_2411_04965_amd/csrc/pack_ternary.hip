@@ -89,8 +89,9 @@ __device__ __forceinline__ u32 pt_code(float w, float t) {
   return (u32)c & 3u;                      // two's complement 2-bit: 00, 01, 11
 }
 // The same code by comparison.  The rounded quotient is 0 unless |w| / t, rounded to float32, exceeds 0.5, that is
-// unless |w| > t/2 + t 2^-25 (a quotient nearer to 0.5 rounds to 0.5, whose mantissa is even).  t/2 is a float32 here,
-// and the next float32 above it exceeds it by at least t 2^-24: for a float32 |w| the condition is |w| > t/2.
+// unless |w| > t/2 + t 2^-25 (a quotient no further from 0.5 rounds to 0.5, whose mantissa is even).  t/2 is a float32 here,
+// and for t = m 2^e, 1 <= m < 2, the next float32 above it exceeds it by 2^(e-24), which is strictly more than
+// t 2^-25 = m 2^(e-25): for a float32 |w| the condition is |w| > t/2.
 // Wants a finite t, which says that every weight is finite, and t/2 free of rounding (t well above the subnormals).
 __device__ __forceinline__ u32 pt_ternary_bits(float w, float half) {
   const u32 u = __float_as_uint(w);

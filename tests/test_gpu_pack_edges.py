@@ -40,3 +40,33 @@ def test_kmajor_rule(N, K, dtype):
     print("[case] pack K-major N=%d K=%d %s" % (N, K, dtype), flush=True)
     W = S.latent_weights(N, K, S.seed_for(7, N + K))
     check(S.snap_bf16(W) if dtype == BF16 else W, B.BL_W_KMAJOR, dtype)
+
+
+def boundary(N, K, t):
+    """Weights whose mean is t: mostly +-t, and every 32nd one just below t/2, t/2 or just above it, next to a +-3t/2."""
+    half = np.float32(t / 2)
+    special = [np.nextafter(half, np.float32(0)), half, np.nextafter(half, np.float32(np.inf))]
+    W = np.full(N * K, t, dtype=np.float32)
+    W[1::2] *= -1
+    for i, b in enumerate(range(0, N * K - 32, 32)):
+        sign = 1 if i & 1 else -1
+        W[b + i % 23] = sign * special[i % 3]
+        W[b + i % 23 + 1] = sign * np.float32(1.5) * t
+    return W.reshape(N, K), special
+
+
+# the comparison holds from 2^-100 to 2^100; outside, the quotient of eq. 2 is formed
+@pytest.mark.parametrize("layout", sorted(DECODE))
+@pytest.mark.parametrize("e", [-127, -110, -101, -100, -99, -6, 0, 99, 100, 101, 126])
+def test_rounding_boundary(e, layout):
+    """The float32 neighbours of half the scale: t/2 and less are 0 (half to even), the next number above is 1, at any scale."""
+    print("[case] pack boundary 2^%d layout=%d" % (e, layout), flush=True)
+    for m in (1.0, 1.0 + 2.0 ** -23, 1.5, 2.0 - 2.0 ** -23):
+        t = np.float32(np.ldexp(m, e))
+        for K in (203, 204):
+            W, special = boundary(35, K, t)
+            T, alpha = O.ternarize(W, 0.0)
+            assert alpha == t
+            for s, c in zip(special, (0, 0, 1)):
+                assert (np.abs(T[np.abs(W) == s]) == c).all()
+            check(W, layout, eps=0.0, ref=(T, alpha))
