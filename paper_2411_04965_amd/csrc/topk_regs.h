@@ -349,6 +349,7 @@ template <int CPW, bool EARLY = false>
 __device__ __forceinline__ void qa_topk_row_regs8(const u32 (&raw)[CPW][2], int nc, int c_begin, int topk, float eps,
                                                   u32* out, float* scale_out, u32* sh) {
   static_assert(CPW == 4 || CPW == 8, "16 or 32 keys per lane");
+  static_assert(!EARLY || CPW == 4, "the early count reads one block of bit planes");
   constexpr int NBK = CPW / 4;
   typedef unsigned short us2 __attribute__((ext_vector_type(2)));
   const int tid = threadIdx.x, lane = tid & 63;
@@ -421,13 +422,12 @@ __device__ __forceinline__ void qa_topk_row_regs8(const u32 (&raw)[CPW][2], int 
   // keys of chunks this wave does not have stay out: they would count as members of the lowest class
   u32 act = nc >= 8 ? ~0u : ((1u << (4 * nc)) - 1u);
   if (NBK == 1) act &= 0xFFFFu;
-  // EARLY (rows of 4097 to 8192 channels: FFN states of smaller models, 5460 of a 1.3B model): the same shortcut, with
-  // its count riding on the first pass (in the place of class 0, which only the last pass uses) instead of on a barrier of its own.
-  // 57 rows of 5460 channels, most of them zeros: 5.8 -> 3.9 us.  Rows of up to 4096 channels are mostly attention
-  // outputs, which are dense: there the count alone cost 0.4 us (32 rows of 4096 channels).
-  const bool early = EARLY && C > 0u;
+  // EARLY (rows of 4097 to 8192 channels): the same shortcut, with its count riding on the first pass (in the place of
+  // class 0, which only the last pass uses) instead of on a barrier of its own.  Such rows are FFN states of smaller models, mostly
+  // zeros: 64 rows of 5460 channels 5.3 -> 3.3 us.  Dense rows pay for the count and the branch (5.6 -> 5.8), so rows of up to
+  // 4096 channels, which are attention outputs as often as FFN states (32 dense rows of 4096: 0.4 us more), go without.
   u32 n_hi = 0;
-  if (early) {
+  if constexpr (EARLY) {
 #pragma unroll
     for (int i = 0; i < 5; ++i) n_hi |= pl[0][i];
     n_hi = (u32)__popc((n_hi | (n_hi >> 16) | pl[0][5]) & act);   // keys' > 0 (11 planes: five words and the low half of the sixth)
@@ -455,7 +455,7 @@ __device__ __forceinline__ void qa_topk_row_regs8(const u32 (&raw)[CPW][2], int 
     w[0] = (u32)__popc(m[1]) | ((u32)__popc(m[2]) << 16);
     w[1] = (u32)__popc(m[3]) | ((u32)__popc(m[4]) << 16);
     w[2] = (u32)__popc(m[5]) | ((u32)__popc(m[6]) << 16);
-    w[3] = (u32)__popc(m[7]) | ((early && p == 0 ? n_hi : (u32)__popc(m[0])) << 16);
+    w[3] = (u32)__popc(m[7]) | ((EARLY && p == 0 ? n_hi : (u32)__popc(m[0])) << 16);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       int v = (int)w[j];
@@ -475,7 +475,7 @@ __device__ __forceinline__ void qa_topk_row_regs8(const u32 (&raw)[CPW][2], int 
     const u32 t1 = (u32)__builtin_amdgcn_readfirstlane((int)qa_sum8_dpp(q.y));
     const u32 t2 = (u32)__builtin_amdgcn_readfirstlane((int)qa_sum8_dpp(q.z));
     const u32 t3 = (u32)__builtin_amdgcn_readfirstlane((int)qa_sum8_dpp(q.w));
-    if (early && p == 0 && (int)(t3 >> 16) <= topk) {     // workgroup-uniform
+    if (EARLY && p == 0 && C > 0u && (int)(t3 >> 16) <= topk) {   // workgroup-uniform
       int sum = 0;
       qa_code_chunks<CPW>(raw, pg, nc, C, 0, 0, 0, s, out + c_begin * 64 + lane, sum, false);
       return;
