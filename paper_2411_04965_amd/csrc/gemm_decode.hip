@@ -1,4 +1,4 @@
-// Decode-shaped linears (1 to 32 tokens; 33 to 64 go on to gemm_mid.hip): the packed ternary weights are streamed from HBM once.
+// Decode-shaped linears (1 to 64 tokens; most of 33 to 64 go on to gemm_mid.hip): the packed ternary weights are streamed from HBM once.
 //   Dense path  (BL_W_GEMM tiles):   skinny int8-MFMA GEMM; three kernels by token count.
 //   Sparse path (BL_W_KMAJOR rows):  eq. 1's sparsity used for I/O — only the weight rows of
 //                                    channels whose INT8 code is non-zero in some token are read.
@@ -626,10 +626,11 @@ __global__ __launch_bounds__(GD_THREADS) void gemm_decode_rows_kernel(
   }
 }
 
-// 17 to 32 tokens.  The tokens' codes are the larger stream here (a block of 16 outputs reads 4 KB
-// of weights per 1024 channels but 32 KB of codes), and split-K partial sums cost as much
+// 17 to 32 tokens, and 33 to 64 where K is long and the outputs few (gr_long_k).  The tokens' codes are the larger
+// stream here (a block of 16 outputs reads 4 KB
+// of weights per 1024 channels but 32 to 64 KB of codes), and split-K partial sums cost as much
 // again.  So the codes stay put: one block of 16 waves per CU keeps the codes of all tokens for its
-// slice of K in LDS (up to 128 KB: all of K for INT4 codes at 8192 channels) and streams the weight
+// slice of K in LDS (up to 128 KB: all of K for INT4 codes of 32 tokens at 8192 channels) and streams the weight
 // tiles of its NWT output tiles past them.  The output tiles go in groups of up to GR_G to the
 // waves, so that one expansion of a token fragment (nibbles to bytes) serves GR_G matrix
 // instructions; wave u works on group u / KS and on part u % KS of the slice.  The parts are added
@@ -879,11 +880,31 @@ __global__ __launch_bounds__(GD_THREADS) void decode_reduce_kernel(
 
 // Kernel choice.  Up to 16 tokens (one MFMA tile of tokens) with enough output tiles to fill the
 // chip: one 16-output tile per block, no split of K, one launch.  Up to 16 tokens and few outputs:
-// 64 outputs per block and K split until the grid is large.  17 to 32 tokens: codes resident in LDS.  More: gemm_mid.hip, which
-// needs no workspace (the split still sizes one there, so that calls are accepted and refused by one rule).
+// 64 outputs per block and K split until the grid is large.  17 to 32 tokens: codes resident in LDS.  More: resident where K is
+// long, else gemm_mid.hip, which needs no workspace (the split sizes one for both, so that calls are accepted and refused by
+// one rule).
 static bool gd_single_tile(int M, int N) { return M <= 16 && (N + 15) / 16 >= 128; }
-// resident kernel: tiles of K per slice so that 16 * MT rows of codes fit
+// resident kernel: tiles of K per slice so that 16 * MT rows of codes fit; output tiles per block at most one per wave
+// (64 tokens: 12, so that the partial tiles and the sums fit the LDS together)
 static int gr_slice_tiles(int MT, bool a4) { return GR_X_BYTES / (MT * 16) / (a4 ? 128 : 256); }
+static int gr_nwt_max(int MT) { return MT == 4 ? 12 : GR_WAVES; }
+// 33 to 64 tokens: long K and few outputs.  The tiles of gemm_mid.hip do not split K over blocks, so there a block's chain of
+// steps is what counts (INT8 64 x 256 x 32768: 39.8 us; 12.8 here), while the split here costs partial sums that grow with the
+// outputs (64 x 8192 x 8192: 19.4 here, 13.6 there) and a second turn of the chip where the blocks are more than the CUs (33 x 5120 x
+// 20480: 28.7 / 25.1).  So from some length of K on (INT4 codes have half the slices but the longer step there; below 40 tokens the
+// step there is shorter) outputs up to a number that grows with K.  Weights from HBM, here / there:
+//   INT8, 64 tokens: 1024 x 6144 11.4 / 11.6; 1024 x 6656 10 % less here; 2048 x 7936 12.7 / 13.8; 2048 x 8192 12.7 / 13.1, 3072 x 8192
+//   13.5 / 13.3; 4096 x 9728 16.0 / 17.0; 4096 x 11008 16.8 / 18.2, 5120 x 11008 18.5 / 18.4, 6144 x 11008 19.6 / 18.5; 6144 x 13824
+//   19.8 / 22.2; 33 tokens: 1024 x 6656 6 % more here, 512 x 7168 level, 1024 x 8192 11.5 / 11.7
+//   INT4, 33 tokens: 512 x 8192 12.4 / 12.5, 1024 x 8192 13.2 / 12.6; 1024 x 8704 12.8 / 13.7; 3072 x 9728 14.3 / 15.2; 4096 x 10240
+//   15.9 / 15.0, 4096 x 12288 16.4 / 17.2; 5120 x 13824 17.9 / 19.6; 6144 x 16384 19.3 / 22.1
+static bool gr_long_k(int M, int N, int KT, bool a4) {
+  if (a4) return KT >= 30 && N <= max(512, min(min(512 * (KT - 31), 176 * (KT - 20)), 6144));
+  const int slices = (KT + gr_slice_tiles(4, false) - 1) / gr_slice_tiles(4, false), per_block = 16 * gr_nwt_max(4);
+  if (KT < 96 && (N + per_block - 1) / per_block * slices > bl_num_cus()) return false;   // (from 96 on two turns are still level)
+  const bool more = M >= 40;
+  return KT >= (more ? 26 : 29) && N <= max(2048, min(512 * (KT - (more ? 28 : 30)), KT < 52 ? 5120 : 6144));
+}
 static int gd_pick_split(int M, int N, int KT, bool a4) {
   if (gd_single_tile(M, N)) return 1;
   if (M > 16) {
@@ -937,11 +958,10 @@ static int gd_run(const void* q, const float* scale, int M, int Kp, const void* 
   return S > 1 ? gd_reduce(S, M, N, A4 ? 10 : 6, scale, alpha, Y, ybf, acc_out, ws, s) : BL_OK;
 }
 
-template <bool A4>
+template <int MT, bool A4>
 static int gr_run(const void* q, const float* scale, int M, int Kp, const void* Wp,
                   const float* alpha, int N, void* Y, bl_dtype ydt, int32_t* acc_out, void* ws,
                   hipStream_t s) {
-  constexpr int MT = 2;
   const int KT = Kp >> 8, NT16 = (N + 15) / 16;
   const int S = gd_pick_split(M, N, KT, A4);
   if (S > 1 && !ws) return BL_EWORKSPACE;
@@ -949,7 +969,7 @@ static int gr_run(const void* q, const float* scale, int M, int Kp, const void* 
   // output tiles per block: as few as still give at most one block per CU (one block takes most
   // of a CU's LDS), at most one per wave
   int NWT = 1;
-  while (NWT < GR_WAVES && ((NT16 + NWT - 1) / NWT) * S > bl_num_cus()) ++NWT;
+  while (NWT < gr_nwt_max(MT) && ((NT16 + NWT - 1) / NWT) * S > bl_num_cus()) ++NWT;
   const int NBn = (NT16 + NWT - 1) / NWT;
   const int NG = (NWT + GR_G - 1) / GR_G;                // groups of output tiles, one per wave
   // parts of the slice per group: every part gets at least one tile; at most 8 working waves (two
@@ -1003,7 +1023,8 @@ bool bl_gemm_decode_glu_ok(int64_t M, int64_t N, int64_t K) {
 // q: INT4 nibble codes [M][Kp / 2] with their scales; H [M, N] bfloat16.
 int bl_launch_gemm_decode_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,
                               const void* Wu, const float* au, int64_t N, void* H, hipStream_t s) {
-  // (more than 32 tokens: 57 x 2 x 5460 x 2048 9.5 us with the codes in LDS, 7.9 with the tiles of gemm_mid.hip)
+  // (more than 32 tokens, weights from HBM: 64 x 2 x 5460 x 2048 11.8 us with the codes in LDS, 10.3 with the tiles of gemm_mid.hip;
+  // 64 x 2 x 2688 x 1024 8.8 / 8.4; 33 x 2 x 11008 x 4096 18.5 / 14.5)
   if (M > 32) return bl_launch_gemm_mid_a4_glu(q, scale, M, K, Wg, ag, Wu, au, N, H, s);
   int NWT, KS, NBn;
   size_t smem;
@@ -1104,9 +1125,10 @@ int bl_launch_gemm_decode(const void* q, const float* scale, bl_act_mode mode, i
 #define GD_ARGS q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, ws, s
   if (gd_single_tile((int)M, (int)N)) return a4 ? gd_run<1, true, true>(GD_ARGS) : gd_run<1, false, true>(GD_ARGS);
   if (M <= 16) return a4 ? gd_run<1, true, false>(GD_ARGS) : gd_run<1, false, false>(GD_ARGS);
-  // (more than 32 tokens: see the head of gemm_mid.hip.  At 32 the two kernels are level -- 4096 x 4096 8.0 us against 7.9,
-  // 4096 x 11008 13.5 / 14.0 -- and below the codes' share of the traffic speaks for keeping them in LDS)
-  if (M <= 32) return a4 ? gr_run<true>(GD_ARGS) : gr_run<false>(GD_ARGS);
+  // (at 32 tokens, weights from HBM, here / in gemm_mid.hip: INT8 4096 x 4096 7.9 us / 8.0, 4096 x 11008 13.3 / 15.2, 12288 x 4096
+  // 9.0 / 8.6, 2048 x 5460 10.5 / 9.9; INT4 7.5 / 8.3, 12.7 / 16.2, 8.6 / 8.7, 7.9 / 10.4)
+  if (M <= 32) return a4 ? gr_run<2, true>(GD_ARGS) : gr_run<2, false>(GD_ARGS);
+  if (gr_long_k((int)M, (int)N, Kp >> 8, a4)) return a4 ? gr_run<4, true>(GD_ARGS) : gr_run<4, false>(GD_ARGS);
   return bl_launch_gemm_mid(q, scale, mode, M, K, Wp, alpha, N, Y, ydt, acc_out, s);
 #undef GD_ARGS
 }

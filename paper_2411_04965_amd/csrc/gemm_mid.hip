@@ -9,10 +9,12 @@
 // activations go through LDS: weights are 2-bit codes, which a lane fetches in fragment order (16 bytes serve 64
 // channels of one output) and expands in registers between the MFMAs.  For a 128 x 128 tile LDS then takes 32 KB of writes
 // and 64 KB of reads per step (about 800 cycles of 1024 of INT8 matrix work), where a tile that also expands the
-// weights into LDS moves 64 + 128 KB.  Measured, product alone (before: 256 x 256 and 128 x 128 tiles with one step of
-// prefetch): INT8 200 x 3200 x 8640 34.8 -> 12.8 us, 1000 x 4096 x 11008 45.8 -> 38.8, 2048 x 2048 x 5460 54.5 -> 22.3,
-// 2048 x 4096 x 11008 100 -> 71 (2.6 POPS); 64 tokens (before: the kernel that keeps the codes in LDS, and a second launch for
-// the sums where K is split): INT8 64 x 4096 x 4096 12.7 -> 8.0, 64 x 4096 x 11008 17.6 -> 14.0, 57 x 2048 x 5460 12.2 -> 9.6; INT4 200 x 9600 x 3200 22.3 -> 10.8, gate/up of 200 x 2 x 8640 x 3200 21.6 -> 14.9.
+// weights into LDS moves 64 + 128 KB.  Measured, product alone, weights from HBM (before: 256 x 256 and
+// 128 x 128 tiles with one step of prefetch): INT8 200 x 3200 x 8640 44.3 -> 14.3 us, 1000 x 4096 x 11008 55.5 -> 40.7,
+// 2048 x 2048 x 5460 55.5 -> 23.2, 2048 x 4096 x 11008 109 -> 74 (2.5 POPS); INT4 200 x 9600 x 3200 22.4 -> 13.1, gate/up of
+// 130 x 2 x 8640 x 3200 25.7 -> 16.9.  64 tokens (before: the kernel that keeps the codes in LDS, and a second launch for the sums
+// where K is split, which is still the better one for long K and few outputs: gr_long_k): INT8 64 x 4096 x 4096 12.5 -> 9.1,
+// 64 x 12288 x 4096 17.8 -> 9.7, 64 x 2048 x 5460 12.2 -> 11.4; gate/up of 64 x 2 x 11008 x 4096 18.4 -> 14.2.
 //
 // Structure.  A group of 4 waves (2 x 2) owns a tile of 64 TM x 64 TN; a wave has TM x TN MFMA tiles (row operand =
 // weights, column operand = tokens, so a lane ends up with groups of 4 consecutive outputs of one token).  One step =
@@ -438,7 +440,8 @@ static int gm_go(const void* q, const float* scale, int M, int KT, const void* W
   return BL_OK;
 }
 
-// ---- dispatch rules.  Costs in turns of the chip (tiles over CUs, rounded up).
+// ---- dispatch rules.  Costs in turns of the chip (tiles over CUs, rounded up).  (The figures below are of repeated calls on one
+// weight matrix; with weights from HBM few tokens take 1 to 2 us more on either side.)
 static int64_t gm_turns(int64_t M, int64_t N, int bm, int bn) {
   const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), cus = bl_num_cus();
   return (tiles + cus - 1) / cus;

@@ -103,3 +103,24 @@ def test_decode_tokens(M, N, K, mul):
     assert torch.equal(y, y4) and torch.equal(acc, acc4.int())
     h = B.bitlinear_a4_gate_up(X, p, a, pu, au, N, want=("H",))["H"]
     assert torch.equal(h, (u4 * y4.clamp_min(0.0).square()).to(BF16))
+
+
+# more than 32 tokens: both sides of the rule on long K (INT8 codes: from 26 K tiles on, from 29 below 40 tokens, with outputs up
+# to 2048, 512 per K tile beyond 28 or 30, 5120 or 6144; INT4 codes: from 30 on with 512, or 512 per tile beyond 31 and 176 per tile
+# beyond 20), one and two turns of the chip
+@pytest.mark.parametrize("M,N,K", [(40, 70, 6401), (39, 70, 7168), (64, 2048, 6656), (64, 2049, 6500), (33, 2048, 7937), (47, 512, 7600),
+                                   (64, 513, 7680), (64, 2560, 9216), (40, 2561, 9000), (64, 5120, 10241), (57, 5121, 9985),
+                                   (35, 4916, 20480), (50, 6144, 13500), (33, 333, 32768), (64, 6144, 24577)])
+def test_decode_tokens_long_k(M, N, K):
+    """33 to 64 tokens with K split over blocks and without, bit for bit."""
+    print("[case] decode long K M=%d N=%d K=%d" % (M, N, K), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    X = torch.randn((M, K), generator=g, device="cuda").to(BF16)
+    W = 0.02 * torch.randn((N, K), generator=g, device="cuda")
+    p, a = B.pack_ternary(W)
+    for mode, call in ((B.BL_ACT_TOPK_INT8_ABSMAX, lambda **kw: B.bitlinear_a8_sparse(X, K // 2, p, a, N, **kw)),
+                       (B.BL_ACT_INT4_ABSMEAN, lambda **kw: B.bitlinear_a4(X, p, a, N, **kw))):
+        acc_ref, y_ref = product(X, W, mode, K // 2)
+        assert torch.equal(call(), y_ref.to(BF16))
+        y, acc = call(y_dtype=torch.float32, want_acc=True)
+        assert torch.equal(y, y_ref) and torch.equal(acc, acc_ref.int())
