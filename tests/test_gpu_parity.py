@@ -412,7 +412,7 @@ def test_config0_pair():
 @pytest.mark.parametrize("M,N,K", [(300, 520, 1000), (130, 2048, 5460), (257, 5460, 2048),
                                    (1100, 1100, 768)])
 def test_prefill_gemm_shapes(M, N, K):
-    """Several tiles, ragged M / N / K tails, both tile sizes, both activation formats."""
+    """Several tiles, ragged M / N / K tails, both activation formats (every tile size: test_gpu_prefill_tiles.py)."""
     say("prefill M=%d N=%d K=%d" % (M, N, K))
     X = S.heavy(M, K, S.seed_for(1, M + N))
     W = S.latent_weights(N, K, S.seed_for(1, K + N + 1))

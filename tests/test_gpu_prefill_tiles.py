@@ -124,3 +124,25 @@ def test_decode_tokens_long_k(M, N, K):
         assert torch.equal(call(), y_ref.to(BF16))
         y, acc = call(y_dtype=torch.float32, want_acc=True)
         assert torch.equal(y, y_ref) and torch.equal(acc, acc_ref.int())
+
+
+# (tokens, outputs, channels) for which the persistent kernels' blocks walk on to a second tile (416 tiles of 256 x 256 on 256 CUs),
+# with rows whose length is no multiple of 8 in bfloat16 and a multiple of 4 in float32
+@pytest.mark.parametrize("M,N,K", [(8190, 3197, 300), (8190, 3196, 777)])
+def test_blocks_walk_on(M, N, K):
+    """Persistent blocks with ragged rows, both code formats, bfloat16 and float32 outputs and accumulators, bit for bit."""
+    print("[case] walk M=%d N=%d K=%d" % (M, N, K), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    X = torch.randn((M, K), generator=g, device="cuda").to(BF16)
+    W = 0.02 * torch.randn((N, K), generator=g, device="cuda")
+    p, a = B.pack_ternary(W)
+    for mode, call in ((B.BL_ACT_TOPK_INT8_ABSMAX, lambda **kw: B.bitlinear_a8_sparse(X, K // 2, p, a, N, **kw)),
+                       (B.BL_ACT_INT4_ABSMEAN, lambda **kw: B.bitlinear_a4(X, p, a, N, **kw))):
+        acc_ref, y_ref = product(X, W, mode, K // 2)
+        assert torch.equal(call(), y_ref.to(BF16))
+        for dt in (BF16, torch.float32):
+            y, acc = call(y_dtype=dt, want_acc=True)
+            assert torch.equal(y, y_ref.to(dt)) and torch.equal(acc, acc_ref.int())
+    for layout in (B.BL_W_MX2, B.BL_W_MX4):
+        p2, a2 = B.pack_ternary(W, layout=layout)
+        assert torch.equal(B.bitlinear_a4(X, p2, a2, N, layout=layout), y_ref.to(BF16))
