@@ -336,7 +336,7 @@ static int gemm_dispatch(const void* q, const void* scale, bl_act_mode mode, int
     return bl_launch_gemm_decode(q, (const float*)scale, mode, M, K, W_packed, alpha, N, Y,
                                  y_dtype, acc_out, ws, s);
   }
-  if (bl_gemm_mid_ok(M, N))
+  if (!bl_gemm_prefill_small_ok(M, N, K, mode == BL_ACT_INT4_ABSMEAN) && bl_gemm_mid_ok(M, N))
     return bl_launch_gemm_mid(q, (const float*)scale, mode, M, K, W_packed, alpha, N, Y, y_dtype, acc_out, s);
   return bl_launch_gemm_prefill(q, (const float*)scale, mode, M, K, W_packed, alpha, N, Y,
                                 y_dtype, acc_out, s);

@@ -146,6 +146,7 @@ int bl_launch_quantize_heads(const void* X, bl_dtype dt, int64_t n_heads, int64_
                              void* q, float* scale, hipStream_t s);
 int bl_launch_dequantize_heads(const void* q, const float* scale, int64_t n_heads, int64_t n4, int64_t D, int bits, void* out,
                                bl_dtype odt, hipStream_t s);
+bool bl_gemm_prefill_small_ok(int64_t M, int64_t N, int64_t K, bool a4);
 int bl_launch_gemm_prefill(const void* q, const float* scale, bl_act_mode mode, int64_t M,
                            int64_t K, const void* Wp, const float* alpha, int64_t N, void* Y,
                            bl_dtype ydt, int32_t* acc_out, hipStream_t s);

@@ -9,7 +9,8 @@
 // two and is folded exactly into the per-token scale in the epilogue.
 // |1024 * acc| <= 8 * K * 1024 < 2^31 for K <= 32768.
 //
-// For problems with enough 256 x 256 tiles; the others take gemm_mid.hip.
+// For problems with enough 256 x 256 tiles, and in 128 x 128 tiles for those of short K and few outputs; the others take
+// gemm_mid.hip.
 //
 // Structure.  Persistent blocks (one per CU) walk the tile list.  Block = 4 waves, tile
 // BM x BN, each wave (BM/2) x (BN/2) as 32x32 MFMA tiles; the MFMA's row operand is the weight
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
   // GP_PIN_OUT uses the results (they cannot be computed later).
 #define GP_PIN_IN(x) asm volatile("" : "+v"(x))
 #define GP_PIN_OUT(x, y) asm volatile("" ::"v"(x), "v"(y))
-  static_assert(TM == 4 && TN == 4, "the interleaving below assumes a 128 x 128 wave tile");
+  static_assert(TM == TN && (TN == 2 || TN == 4), "the interleaving below assumes a square wave tile");
   constexpr int ROWS = 2 * TN;                   // MFMA rows (one weight fragment each) per half step
   static_assert(NWR_A == ROWS && NWR_B == ROWS, "one A write and one B write per MFMA row");
   constexpr int A_EVERY = ROWS / LA, B_EVERY = ROWS / LB;
@@ -295,20 +296,21 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
 #pragma unroll
             for (int b = 0; b < TM; ++b) {
               GP_MFMA(acc[a][b], wF[sub][a], xF[sub][b]);
-              // slots behind MFMA b of this row (4 per row)
-              if (b == 0) {
+              // slots behind MFMA b of this row (4 per row; a 2-MFMA row takes two at a time)
+              const int s0 = (TM == 4) ? b : 2 * b, s1 = (TM == 4) ? b : 2 * b + 1;
+              if (s0 == 0) {
                 xS[sub][a] = read_x(stage, 2 + sub, a);
                 wS[sub][a] = read_w(stage, 2 + sub, a);
               }
-              if (b == 1) {
+              if (s0 <= 1 && 1 <= s1) {
                 if (hrow > 0) store_b(st_other, hrow - 1, cw_prev);
               }
-              if (b == 2) {
+              if (s0 <= 2 && 2 <= s1) {
                 GP_PIN_IN(w);
                 cw.x = (w << 6) & MB; cw.y = (w << 4) & MB;
                 GP_PIN_OUT(cw.x, cw.y);
               }
-              if (b == 3) {
+              if (s0 <= 3 && 3 <= s1) {
                 GP_PIN_IN(w);
                 cw.z = (w << 2) & MB; cw.w = w & MB;
                 GP_PIN_OUT(cw.z, cw.w);
@@ -342,25 +344,26 @@ __global__ __launch_bounds__(GP_THREADS, 1) void gemm_prefill_kernel(
 #pragma unroll
             for (int b = 0; b < TM; ++b) {
               GP_MFMA(acc[a][b], wS[sub][a], xS[sub][b]);
-              if (b == 0) {
+              const int s0 = (TM == 4) ? b : 2 * b, s1 = (TM == 4) ? b : 2 * b + 1;
+              if (s0 == 0) {
                 xF[sub][a] = read_x(stage ^ 1, sub, a);
                 wF[sub][a] = read_w(stage ^ 1, sub, a);
               }
-              if (b == 1) {
+              if (s0 <= 1 && 1 <= s1) {
                 if (A4) {
                   if (hrow > 0) store_a(st_own, hrow - 1, cx_prev);
                 } else {                          // INT8: a plain copy, nothing to wait for
                   store_a(st_own, hrow, make_uint4(a_reg[hrow].x, a_reg[hrow].y, a_reg[hrow].z, a_reg[hrow].w));
                 }
               }
-              if (b == 2) {
+              if (s0 <= 2 && 2 <= s1) {
                 if (A4) {
                   GP_PIN_IN(x0);
                   cx.x = (x0 << 4) & MA; cx.y = x0 & MA;
                   GP_PIN_OUT(cx.x, cx.y);
                 }
               }
-              if (b == 3) {
+              if (s0 <= 3 && 3 <= s1) {
                 if (A4) {
                   GP_PIN_IN(x1);
                   cx.z = (x1 << 4) & MA; cx.w = x1 & MA;
@@ -528,8 +531,9 @@ static int gp_go(const void* q, const float* scale, int M, int Kp, const void* W
                  void* Y, int32_t* acc_out, int MT, int NTB, hipStream_t s) {
   constexpr int smem = GpSmem<BM, BN>::total;
   BL_SET_MAX_LDS_ONCE((gemm_prefill_kernel<BM, BN, A4, OUT, ACC>), smem);
-  // persistent blocks: one per CU (128 KB of LDS, 512 registers per lane)
-  const int grid = min(MT * NTB, bl_num_cus());
+  // persistent blocks: one per CU for the large tile (128 KB of LDS, 512 registers per lane), two for the small one
+  const int per_cu = BM == 256 ? 1 : 2;
+  const int grid = min(MT * NTB, bl_num_cus() * per_cu);
   gemm_prefill_kernel<BM, BN, A4, OUT, ACC><<<(unsigned)grid, GP_THREADS, smem, s>>>(
       (const unsigned char*)q, scale, M, Kp, (const unsigned char*)Wp, alpha, N, Y, acc_out, MT, NTB);
   BL_HIP_CHECK_LAUNCH();
@@ -548,11 +552,26 @@ static int gp_launch(const void* q, const float* scale, int M, int Kp, const voi
 #undef GP_CALL
 }
 
+// 128 x 128 tiles for short K and fewer than 1024 outputs: there a tile's fixed parts are what counts, and a persistent block has the
+// first step of its next tile in flight while it writes the last one (the blocks of gemm_mid.hip take one tile each).  One step of
+// 256 channels and more than a third of a turn of the chip, or for INT8 codes up to three steps and more than a turn.  Weights from
+// HBM, here / without: INT8 32768 x 768 x 256 18.1 us / 24.1, 8192 x 512 x 256 7.1 / 7.5, 4096 x 512 x 256 6.3 / 7.0, 2048 x 512 x 256
+// 6.0 / 5.8; 16384 x 768 x 768 17.1 / 19.4, 65536 x 256 x 512 18.0 / 20.5, 8192 x 512 x 512 8.1 / 7.5, 16384 x 512 x 1024 15.0 / 14.4;
+// INT4 32768 x 768 x 256 19.0 / 21.8, 16384 x 512 x 512 11.3 / 10.4.  (From 1024 outputs on they were never used; 8192 x 2048 x
+// 256 would take 14.2 instead of 15.8.)
+bool bl_gemm_prefill_small_ok(int64_t M, int64_t N, int64_t K, bool a4) {
+  const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), cus = bl_num_cus();
+  return N < 1024 && ((K <= 256 && 3 * tiles > cus) || (!a4 && K <= 768 && tiles > cus));
+}
+
 int bl_launch_gemm_prefill(const void* q, const float* scale, bl_act_mode mode, int64_t M,
                            int64_t K, const void* Wp, const float* alpha, int64_t N, void* Y,
                            bl_dtype ydt, int32_t* acc_out, hipStream_t s) {
   const int Kp = (int)bl_round_up(K, BL_KPAD);
   const bool a4 = mode == BL_ACT_INT4_ABSMEAN;
-  if (a4) return gp_launch<256, 256, true>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s);
-  return gp_launch<256, 256, false>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s);
+#define GP_TILES(B) \
+  (a4 ? gp_launch<B, B, true>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s) \
+      : gp_launch<B, B, false>(q, scale, (int)M, Kp, Wp, alpha, (int)N, Y, ydt, acc_out, s))
+  return bl_gemm_prefill_small_ok(M, N, K, a4) ? GP_TILES(128) : GP_TILES(256);
+#undef GP_TILES
 }

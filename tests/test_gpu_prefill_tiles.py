@@ -126,9 +126,11 @@ def test_decode_tokens_long_k(M, N, K):
         assert torch.equal(y, y_ref) and torch.equal(acc, acc_ref.int())
 
 
-# (tokens, outputs, channels) for which the persistent kernels' blocks walk on to a second tile (416 tiles of 256 x 256 on 256 CUs),
-# with rows whose length is no multiple of 8 in bfloat16 and a multiple of 4 in float32
-@pytest.mark.parametrize("M,N,K", [(8190, 3197, 300), (8190, 3196, 777)])
+# (tokens, outputs, channels) for which the persistent kernels' blocks walk on to a second tile, on 256 CUs, with rows whose length is
+# no multiple of 8 in bfloat16 and a multiple of 4 in float32: 256 x 256 tiles (416 of them), 128 x 128 tiles for short K and few
+# outputs (645 with three steps of K for INT8 codes, 645 and 96 with one step)
+@pytest.mark.parametrize("M,N,K", [(8190, 3197, 300), (8190, 3196, 777), (16500, 515, 700), (16500, 516, 513), (16500, 517, 256),
+                                   (16500, 516, 255), (3000, 389, 256)])
 def test_blocks_walk_on(M, N, K):
     """Persistent blocks with ragged rows, both code formats, bfloat16 and float32 outputs and accumulators, bit for bit."""
     print("[case] walk M=%d N=%d K=%d" % (M, N, K), flush=True)
