@@ -148,3 +148,22 @@ def test_blocks_walk_on(M, N, K):
     for layout in (B.BL_W_MX2, B.BL_W_MX4):
         p2, a2 = B.pack_ternary(W, layout=layout)
         assert torch.equal(B.bitlinear_a4(X, p2, a2, N, layout=layout), y_ref.to(BF16))
+
+
+@pytest.mark.parametrize("layout", [B.BL_W_MX2, B.BL_W_MX4])
+@pytest.mark.parametrize("M,N,K", [(8190, 3197, 300), (8190, 3196, 777), (300, 517, 256)])
+def test_block_float_outputs(M, N, K, layout):
+    """The block-float GEMMs in every output form, blocks that walk on to a second tile among them: INT4 codes bit for bit; FP4 codes,
+    whose two output types round the same float32 sums, against each other."""
+    print("[case] block float M=%d N=%d K=%d layout=%d" % (M, N, K, layout), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    X = torch.randn((M, K), generator=g, device="cuda").to(BF16)
+    W = 0.02 * torch.randn((N, K), generator=g, device="cuda")
+    acc_ref, y_ref = product(X, W, B.BL_ACT_INT4_ABSMEAN)
+    p, a = B.pack_ternary(W, layout=layout)
+    for dt in (BF16, torch.float32):
+        assert torch.equal(B.bitlinear_a4(X, p, a, N, layout=layout, y_dtype=dt), y_ref.to(dt))
+        y, acc = B.bitlinear_a4(X, p, a, N, layout=layout, y_dtype=dt, want_acc=True)
+        assert torch.equal(y, y_ref.to(dt)) and torch.equal(acc, acc_ref.int())
+    y = B.bitlinear_a4(X, p, a, N, layout=layout, act_fp4=True, y_dtype=torch.float32)
+    assert torch.equal(B.bitlinear_a4(X, p, a, N, layout=layout, act_fp4=True), y.to(BF16))
