@@ -989,11 +989,11 @@ static int gr_run(const void* q, const float* scale, int M, int Kp, const void* 
   return S > 1 ? gd_reduce(S, M, N, A4 ? 10 : 6, scale, alpha, Y, ybf, acc_out, ws, s) : BL_OK;
 }
 
-// Gate and up projection of 17 to 32 tokens with eq. 5 in the same launch (INT4 codes, both matrices in
+// Gate and up projection of 17 to 64 tokens with eq. 5 in the same launch (INT4 codes, both matrices in
 // BL_W_GEMM): possible where all of K fits the LDS beside the tokens (no split across blocks).
-static bool gr_glu_plan(int M, int N, int Kp, int& NWT, int& KS, int& NBn, size_t& smem) {
-  if (M <= 16 || M > 32) return false;
-  constexpr int MT = 2;
+static bool gr_glu_plan(int M, int N, int Kp, int& MT, int& NWT, int& KS, int& NBn, size_t& smem) {
+  if (M <= 16 || M > 64) return false;
+  MT = M > 32 ? 4 : 2;
   const int KT = Kp >> 8;
   if (KT > gr_slice_tiles(MT, true)) return false;
   const int NTv = 2 * ((N + 15) / 16);                   // gate and up tiles
@@ -1010,32 +1010,39 @@ static bool gr_glu_plan(int M, int N, int Kp, int& NWT, int& KS, int& NBn, size_
 }
 
 bool bl_gemm_decode_glu_ok(int64_t M, int64_t N, int64_t K) {
-  int NWT, KS, NBn;
+  int MT, NWT, KS, NBn;
   size_t smem;
   if (M > 64 || N > ((int64_t)1 << 27)) return false;
-  const int Kp = (int)bl_round_up(K, BL_KPAD);
-  // (33 to 64 tokens run in gemm_mid.hip, which takes any K; rows wider than this keep to the composed path, whose larger
-  // workspace their callers already pass)
-  if (M > 32) return (Kp >> 8) <= gr_slice_tiles(4, true);
-  return gr_glu_plan((int)M, (int)N, Kp, NWT, KS, NBn, smem);
+  // (33 to 64 tokens mostly run in gemm_mid.hip, which takes any K; rows too wide for this plan keep to the composed path, whose
+  // larger workspace their callers already pass)
+  return gr_glu_plan((int)M, (int)N, (int)bl_round_up(K, BL_KPAD), MT, NWT, KS, NBn, smem);
+}
+
+template <int MT>
+static int gr_go_glu(const void* q, const float* scale, int M, int Kp, const void* Wg, const float* ag, const void* Wu,
+                     const float* au, int N, void* H, int NWT, int KS, int NBn, size_t smem, hipStream_t s) {
+  BL_SET_MAX_LDS_ONCE((gemm_decode_resident_kernel<MT, true, true>), GR_LDS_MAX);
+  gemm_decode_resident_kernel<MT, true, true><<<(unsigned)NBn, GR_THREADS, smem, s>>>(
+      (const unsigned char*)q, scale, M, Kp, (const unsigned char*)Wg, ag, N, H, 1, nullptr, nullptr, NBn, 1, NWT, KS,
+      (const unsigned char*)Wu, au);
+  BL_HIP_CHECK_LAUNCH();
+  return BL_OK;
 }
 
 // q: INT4 nibble codes [M][Kp / 2] with their scales; H [M, N] bfloat16.
 int bl_launch_gemm_decode_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,
                               const void* Wu, const float* au, int64_t N, void* H, hipStream_t s) {
-  // (more than 32 tokens, weights from HBM: 64 x 2 x 5460 x 2048 11.8 us with the codes in LDS, 10.3 with the tiles of gemm_mid.hip;
-  // 64 x 2 x 2688 x 1024 8.8 / 8.4; 33 x 2 x 11008 x 4096 18.5 / 14.5)
-  if (M > 32) return bl_launch_gemm_mid_a4_glu(q, scale, M, K, Wg, ag, Wu, au, N, H, s);
-  int NWT, KS, NBn;
+  int MT, NWT, KS, NBn;
   size_t smem;
   const int Kp = (int)bl_round_up(K, BL_KPAD);
-  if (!gr_glu_plan((int)M, (int)N, Kp, NWT, KS, NBn, smem)) return BL_EUNSUPPORTED;
-  BL_SET_MAX_LDS_ONCE((gemm_decode_resident_kernel<2, true, true>), GR_LDS_MAX);
-  gemm_decode_resident_kernel<2, true, true><<<(unsigned)NBn, GR_THREADS, smem, s>>>(
-      (const unsigned char*)q, scale, (int)M, Kp, (const unsigned char*)Wg, ag, (int)N, H, 1, nullptr, nullptr, NBn, 1, NWT, KS,
-      (const unsigned char*)Wu, au);
-  BL_HIP_CHECK_LAUNCH();
-  return BL_OK;
+  if (!gr_glu_plan((int)M, (int)N, Kp, MT, NWT, KS, NBn, smem)) return BL_EUNSUPPORTED;
+  if (MT == 2) return gr_go_glu<2>(q, scale, (int)M, Kp, Wg, ag, Wu, au, (int)N, H, NWT, KS, NBn, smem, s);
+  // more than 32 tokens: resident while one tile pair per block covers the outputs (NWT = 2: 4096 outputs on 256 CUs) and K is more
+  // than four steps of 256.  With quantizer, weights from HBM, 64 tokens, here / in gemm_mid.hip: 2 x 3000 x 1152 8.9 us / 9.6, 2 x 4096 x
+  // 1536 9.6 / 10.4, 2 x 1024 x 2688 10.3 / 11.2, 2 x 4096 x 4096 13.1 / 13.2; 2 x 2688 x 1024 8.7 / 8.1; 2 x 4160 x 4096 15.0 / 13.4, 2 x
+  // 5460 x 2048 11.8 / 10.2, 2 x 11008 x 4096 18.4 / 14.2
+  if (NWT == 2 && (Kp >> 8) > 4) return gr_go_glu<4>(q, scale, (int)M, Kp, Wg, ag, Wu, au, (int)N, H, NWT, KS, NBn, smem, s);
+  return bl_launch_gemm_mid_a4_glu(q, scale, M, K, Wg, ag, Wu, au, N, H, s);
 }
 
 // The fused INT4 linear is used for one bfloat16 token when the one-tile-per-block kernel would be

@@ -167,3 +167,19 @@ def test_block_float_outputs(M, N, K, layout):
         assert torch.equal(y, y_ref.to(dt)) and torch.equal(acc, acc_ref.int())
     y = B.bitlinear_a4(X, p, a, N, layout=layout, act_fp4=True, y_dtype=torch.float32)
     assert torch.equal(B.bitlinear_a4(X, p, a, N, layout=layout, act_fp4=True), y.to(BF16))
+
+
+# 33 to 64 tokens: gate and up with the codes resident (one tile pair per block, more than four steps of K) and without
+@pytest.mark.parametrize("M,N,K", [(33, 70, 1025), (64, 4096, 1200), (50, 4097, 1200), (64, 4090, 1024), (64, 1021, 4096), (47, 2688, 4001)])
+def test_decode_gate_up(M, N, K):
+    """Gate and up with eq. 5 in the same launch, bit for bit."""
+    print("[case] gate/up M=%d N=%d K=%d" % (M, N, K), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    X = torch.randn((M, K), generator=g, device="cuda").to(BF16)
+    W = 0.02 * torch.randn((N, K), generator=g, device="cuda")
+    Wu = 0.02 * torch.randn((N, K), generator=g, device="cuda")
+    g4, u4 = product(X, W, B.BL_ACT_INT4_ABSMEAN)[1], product(X, Wu, B.BL_ACT_INT4_ABSMEAN)[1]
+    p, a = B.pack_ternary(W)
+    pu, au = B.pack_ternary(Wu)
+    h = B.bitlinear_a4_gate_up(X, p, a, pu, au, N, want=("H",))["H"]
+    assert torch.equal(h, (u4 * g4.clamp_min(0.0).square()).to(BF16))
