@@ -41,11 +41,12 @@ enum { GM_ROWS = 0, GM_ANY = 1 };
 template <int FMT, int TM, int TN, int G>
 struct GmFmt {
   static constexpr bool mx = FMT == GM_MX;
+  static_assert(!mx || TM == 1, "block-float tiles are 64 tokens: two waves share a 32-token block row");
   static constexpr int bm = 64 * TM, bn = 64 * TN;
   static constexpr int nsub = mx ? 4 : 8;                  // MFMA sub-steps per step of 256 channels
   static constexpr int la = (FMT == GM_I8 ? 4 : FMT == GM_I4 ? 2 : 3) * TM;   // 16-byte activation loads per thread and step
   static constexpr int per_sub = FMT == GM_I4 ? 1 : TM;    // of them written to LDS per sub-step
-  static constexpr int stage = mx ? 2 * TM * 6144 : bm * 256;
+  static constexpr int stage = mx ? 2 * 6144 : bm * 256;
   static constexpr int shift = FMT == GM_I8 ? 6 : FMT == GM_I4 ? 10 : 0;   // the int8 expansion scales the sums by 2^shift
   static constexpr int tb_row = bn * 2 + 16;               // epilogue: one token's outputs in LDS, padded against conflicts
   static constexpr int sums = (G - 1) * bm * bn * 4;       // epilogue: accumulators of groups 1 ...
@@ -101,17 +102,16 @@ __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
   unsigned char* const lds = gm_smem + group * 2 * STAGE;
 
   // ---- activation sources.  Row-major codes: piece i of a thread is row (tid / PR) + (256 / PR) i, 16-byte piece
-  // tid % PR of the step's PR pieces per row; block form: wave w copies the 6 KB of its 32-token block in order.
+  // tid % PR of the step's PR pieces per row; block form: a wave copies half of the 6 KB of a 32-token block in order.
   // Rows (blocks) past the end re-read the last one; their results are not stored.
   constexpr int PR = FMT == GM_I4 ? 8 : 16;
   constexpr int A_STEP = MX ? 6144 : PR * 16;              // bytes of one step along a row (block row)
-  // (TM = 1: two waves share a block row, 3 KB each)
-  const int A_WAVE = TM == 2 ? 0 : (wave & 1) * 3072;
+  const int A_WAVE = (wave & 1) * 3072;                    // (block form: two waves share a block row, 3 KB each)
   const unsigned char* a_base;
   u32 a_off[MX ? 1 : LA];
   if constexpr (MX) {
     const int MB = (M + 31) >> 5;
-    a_base = A + ((size_t)min((m0 >> 5) + (TM == 2 ? wave : wave >> 1), MB - 1) * KT + kt0) * 6144;
+    a_base = A + ((size_t)min((m0 >> 5) + (wave >> 1), MB - 1) * KT + kt0) * 6144;
     a_off[0] = A_WAVE + lane * 16;
   } else {
     const u32 row_bytes = (u32)KT * (PR * 16);
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
     else a_reg[set][i] = gm_load16(a_rsrc, a_off[i], so);
   };
   // LDS: a row's 256 bytes cover all banks, its 16-byte chunk c sits at c ^ (row % 16); block form as it comes
-  const int a_dst = MX ? (TM == 2 ? wave : wave >> 1) * 6144 + A_WAVE + lane * 16
+  const int a_dst = MX ? (wave >> 1) * 6144 + A_WAVE + lane * 16
                        : (tid / PR) * 256 + (((FMT == GM_I4 ? 2 * (tid % PR) : tid % PR) ^ ((tid / PR) & 15)) << 4);
   auto store_a = [&](int st, int set, int i) {
     unsigned char* d = lds + st * STAGE + a_dst;
@@ -185,9 +185,9 @@ __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
   if constexpr (MX) {
 #pragma unroll
     for (int j = 0; j < NSUB; ++j)
-      x_off[j] = wm * TM * 6144 + (j >> 1) * 3072 + l32 * 64 + (((2 * lh + (j & 1)) ^ ((l32 >> 2) & 3)) << 4);
+      x_off[j] = wm * 6144 + (j >> 1) * 3072 + l32 * 64 + (((2 * lh + (j & 1)) ^ ((l32 >> 2) & 3)) << 4);
 #pragma unroll
-    for (int e = 0; e < 2; ++e) xq_off[e] = wm * TM * 6144 + 2048 + l32 * 32 + (((2 * lh + e) ^ ((l32 >> 3) & 3)) << 3);
+    for (int e = 0; e < 2; ++e) xq_off[e] = wm * 6144 + 2048 + l32 * 32 + (((2 * lh + e) ^ ((l32 >> 3) & 3)) << 3);
   } else {
 #pragma unroll
     for (int j = 0; j < NSUB; ++j)

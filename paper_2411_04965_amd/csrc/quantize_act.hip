@@ -509,7 +509,8 @@ __global__ __launch_bounds__(NT) void quant_topk_int8_kernel(
 // bits of the threshold is a trip through LDS and a barrier of 16 waves.  Here a pass is 4 NV comparisons whose lane
 // masks are counted on the scalar unit, and the search ends as soon as a candidate leaves exactly topk keys (after
 // about as many passes as it takes to tell the topk-th key from the next one: a dozen at 512 channels); rows with fewer
-// than topk non-zero channels need none.  16 rows of 512 channels: 12.2 us with the kernel above, 5.8 here (a launch takes about 2).
+// than topk non-zero channels need none.  At any number of rows (kernel above / here): 512 channels 1 row 11.1 us / 4.1, 64 rows 11.7 / 6.4,
+// 4096 rows 27 / 9.3, 65536 rows 338 / 71; 1024 channels 1 row 11.3 / 7.4, 256 rows, one per CU, 10.1 / 9.5, 65536 rows 420 / 115.
 // Same keys, same tie order (chunk, lane, channel), same arithmetic, so the codes are the same bit for bit.
 template <int NV>
 __global__ __launch_bounds__(64) void quant_topk_int8_f32_wave_kernel(
