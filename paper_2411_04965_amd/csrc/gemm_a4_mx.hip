@@ -459,18 +459,22 @@ __global__ __launch_bounds__(GX_THREADS, 1) void gemm_a4_mx_kernel(
             }
             __builtin_amdgcn_sched_barrier(0);
           }
+          if (interior) {                                    // uniform: all reads in flight, then all stores
+            v4i v[NPASS];
 #pragma unroll
-          for (int i = 0; i < NPASS; ++i) {
-            const int row = b * 32 + i * ROWS_PER_PASS;
-            const v4i v = *reinterpret_cast<const v4i*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
-            if (interior || (row < m_left && n_left >= 8)) *reinterpret_cast<v4i_align2*>(ywave + (size_t)row * N + lane_off) = v;
-          }
-          if (!interior && (N & 7)) {                        // uniform
+            for (int i = 0; i < NPASS; ++i)
+              v[i] = *reinterpret_cast<const v4i*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < NPASS; ++i)
+              *reinterpret_cast<v4i_align2*>(ywave + (size_t)(b * 32 + i * ROWS_PER_PASS) * N + lane_off) = v[i];
+          } else {                                           // (kept small: unrolled it cost interior tiles 1 %)
 #pragma unroll 1
             for (int i = 0; i < NPASS; ++i) {
               const int row = b * 32 + i * ROWS_PER_PASS;
               const v4i v = *reinterpret_cast<const v4i*>(tbuf + (rr + i * ROWS_PER_PASS) * TB_ROW + cc * 16);
-              if (row < m_left && 0 < n_left && n_left < 8) bl_store_tail8(ywave + (size_t)row * N + lane_off, v, n_left);
+              if (row < m_left && n_left >= 8) *reinterpret_cast<v4i_align2*>(ywave + (size_t)row * N + lane_off) = v;
+              else if (row < m_left && n_left > 0) bl_store_tail8(ywave + (size_t)row * N + lane_off, v, n_left);
             }
           }
           __builtin_amdgcn_sched_barrier(0);
