@@ -144,8 +144,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t sb_rsrc(const uint16_t* base) 
 // one is multiplied.  A row of a stage is 128 bytes whose 16-byte piece p sits at p ^ ((row / 2) % 8): the
 // 16 rows that one phase of a fragment read touches then cover the 16 slots of a 256-byte bank window.
 //
-// Bound by the matrix cores as far as the four waves keep them fed (1.38 PFLOP/s at 8192^3; 1.03 with flat addresses and all of a
-// sub-step's loads ahead of its MFMAs): with 256 x 256 tiles a wave is alone on its SIMD, so everything
+// Bound by the matrix cores as far as the four waves keep them fed (8192^3 under the profiler: 829 us, 1.33 PFLOP/s; 957 us with flat
+// addresses and all of a sub-step's loads ahead of its MFMAs): with 256 x 256 tiles a wave is alone on its SIMD, so everything
 // else has to be issued in the shadow of its MFMAs (32 cycles each).  Hence one MFMA at a time between an LDS read,
 // an LDS write and a request; operands by buffer loads (a uniform step offset and one 32-bit offset per piece: flat
 // addresses took about ten vector instructions per piece); the barrier before the last sub-step, which reads the next step's
