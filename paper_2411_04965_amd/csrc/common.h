@@ -69,6 +69,45 @@ __device__ __forceinline__ void bl_store_tail8(uint16_t* p, v4i v, int n_left) {
     if (e < n_left) p[e] = (uint16_t)((u32)v[e >> 1] >> (16 * (e & 1)));
 }
 
+// Four consecutive outputs of one token at element o = m * N + n (n % 4 == 0): values to Y (nullable), integers to acc_out
+// (nullable); rows whose length is no multiple of 4 by elements.
+__device__ __forceinline__ void bl_store_out4(void* Y, int y_bf16, int32_t* acc_out, size_t o, int n, int N,
+                                          const int (&iv)[4], const float (&fv)[4]) {
+  if ((N & 3) == 0) {
+    if (Y) {
+      if (y_bf16) {
+        *reinterpret_cast<uint2*>((uint16_t*)Y + o) = make_uint2(bl_pack_bf16(fv[0], fv[1]), bl_pack_bf16(fv[2], fv[3]));
+      } else {
+        *reinterpret_cast<float4*>((float*)Y + o) = make_float4(fv[0], fv[1], fv[2], fv[3]);
+      }
+    }
+    if (acc_out) *reinterpret_cast<int4*>(acc_out + o) = make_int4(iv[0], iv[1], iv[2], iv[3]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (n + r < N) {
+        if (Y) {
+          if (y_bf16) ((uint16_t*)Y)[o + r] = bl_f32_to_bf16_rne(fv[r]);
+          else ((float*)Y)[o + r] = fv[r];
+        }
+        if (acc_out) acc_out[o + r] = iv[r];
+      }
+    }
+  }
+}
+
+// Codes in fragment order (what gemm_direct.hip reads; its header gives the layout): R tokens in the 16-token tile of token m.
+__device__ __forceinline__ int bl_frag_rows(int64_t m, int64_t M) { return (int)min((int64_t)16, M - (m & ~(int64_t)15)); }
+// the word of 4 INT8 codes that lane l of a wave makes of channels 256 kt + 4 l ..., kt = 0; the next kt is 64 R words on
+__device__ __forceinline__ int64_t bl_frag_word8(int64_t m, int R, int Kp, int l) {
+  return (m & ~(int64_t)15) * (Kp / 4) + ((l & 15) >> 2) * 16 * R + ((l >> 4) * R + (int)(m & 15)) * 4 + (l & 3);
+}
+// the first of the two words of 16 INT4 codes of channels 16 h ...
+__device__ __forceinline__ int64_t bl_frag_word4(int64_t m, int R, int Kp, int h) {
+  return (m & ~(int64_t)15) * (Kp / 8) + (int64_t)(h >> 4) * 32 * R + ((h >> 1) & 1) * 16 * R +
+         (((h >> 2) & 3) * R + (int)(m & 15)) * 4 + (h & 1) * 2;
+}
+
 // Sum over a 64-lane wave (all lanes get the result).
 __device__ __forceinline__ double bl_wave_sum_f64(double v) {
 #pragma unroll
@@ -140,6 +179,14 @@ int bl_launch_quantize_glu(const void* G, const void* U, bl_dtype dt, int64_t M,
 int bl_launch_quantize(const void* X, bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode,
                        int64_t topk, float eps, void* q, void* scale, int32_t* rowsum,
                        int32_t* sel_idx, hipStream_t s);
+// the same codes in fragment order, for gemm_direct.hip
+bool bl_quantize_frag_ok(bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode);
+int bl_launch_quantize_frag(const void* X, int64_t M, int64_t K, bl_act_mode mode, int64_t topk, float eps, void* q,
+                            float* scale, hipStream_t s);
+int bl_launch_gemm_direct(const void* q, const float* scale, bl_act_mode mode, int64_t M, int64_t K, const void* Wp,
+                          const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);
+int bl_launch_gemm_direct_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,
+                              const void* Wu, const float* au, int64_t N, void* H, hipStream_t s);
 int bl_launch_unpack_act(const void* q, bl_act_mode mode, int64_t M, int64_t K, int8_t* codes,
                          hipStream_t s);
 int bl_launch_quantize_heads(const void* X, bl_dtype dt, int64_t n_heads, int64_t n4, int64_t D, int bits, float eps,

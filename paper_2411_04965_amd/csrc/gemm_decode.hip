@@ -1,4 +1,5 @@
-// Decode-shaped linears (1 to 64 tokens; most of 33 to 64 go on to gemm_mid.hip): the packed ternary weights are streamed from HBM once.
+// Decode-shaped linears (1 to 64 tokens; most of 33 to 64 go on to gemm_mid.hip): the packed ternary weights are streamed from HBM
+// once.  Codes come row-major here, from callers that quantize themselves (or from tokens that gemm_direct.hip does not take).
 //   Dense path  (BL_W_GEMM tiles):   skinny int8-MFMA GEMM; three kernels by token count.
 //   Sparse path (BL_W_KMAJOR rows):  eq. 1's sparsity used for I/O — only the weight rows of
 //                                    channels whose INT8 code is non-zero in some token are read.

@@ -39,34 +39,6 @@ struct GvMat {
   int N, NT;                   // outputs, tiles of 16
 };
 
-__device__ __forceinline__ void gv_store4(void* Y, int y_bf16, int32_t* acc_out, size_t o, int n, int N,
-                                          const int (&iv)[4], const float (&fv)[4]) {
-  if ((N & 3) == 0) {
-    if (Y) {
-      if (y_bf16) {
-        uint2 p;
-        p.x = (u32)bl_f32_to_bf16_rne(fv[0]) | ((u32)bl_f32_to_bf16_rne(fv[1]) << 16);
-        p.y = (u32)bl_f32_to_bf16_rne(fv[2]) | ((u32)bl_f32_to_bf16_rne(fv[3]) << 16);
-        *reinterpret_cast<uint2*>((uint16_t*)Y + o) = p;
-      } else {
-        *reinterpret_cast<float4*>((float*)Y + o) = make_float4(fv[0], fv[1], fv[2], fv[3]);
-      }
-    }
-    if (acc_out) *reinterpret_cast<int4*>(acc_out + o) = make_int4(iv[0], iv[1], iv[2], iv[3]);
-  } else {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if (n + r < N) {
-        if (Y) {
-          if (y_bf16) ((uint16_t*)Y)[o + r] = bl_f32_to_bf16_rne(fv[r]);
-          else ((float*)Y)[o + r] = fv[r];
-        }
-        if (acc_out) acc_out[o + r] = iv[r];
-      }
-    }
-  }
-}
-
 // eq. 7 for up to QM bfloat16 token rows by the whole workgroup (QM <= 8 = waves): int8 codes to
 // codes[m * pitch + k] (zero from K to Kp), beta / sqrt(7) to dq[m].  A thread holds pieces tid and
 // tid + 512 (8 channels each) of every token (K % 8 == 0, Kp <= 8192); the kernel loads them before
@@ -302,7 +274,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_stream_kernel(
 
   // ---- the tokens' codes
   if constexpr (TK > 0) {
-    qa_topk_row_regs8<TKR>(traw, tk_nc, tk_begin, topk, eps, reinterpret_cast<u32*>(codes), sh_dq, sh_tk);
+    qa_topk_row_regs8<TKR>(traw, tk_nc, tk_begin, topk, eps, reinterpret_cast<u32*>(codes) + tk_begin * 64 + lane, 64, sh_dq, sh_tk);
   } else if (QM > 0) {
     const int ne_max = (upb + (urem > 0 ? 1 : 0)) * (GLU ? 2 : 1);    // the launch's LDS holds this many entries
     double* part = reinterpret_cast<double*>(gv_smem + (size_t)M * pitch + (size_t)ne_max * GV_WAVES * 1024);
@@ -455,7 +427,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_stream_kernel(
     float fv[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) fv[r] = ((float)iv[r] * d) * alpha;
-    gv_store4(mm.Y, y_bf16, mm.acc, (size_t)m * mm.N + n, n, mm.N, iv, fv);
+    bl_store_out4(mm.Y, y_bf16, mm.acc, (size_t)m * mm.N + n, n, mm.N, iv, fv);
   } else {
     if (wave >= n0) return;
     const int nt = nt0 + wave;
@@ -472,8 +444,8 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_stream_kernel(
       uu[r] = ((float)iu[r] * d) * au;
     }
     const size_t o = (size_t)m * N + n;
-    if (m0.Y || m0.acc) gv_store4(m0.Y, y_bf16, m0.acc, o, n, N, ig, g);
-    if (m1.Y || m1.acc) gv_store4(m1.Y, y_bf16, m1.acc, o, n, N, iu, uu);
+    if (m0.Y || m0.acc) bl_store_out4(m0.Y, y_bf16, m0.acc, o, n, N, ig, g);
+    if (m1.Y || m1.acc) bl_store_out4(m1.Y, y_bf16, m1.acc, o, n, N, iu, uu);
     if (H) {
       uint16_t h[4];
 #pragma unroll

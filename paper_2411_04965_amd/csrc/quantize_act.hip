@@ -172,7 +172,7 @@ __global__ __launch_bounds__(QA_THREADS) void quant_int4_kernel(
 template <bool MX6, int NV>
 __global__ __launch_bounds__(QA_THREADS) void quant_int4_regs_kernel(
     const uint16_t* __restrict__ X, int64_t M, int K, int Kp, float eps, u32* __restrict__ q_out,
-    float* __restrict__ scale_out, int32_t* __restrict__ rowsum_out, int stat) {
+    float* __restrict__ scale_out, int32_t* __restrict__ rowsum_out, int stat, int frag) {
   __shared__ double red[QA_WAVES];
   __shared__ u32 redm[QA_WAVES];
   __shared__ int redi[QA_WAVES];
@@ -303,9 +303,9 @@ __global__ __launch_bounds__(QA_THREADS) void quant_int4_regs_kernel(
         }
       } else {
         // nibble form: byte b of a word = level b | level 4 + b << 4
+        u32* const o = frag ? q_out + bl_frag_word4(m, bl_frag_rows(m, M), Kp, h) : out + 2 * h;
 #pragma unroll
-        for (int g = 0; g < 2; ++g)
-          out[2 * h + g] = (lv[2 * g] & 0x0F0F0F0Fu) | ((lv[2 * g + 1] << 4) & 0xF0F0F0F0u);
+        for (int g = 0; g < 2; ++g) o[g] = (lv[2 * g] & 0x0F0F0F0Fu) | ((lv[2 * g + 1] << 4) & 0xF0F0F0F0u);
       }
     }
   }
@@ -652,7 +652,7 @@ __global__ __launch_bounds__(QA_THREADS) void quant_topk_int8_regs_kernel(
 template <int CPW, bool EARLY>
 __global__ __launch_bounds__(512) void quant_topk_int8_regs8_kernel(
     const uint16_t* __restrict__ X, int K, int Kp, int topk, float eps, u32* __restrict__ q_out,
-    float* __restrict__ scale_out) {
+    float* __restrict__ scale_out, int frag_M) {
   __shared__ __align__(16) u32 sh[80];
   const int64_t m = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -670,7 +670,9 @@ __global__ __launch_bounds__(512) void quant_topk_int8_regs8_kernel(
     raw[i][0] = v.x;
     raw[i][1] = v.y;
   }
-  qa_topk_row_regs8<CPW, EARLY>(raw, nc, c_begin, topk, eps, q_out + m * (int64_t)(Kp / 4), scale_out + m, sh);
+  const int R = frag_M ? bl_frag_rows(m, frag_M) : 1;      // frag_M: all tokens of a call whose codes go out in fragment order
+  u32* const out = q_out + (frag_M ? bl_frag_word8(m, R, Kp, lane) : m * (int64_t)(Kp / 4) + lane);
+  qa_topk_row_regs8<CPW, EARLY>(raw, nc, c_begin, topk, eps, out + c_begin * 64 * R, 64 * R, scale_out + m, sh);
 }
 
 // The same selection with one wave per token, for many tokens of moderate width: the fixed cost of a
@@ -1100,6 +1102,17 @@ static int qa_run_row_kernels(const RawT* X, int64_t M, int K, int Kp, bl_act_mo
   return BL_OK;
 }
 
+// Up to 256 tokens, K % 4 == 0 and Kp <= 12288 (at most 6 chunks of 256 channels per wave); frag_M: fragment order, all tokens.
+static void qa_run_topk_regs8(const void* x, int64_t M, int K, int Kp, int topk, float eps, void* q, void* scale, int frag_M,
+                              hipStream_t s) {
+#define QA_R8(CPW, EARLY) \
+  quant_topk_int8_regs8_kernel<CPW, EARLY><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale, frag_M)
+  if (Kp <= 4096) QA_R8(4, false);
+  else if (Kp <= 8192) QA_R8(4, true);
+  else QA_R8(8, false);
+#undef QA_R8
+}
+
 // Top_k + INT8 with the keys in registers, one memory pass (K % 4 == 0, Kp <= 12288).
 template <int GLU>
 static int qa_run_topk_regs(const void* x, const void* x2, int64_t M, int K, int Kp, int topk, float eps,
@@ -1109,13 +1122,7 @@ static int qa_run_topk_regs(const void* x, const void* x2, int64_t M, int K, int
   // 0.075 ms at 4096 channels, 0.077 against 0.110 ms at 5460; from 8 register blocks on it loses)
   const int nb = (Kp / 256 + 3) / 4;
   if (GLU == 0 && rowsum == nullptr && M <= 256) {
-    // (K % 4 == 0 and Kp <= 12288 by dispatch: at most 6 chunks of 256 channels per wave)
-    if (Kp <= 4096)
-      quant_topk_int8_regs8_kernel<4, false><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale);
-    else if (Kp <= 8192)
-      quant_topk_int8_regs8_kernel<4, true><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale);
-    else
-      quant_topk_int8_regs8_kernel<8, false><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale);
+    qa_run_topk_regs8(x, M, K, Kp, topk, eps, q, scale, 0, s);
   } else if (M >= 2048 && nb <= 6) {
     const unsigned grid = (unsigned)((M + QA_WAVES - 1) / QA_WAVES);
     if (nb <= 4)
@@ -1181,7 +1188,7 @@ int bl_launch_quantize(const void* X, bl_dtype dt, int64_t M, int64_t K64, bl_ac
     const bool mx6 = mode == BL_ACT_INT4_ABSMEAN_MX6;
     const int nvv = (Kp / 16 + QA_THREADS - 1) / QA_THREADS;      // half units per thread: 1 .. 4
     const unsigned grid = mx6 ? (unsigned)((M + 7) / 8 * 8) : (unsigned)M;   // MX6: a multiple of 8
-#define QA_I4(MX, NVV) quant_int4_regs_kernel<MX, NVV><<<grid, QA_THREADS, 0, s>>>((const uint16_t*)X, M, K, Kp, eps, (u32*)q, (float*)scale, rowsum, stat)
+#define QA_I4(MX, NVV) quant_int4_regs_kernel<MX, NVV><<<grid, QA_THREADS, 0, s>>>((const uint16_t*)X, M, K, Kp, eps, (u32*)q, (float*)scale, rowsum, stat, 0)
     if (mx6) { if (nvv <= 1) QA_I4(true, 1); else if (nvv <= 2) QA_I4(true, 2); else QA_I4(true, 4); }
     else { if (nvv <= 1) QA_I4(false, 1); else if (nvv <= 2) QA_I4(false, 2); else QA_I4(false, 4); }
 #undef QA_I4
@@ -1204,6 +1211,33 @@ int bl_launch_quantize(const void* X, bl_dtype dt, int64_t M, int64_t K64, bl_ac
   }
   if (K % 4 == 0) return qa_run_row_kernels<u32, 4>(x, M, K, Kp, mode, (int)topk, eps, q, scale, rowsum, sel_idx, s);
   return qa_run_row_kernels<u32, 1>(x, M, K, Kp, mode, (int)topk, eps, q, scale, rowsum, sel_idx, s);
+}
+
+// Fragment order comes from the register kernels only.
+bool bl_quantize_frag_ok(bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode) {
+  const int64_t Kp = bl_round_up(K, BL_KPAD);
+  if (dt != BL_BF16 || M > 256) return false;
+  if (mode == BL_ACT_INT4_ABSMEAN) return K % 8 == 0 && Kp <= 16384;
+  return mode == BL_ACT_TOPK_INT8_ABSMAX && K % 4 == 0 && Kp <= 12288;
+}
+
+int bl_launch_quantize_frag(const void* X, int64_t M, int64_t K64, bl_act_mode mode, int64_t topk, float eps, void* q,
+                            float* scale, hipStream_t s) {
+  if (!bl_quantize_frag_ok(BL_BF16, M, K64, mode)) return BL_EUNSUPPORTED;
+  const int K = (int)K64, Kp = (int)bl_round_up(K64, BL_KPAD);
+  if (mode == BL_ACT_INT4_ABSMEAN) {
+    const int nvv = (Kp / 16 + QA_THREADS - 1) / QA_THREADS;
+#define QA_I4F(NVV) \
+  quant_int4_regs_kernel<false, NVV><<<(unsigned)M, QA_THREADS, 0, s>>>((const uint16_t*)X, M, K, Kp, eps, (u32*)q, scale, nullptr, 0, 1)
+    if (nvv <= 1) QA_I4F(1);
+    else if (nvv <= 2) QA_I4F(2);
+    else QA_I4F(4);
+#undef QA_I4F
+  } else {
+    qa_run_topk_regs8(X, M, K, Kp, (int)topk, eps, q, scale, (int)M, s);
+  }
+  BL_HIP_CHECK_LAUNCH();
+  return BL_OK;
 }
 
 int bl_launch_unpack_act(const void* q, bl_act_mode mode, int64_t M, int64_t K, int8_t* codes,

@@ -94,7 +94,7 @@ __device__ __forceinline__ void qa_bit_transpose16(u32 (&w)[8]) {
 template <int CPW>
 __device__ __forceinline__ void qa_code_chunks(const u32 (&raw)[CPW][2], const u32 (&pg)[CPW][2], int nc, u32 tau,
                                                int r, int eq_base, int eq_here, float s, u32* out0, int& sum,
-                                               bool ties_matter = true) {
+                                               bool ties_matter = true, int stride = 64) {
   const int lane = threadIdx.x & 63;
   const bool eq_all = !ties_matter || eq_base + eq_here <= r;
   const bool eq_none = eq_base >= r;
@@ -141,7 +141,7 @@ __device__ __forceinline__ void qa_code_chunks(const u32 (&raw)[CPW][2], const u
       const u32 keep4 = (__builtin_amdgcn_perm(k1, k0, 0x07050301u) >> 7) * 255u;
       const u32 word = (w01 | w23) & keep4;
       sum = __builtin_amdgcn_sdot4((int)word, 0x01010101, sum, false);
-      out0[i * 64] = word;
+      out0[i * stride] = word;
     }
   }
 }
@@ -326,6 +326,7 @@ __device__ __forceinline__ void qa_topk_row_regs(const void* __restrict__ x, con
 //     tie rule (lower channel first; waves own contiguous channel ranges) needs: no further exchange.
 //   raw     this wave's chunks of 256 channels as loaded by the caller (chunk i of the wave = chunk
 //           c_begin + i of the token; 4 consecutive channels per lane; zero beyond K and beyond nc)
+//   out     the lane's word of the wave's first chunk; `stride` words on lies its word of the next one
 //   sh      80 words of LDS scratch (16-byte aligned): row maxima [8], early counts [8], class sizes [2][32]
 // Chunks are dealt to the waves in contiguous ranges of per_wave = ceil(n_chunks / 8), so channel
 // order is (wave, chunk, lane, j) order as in the 4-wave body.  Every thread of the workgroup must
@@ -347,7 +348,7 @@ __device__ __forceinline__ u32 qa_max8_dpp(u32 x) {
 
 template <int CPW, bool EARLY = false>
 __device__ __forceinline__ void qa_topk_row_regs8(const u32 (&raw)[CPW][2], int nc, int c_begin, int topk, float eps,
-                                                  u32* out, float* scale_out, u32* sh) {
+                                                  u32* out, int stride, float* scale_out, u32* sh) {
   static_assert(CPW == 4 || CPW == 8, "16 or 32 keys per lane");
   static_assert(!EARLY || CPW == 4, "the early count reads one block of bit planes");
   constexpr int NBK = CPW / 4;
@@ -397,7 +398,7 @@ __device__ __forceinline__ void qa_topk_row_regs8(const u32 (&raw)[CPW][2], int 
       const int total_hi = __builtin_amdgcn_readfirstlane((int)qa_sum8_dpp(sh[8 + (lane & 7)]));
       if (total_hi <= topk) {
         int sum = 0;
-        qa_code_chunks<CPW>(raw, pg, nc, C, 0, 0, 0, s, out + c_begin * 64 + lane, sum, false);
+        qa_code_chunks<CPW>(raw, pg, nc, C, 0, 0, 0, s, out, sum, false, stride);
         return;
       }
     }
@@ -477,7 +478,7 @@ __device__ __forceinline__ void qa_topk_row_regs8(const u32 (&raw)[CPW][2], int 
     const u32 t3 = (u32)__builtin_amdgcn_readfirstlane((int)qa_sum8_dpp(q.w));
     if (EARLY && p == 0 && C > 0u && (int)(t3 >> 16) <= topk) {   // workgroup-uniform
       int sum = 0;
-      qa_code_chunks<CPW>(raw, pg, nc, C, 0, 0, 0, s, out + c_begin * 64 + lane, sum, false);
+      qa_code_chunks<CPW>(raw, pg, nc, C, 0, 0, 0, s, out, sum, false, stride);
       return;
     }
     // cum[c] = undecided keys of class c or higher; the topk-th largest key is in the highest class
@@ -519,5 +520,5 @@ __device__ __forceinline__ void qa_topk_row_regs8(const u32 (&raw)[CPW][2], int 
   }
   const bool low = tau == 0;
   int sum = 0;
-  qa_code_chunks<CPW>(raw, pg, nc, tau + C, r, low ? r : eq_base, eq_here, s, out + c_begin * 64 + lane, sum);
+  qa_code_chunks<CPW>(raw, pg, nc, tau + C, r, low ? r : eq_base, eq_here, s, out, sum, true, stride);
 }
