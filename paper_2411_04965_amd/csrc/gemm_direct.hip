@@ -184,10 +184,10 @@ static int gx_go(const void* q, const float* scale, int M, int KT, const void* W
 }
 
 // ---- tile choice.  What a block costs goes with the 1 KB loads of its K loop (INT8 codes: four per token tile and K tile, INT4
-// two; one per output tile) plus the sums of its accumulator tiles, worth 12 loads each; blocks beyond one per CU share CUs, so
-// their number counts half as turns of the chip (rounded up) and half as it is.  Against the best of all tiles at 66 sizes
-// (4 to 320 tokens, 1024 to 12288 outputs, 1024 to 11008 channels, weights from HBM) the choice is 1 % slower on average, 16 % at
-// most.  Products alone, before (resident codes and split K, or 64 x 64 tiles with a barrier per step) -> here, us:
+// two; one per output tile) plus the sums of its accumulator tiles, worth 6 loads each.  Blocks beyond one per CU come in turns;
+// where their sums leave LDS for two blocks on a CU (up to 10 accumulator tiles), a turn costs less and a part of one counts as such.
+// Against the best of all tiles at 96 sizes (4 to 320 tokens, 1024 to 12288 outputs, 1024 to 11008 channels, weights from HBM) the
+// choice is within 8 % everywhere.  Products alone, before (resident codes and split K, or 64 x 64 tiles with a barrier per step) -> here, us:
 //   INT8   32 x 4096 x 4096 7.9 -> 4.2, 32 x 4096 x 11008 13.1 -> 7.1, 57 x 2048 x 5460 9.5 -> 4.7, 64 x 4096 x 11008 16.7 -> 8.8,
 //          200 x 3200 x 8640 14.3 -> 11.2, 256 x 4096 x 4096 9.4 -> 7.8
 //   INT4   32 x 12288 x 4096 8.9 -> 5.6, 64 x 12288 x 4096 9.5 -> 7.4; gate and up 32 x 2 x 11008 x 4096 12.8 -> 8.0,
@@ -195,8 +195,9 @@ static int gx_go(const void* q, const float* scale, int M, int KT, const void* W
 static double gx_cost(int64_t M, int64_t N, int KT, int code_loads, int mt, int nt, int ntm) {
   const int64_t blocks = ((M + 16 * mt - 1) / (16 * mt)) * (((N + 15) / 16 + ntm - 1) / ntm), cus = bl_num_cus();
   const double share = (double)blocks / cus, turns = (double)((blocks + cus - 1) / cus);
-  const double busy = 0.5 * (share + turns) < 1.0 ? 1.0 : 0.5 * (share + turns);
-  return busy * (KT * (code_loads * mt + nt) + 12 * mt * nt);
+  double busy = turns;
+  if (mt * nt <= 10 && turns > 1.0) busy = 0.85 * (0.7 * turns + 0.3 * share);
+  return busy * (KT * (code_loads * mt + nt) + 6 * mt * nt);
 }
 
 struct GxTile { int mt, nt; };
@@ -212,6 +213,12 @@ static int gx_pick(const GxTile (&tiles)[COUNT], int64_t M, int64_t N, int KT, i
   return best;
 }
 
+// Up to how many outputs these tiles are the better choice (quantizer and product, before / here, us).  INT8: 256 x 6144 x 8192
+// 24.8 / 23.6, 150 x 8192 x 8192 22.9 / 22.7; 200 x 8192 x 8192 24.8 / 26.8, 64 x 32000 x 2048 15.4 / 16.0.  INT4: 128 x 12288 x 4096
+// 15.7 / 14.8; 200 x 9600 x 3200 18.3 / 19.4, 64 x 32000 x 2048 12.2 / 13.5.  Gate and up (both counted): 57 x 2 x 11008 x 4096
+// 15.6 / 15.1; 64 x 2 x 20000 x 4096 22.8 / 23.1, 64 x 2 x 32000 x 2048 18.3 / 21.5.
+bool bl_gemm_direct_ok(int64_t M, int64_t n_cols) { return M * n_cols <= 6144 * (int64_t)bl_num_cus(); }
+
 #define GX_GO(A4, GLU, MT, NT) \
   return gx_go<A4, GLU, MT, NT>(q, scale, (int)M, KT, Wp, Wp2, alpha, alpha2, (int)N, Y, ybf, acc_out, s)
 
@@ -222,7 +229,7 @@ int bl_launch_gemm_direct(const void* q, const float* scale, bl_act_mode mode, i
   const void* Wp2 = nullptr;
   const float* alpha2 = nullptr;
   if (mode == BL_ACT_INT4_ABSMEAN) {
-    static constexpr GxTile tiles[] = {{1, 1}, {1, 2}, {1, 3}, {1, 4}, {1, 6}, {2, 2}, {2, 3}, {2, 4}, {2, 6}, {4, 3}};
+    static constexpr GxTile tiles[] = {{1, 1}, {1, 2}, {1, 3}, {1, 4}, {1, 6}, {2, 2}, {2, 3}, {2, 4}, {2, 6}};
     switch (gx_pick(tiles, M, N, KT, 2, false)) {
       case 0: GX_GO(true, false, 1, 1);
       case 1: GX_GO(true, false, 1, 2);
@@ -232,8 +239,7 @@ int bl_launch_gemm_direct(const void* q, const float* scale, bl_act_mode mode, i
       case 5: GX_GO(true, false, 2, 2);
       case 6: GX_GO(true, false, 2, 3);
       case 7: GX_GO(true, false, 2, 4);
-      case 8: GX_GO(true, false, 2, 6);
-      default: GX_GO(true, false, 4, 3);
+      default: GX_GO(true, false, 2, 6);
     }
   }
   static constexpr GxTile tiles[] = {{1, 1}, {1, 2}, {1, 3}, {1, 4}, {1, 6}, {2, 2}, {2, 3}, {2, 4}, {2, 6}, {2, 8}, {3, 4}};
