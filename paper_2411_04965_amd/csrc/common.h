@@ -108,6 +108,26 @@ __device__ __forceinline__ int64_t bl_frag_word4(int64_t m, int R, int Kp, int h
          (((h >> 2) & 3) * R + (int)(m & 15)) * 4 + (h & 1) * 2;
 }
 
+// Weights that the next launch streams, touched (one load per 128-byte line) by the blocks of a quantizer's launch that have no
+// token: the quantizer's chain of latencies leaves HBM idle, and a product whose vector loads find the weights in L2 does not queue
+// its code loads behind HBM (a CU's vector loads return in order).  Blocks go round robin to the eight XCDs, and the product
+// deals its outputs to them in eight contiguous ranges: XCD x touches its eighth of each matrix.
+struct BlTouch {
+  const unsigned char* w[2];   // one matrix or two of one size
+  int n_mat, lines, blocks;    // 128-byte lines per matrix; blocks of the launch, a multiple of 8 (0: none)
+};
+template <int THREADS>
+__device__ __forceinline__ void bl_touch(const BlTouch& t, int first_block) {
+  const int x = (int)blockIdx.x & 7, step = (t.blocks >> 3) * THREADS;
+  const int lo = (int)((int64_t)t.lines * x >> 3), n = (int)((int64_t)t.lines * (x + 1) >> 3) - lo;
+  u32 v = 0;
+  for (int i = (((int)blockIdx.x - first_block) >> 3) * THREADS + (int)threadIdx.x; i < n * t.n_mat; i += step) {
+    const int j = i >= n ? 1 : 0;
+    v ^= *reinterpret_cast<const u32*>(t.w[j] + (size_t)(lo + i - j * n) * 128);
+  }
+  asm volatile("" ::"v"(v));
+}
+
 // Sum over a 64-lane wave (all lanes get the result).
 __device__ __forceinline__ double bl_wave_sum_f64(double v) {
 #pragma unroll
@@ -179,10 +199,10 @@ int bl_launch_quantize_glu(const void* G, const void* U, bl_dtype dt, int64_t M,
 int bl_launch_quantize(const void* X, bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode,
                        int64_t topk, float eps, void* q, void* scale, int32_t* rowsum,
                        int32_t* sel_idx, hipStream_t s);
-// the same codes in fragment order, for gemm_direct.hip
+// the same codes in fragment order, for gemm_direct.hip; W, W2 (nullable), w_bytes each: the product's weights
 bool bl_quantize_frag_ok(bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode);
 int bl_launch_quantize_frag(const void* X, int64_t M, int64_t K, bl_act_mode mode, int64_t topk, float eps, void* q,
-                            float* scale, hipStream_t s);
+                            float* scale, const void* W, const void* W2, size_t w_bytes, hipStream_t s);
 bool bl_gemm_direct_ok(int64_t M, int64_t n_cols);
 int bl_launch_gemm_direct(const void* q, const float* scale, bl_act_mode mode, int64_t M, int64_t K, const void* Wp,
                           const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);

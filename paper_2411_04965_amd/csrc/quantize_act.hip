@@ -172,7 +172,11 @@ __global__ __launch_bounds__(QA_THREADS) void quant_int4_kernel(
 template <bool MX6, int NV>
 __global__ __launch_bounds__(QA_THREADS) void quant_int4_regs_kernel(
     const uint16_t* __restrict__ X, int64_t M, int K, int Kp, float eps, u32* __restrict__ q_out,
-    float* __restrict__ scale_out, int32_t* __restrict__ rowsum_out, int stat, int frag) {
+    float* __restrict__ scale_out, int32_t* __restrict__ rowsum_out, int stat, int frag, BlTouch touch) {
+  if (!MX6 && blockIdx.x >= M) {                 // (whole workgroup)
+    bl_touch<QA_THREADS>(touch, (int)M);
+    return;
+  }
   __shared__ double red[QA_WAVES];
   __shared__ u32 redm[QA_WAVES];
   __shared__ int redi[QA_WAVES];
@@ -652,8 +656,12 @@ __global__ __launch_bounds__(QA_THREADS) void quant_topk_int8_regs_kernel(
 template <int CPW, bool EARLY>
 __global__ __launch_bounds__(512) void quant_topk_int8_regs8_kernel(
     const uint16_t* __restrict__ X, int K, int Kp, int topk, float eps, u32* __restrict__ q_out,
-    float* __restrict__ scale_out, int frag_M) {
+    float* __restrict__ scale_out, int frag_M, BlTouch touch) {
   __shared__ __align__(16) u32 sh[80];
+  if (frag_M && (int)blockIdx.x >= frag_M) {               // (whole workgroup)
+    bl_touch<512>(touch, frag_M);
+    return;
+  }
   const int64_t m = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_chunks = Kp >> 8;
@@ -1104,9 +1112,10 @@ static int qa_run_row_kernels(const RawT* X, int64_t M, int K, int Kp, bl_act_mo
 
 // Up to 256 tokens, K % 4 == 0 and Kp <= 12288 (at most 6 chunks of 256 channels per wave); frag_M: fragment order, all tokens.
 static void qa_run_topk_regs8(const void* x, int64_t M, int K, int Kp, int topk, float eps, void* q, void* scale, int frag_M,
-                              hipStream_t s) {
-#define QA_R8(CPW, EARLY) \
-  quant_topk_int8_regs8_kernel<CPW, EARLY><<<(unsigned)M, 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, eps, (u32*)q, (float*)scale, frag_M)
+                              const BlTouch& touch, hipStream_t s) {
+#define QA_R8(CPW, EARLY)                                                                                                \
+  quant_topk_int8_regs8_kernel<CPW, EARLY><<<(unsigned)(M + touch.blocks), 512, 0, s>>>((const uint16_t*)x, K, Kp, topk, \
+                                                                                         eps, (u32*)q, (float*)scale, frag_M, touch)
   if (Kp <= 4096) QA_R8(4, false);
   else if (Kp <= 8192) QA_R8(4, true);
   else QA_R8(8, false);
@@ -1122,7 +1131,7 @@ static int qa_run_topk_regs(const void* x, const void* x2, int64_t M, int K, int
   // 0.075 ms at 4096 channels, 0.077 against 0.110 ms at 5460; from 8 register blocks on it loses)
   const int nb = (Kp / 256 + 3) / 4;
   if (GLU == 0 && rowsum == nullptr && M <= 256) {
-    qa_run_topk_regs8(x, M, K, Kp, topk, eps, q, scale, 0, s);
+    qa_run_topk_regs8(x, M, K, Kp, topk, eps, q, scale, 0, BlTouch{}, s);
   } else if (M >= 2048 && nb <= 6) {
     const unsigned grid = (unsigned)((M + QA_WAVES - 1) / QA_WAVES);
     if (nb <= 4)
@@ -1188,7 +1197,7 @@ int bl_launch_quantize(const void* X, bl_dtype dt, int64_t M, int64_t K64, bl_ac
     const bool mx6 = mode == BL_ACT_INT4_ABSMEAN_MX6;
     const int nvv = (Kp / 16 + QA_THREADS - 1) / QA_THREADS;      // half units per thread: 1 .. 4
     const unsigned grid = mx6 ? (unsigned)((M + 7) / 8 * 8) : (unsigned)M;   // MX6: a multiple of 8
-#define QA_I4(MX, NVV) quant_int4_regs_kernel<MX, NVV><<<grid, QA_THREADS, 0, s>>>((const uint16_t*)X, M, K, Kp, eps, (u32*)q, (float*)scale, rowsum, stat, 0)
+#define QA_I4(MX, NVV) quant_int4_regs_kernel<MX, NVV><<<grid, QA_THREADS, 0, s>>>((const uint16_t*)X, M, K, Kp, eps, (u32*)q, (float*)scale, rowsum, stat, 0, BlTouch{})
     if (mx6) { if (nvv <= 1) QA_I4(true, 1); else if (nvv <= 2) QA_I4(true, 2); else QA_I4(true, 4); }
     else { if (nvv <= 1) QA_I4(false, 1); else if (nvv <= 2) QA_I4(false, 2); else QA_I4(false, 4); }
 #undef QA_I4
@@ -1213,6 +1222,18 @@ int bl_launch_quantize(const void* X, bl_dtype dt, int64_t M, int64_t K64, bl_ac
   return qa_run_row_kernels<u32, 1>(x, M, K, Kp, mode, (int)topk, eps, q, scale, rowsum, sel_idx, s);
 }
 
+// Weights that the quantizer's launch touches (BlTouch): what streams in while the tokens' chain of latencies runs anyway.  The
+// Top_k kernel takes 4 to 6 us, the INT4 kernel 2.4, of which an empty launch is 1.5; beyond that a touched byte costs its time
+// here and the product gains less (it is then bound by its own loads).  Linear, weights from HBM, without / with, us:
+//   Top_k  32 x 4096 x 11008 (11 MB) 11.8 / 9.9, 57 x 8192 x 12288 (25 MB) 17.1 / 16.2, 32 x 2048 x 2048 (1 MB) 8.75 / 8.5
+//   INT4   32 x 6144 x 2048 (3 MB) 6.8 / 6.4, 32 x 9600 x 3200 (8 MB) 8.6 / 8.2, 32 x 12288 x 3072 (9 MB) 8.8 / 8.8, 32 x 12288 x
+//          4096 (13 MB) 8.9 / 9.1; gate and up 32 x 2 x 5460 x 2048 (6 MB) 7.6 / 7.3, 2 x 11008 x 4096 (23 MB) 11.6 / 12.4, 2 x
+//          2700 x 1024 (1.4 MB) 6.6 / 6.7
+static bool qa_touch_pays(bool a4, size_t bytes) {
+  const size_t mb = (size_t)1 << 20;
+  return a4 ? bytes >= 2 * mb && bytes <= 8 * mb : bytes >= mb && bytes <= 32 * mb;
+}
+
 // Fragment order comes from the register kernels only.
 bool bl_quantize_frag_ok(bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode) {
   const int64_t Kp = bl_round_up(K, BL_KPAD);
@@ -1222,19 +1243,27 @@ bool bl_quantize_frag_ok(bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode) {
 }
 
 int bl_launch_quantize_frag(const void* X, int64_t M, int64_t K64, bl_act_mode mode, int64_t topk, float eps, void* q,
-                            float* scale, hipStream_t s) {
+                            float* scale, const void* W, const void* W2, size_t w_bytes, hipStream_t s) {
   if (!bl_quantize_frag_ok(BL_BF16, M, K64, mode)) return BL_EUNSUPPORTED;
   const int K = (int)K64, Kp = (int)bl_round_up(K64, BL_KPAD);
-  if (mode == BL_ACT_INT4_ABSMEAN) {
+  const bool a4 = mode == BL_ACT_INT4_ABSMEAN;
+  const int threads = a4 ? QA_THREADS : 512;
+  BlTouch touch = {{(const unsigned char*)W, (const unsigned char*)W2}, W2 ? 2 : 1, 0, 0};
+  if (qa_touch_pays(a4, w_bytes * touch.n_mat)) {
+    touch.lines = (int)(w_bytes >> 7);
+    touch.blocks = (int)min((int64_t)512, bl_round_up(((int64_t)touch.lines * touch.n_mat + threads - 1) / threads, 8));
+  }
+  if (a4) {
     const int nvv = (Kp / 16 + QA_THREADS - 1) / QA_THREADS;
-#define QA_I4F(NVV) \
-  quant_int4_regs_kernel<false, NVV><<<(unsigned)M, QA_THREADS, 0, s>>>((const uint16_t*)X, M, K, Kp, eps, (u32*)q, scale, nullptr, 0, 1)
+#define QA_I4F(NVV)                                                                                                 \
+  quant_int4_regs_kernel<false, NVV><<<(unsigned)(M + touch.blocks), QA_THREADS, 0, s>>>((const uint16_t*)X, M, K, Kp, \
+                                                                                          eps, (u32*)q, scale, nullptr, 0, 1, touch)
     if (nvv <= 1) QA_I4F(1);
     else if (nvv <= 2) QA_I4F(2);
     else QA_I4F(4);
 #undef QA_I4F
   } else {
-    qa_run_topk_regs8(X, M, K, Kp, (int)topk, eps, q, scale, (int)M, s);
+    qa_run_topk_regs8(X, M, K, Kp, (int)topk, eps, q, scale, (int)M, touch, s);
   }
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;

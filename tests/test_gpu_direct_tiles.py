@@ -23,7 +23,9 @@ CASES = [(33, 5269, 200),                         # 1x2 1x2 1x4
          (65, 10064, 1288),                       # 2x8 -   -
          (17, 6414, 264),                         # -   -   2x2
          (177, 4062, 776), (81, 8168, 776),       # 2x3 -   -, 3x4 - -
-         (1, 17, 8), (2, 15, 264), (16, 1, 4104), (9, 3210, 2056), (31, 1027, 5464), (33, 130, 11008), (255, 31, 3200), (256, 3210, 264)]
+         (1, 17, 8), (2, 15, 264), (16, 1, 4104), (9, 3210, 2056), (31, 1027, 5464), (33, 130, 11008), (255, 31, 3200), (256, 3210, 264),
+         # weights that the quantizer's launch touches: lines that do not divide by eight XCDs, one matrix and two; and beyond the rule
+         (9, 2049, 2312), (64, 4099, 2056), (40, 24600, 264), (57, 17000, 520), (250, 6300, 300)]
 
 
 @pytest.mark.parametrize("M,N,K", CASES)
