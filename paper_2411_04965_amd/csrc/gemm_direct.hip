@@ -192,23 +192,19 @@ static int gx_go(const void* q, const float* scale, int M, int KT, const void* W
 //          200 x 3200 x 8640 14.3 -> 11.2, 256 x 4096 x 4096 9.4 -> 7.8
 //   INT4   32 x 12288 x 4096 8.9 -> 5.6, 64 x 12288 x 4096 9.5 -> 7.4; gate and up 32 x 2 x 11008 x 4096 12.8 -> 8.0,
 //          64 x 2 x 5460 x 2048 8.0 -> 5.2
-static double gx_cost(int64_t M, int64_t N, int KT, int code_loads, int mt, int nt, int ntm) {
-  const int64_t blocks = ((M + 16 * mt - 1) / (16 * mt)) * (((N + 15) / 16 + ntm - 1) / ntm), cus = bl_num_cus();
-  const double share = (double)blocks / cus, turns = (double)((blocks + cus - 1) / cus);
-  double busy = turns;
-  if (mt * nt <= 10 && turns > 1.0) busy = 0.85 * (0.7 * turns + 0.3 * share);
-  return busy * (KT * (code_loads * mt + nt) + 6 * mt * nt);
-}
-
 struct GxTile { int mt, nt; };
 
 template <int COUNT>
 static int gx_pick(const GxTile (&tiles)[COUNT], int64_t M, int64_t N, int KT, int code_loads, bool glu) {
+  const int cus = bl_num_cus(), m16 = (int)((M + 15) / 16), n16 = (int)((N + 15) / 16);   // (M N <= 2^40, M <= 256: 32 bits each)
   int best = 0;
-  double best_cost = 0.0;
+  float best_cost = 0.0f;
   for (int i = 0; i < COUNT; ++i) {
-    const double c = gx_cost(M, N, KT, code_loads, tiles[i].mt, tiles[i].nt, glu ? tiles[i].nt / 2 : tiles[i].nt);
-    if (i == 0 || c < best_cost) { best = i; best_cost = c; }
+    const int mt = tiles[i].mt, nt = tiles[i].nt, ntm = glu ? nt / 2 : nt;
+    const float share = (float)((m16 + mt - 1) / mt) * (float)((n16 + ntm - 1) / ntm) / (float)cus, turns = ceilf(share);
+    const float busy = mt * nt <= 10 && turns > 1.0f ? 0.85f * (0.7f * turns + 0.3f * share) : turns;
+    const float cost = busy * (float)(KT * (code_loads * mt + nt) + 6 * mt * nt);
+    if (i == 0 || cost < best_cost) { best = i; best_cost = cost; }
   }
   return best;
 }
