@@ -309,7 +309,7 @@ static int gemm_dispatch(const void* q, const void* scale, bl_act_mode mode, int
   if (mode == BL_ACT_FP4_E1M2_B32) return BL_EUNSUPPORTED;   // a quantizer format only: no MFMA operand type
   if (int4_nibble_mode(mode)) mode = BL_ACT_INT4_ABSMEAN;   // same codes, same rescale
   if (mx_mode(mode) != mx_layout(layout)) return BL_EINVAL;
-  if (mode == BL_ACT_INT4_ABSMEAN_MX6 && layout == BL_W_MX2 && bl_gemm_mid_mx_ok(M, N))
+  if (mode == BL_ACT_INT4_ABSMEAN_MX6 && layout == BL_W_MX2 && bl_gemm_mid_mx_ok(M, N, K, false))
     return bl_launch_gemm_mid_mx(q, (const float*)scale, M, K, W_packed, alpha, N, Y, y_dtype, acc_out, s);
   if (mode == BL_ACT_INT4_ABSMEAN_MX6)
     return bl_launch_gemm_a4_mx(q, (const float*)scale, M, K, W_packed, layout == BL_W_MX2, alpha, N, Y, y_dtype,
@@ -518,7 +518,7 @@ extern "C" int bitlinear_a4_gate_up(const void* X, bl_dtype x_dtype, int64_t M, 
   if (mx_layout(layout) && H && !G && !U) {
     rc = bl_launch_quantize(X, x_dtype, M, K, mode, 0, eps, codes, scales, nullptr, nullptr, s);
     if (rc) return rc;
-    if (layout == BL_W_MX2 && bl_gemm_mid_mx_ok(M, 2 * N))
+    if (layout == BL_W_MX2 && bl_gemm_mid_mx_ok(M, N, K, true))
       return bl_launch_gemm_mid_mx_glu(codes, (const float*)scales, M, K, W_gate, alpha_gate, W_up, alpha_up, N, H, s);
     return bl_launch_gemm_a4_mx_glu(codes, (const float*)scales, M, K, W_gate, alpha_gate, W_up, alpha_up,
                                     layout == BL_W_MX2, N, H, s);
@@ -587,7 +587,7 @@ extern "C" int bitlinear_gemm_glu(const void* q, const float* scale, int64_t M, 
   if (rc) return rc;
   if (!bl_aligned16(q) || !bl_aligned16(W_gate) || !bl_aligned16(W_up) || !bl_aligned16(H)) return BL_EALIGN;
   if (reinterpret_cast<uintptr_t>(scale) & 3) return BL_EALIGN;
-  if (layout == BL_W_MX2 && bl_gemm_mid_mx_ok(M, 2 * N))
+  if (layout == BL_W_MX2 && bl_gemm_mid_mx_ok(M, N, K, true))
     return bl_launch_gemm_mid_mx_glu(q, scale, M, K, W_gate, alpha_gate, W_up, alpha_up, N, H, (hipStream_t)stream);
   return bl_launch_gemm_a4_mx_glu(q, scale, M, K, W_gate, alpha_gate, W_up, alpha_up, layout == BL_W_MX2, N, H,
                                   (hipStream_t)stream);

@@ -226,7 +226,7 @@ size_t bl_gemm_decode_ws_bytes(int64_t M, int64_t N, int64_t K);
 bool bl_gemm_mid_ok(int64_t M, int64_t N);
 int bl_launch_gemm_mid(const void* q, const float* scale, bl_act_mode mode, int64_t M, int64_t K, const void* Wp,
                        const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);
-bool bl_gemm_mid_mx_ok(int64_t M, int64_t n_cols);
+bool bl_gemm_mid_mx_ok(int64_t M, int64_t N, int64_t K, bool glu);
 int bl_launch_gemm_mid_mx(const void* q, const float* scale, int64_t M, int64_t K, const void* Wp, const float* alpha,
                           int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);
 int bl_launch_gemm_mid_mx_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,

@@ -16,7 +16,7 @@
 // where K is split, which is still the better one for long K and few outputs: gr_long_k): INT8 64 x 4096 x 4096 12.5 -> 9.1,
 // 64 x 12288 x 4096 17.8 -> 9.7, 64 x 2048 x 5460 12.2 -> 11.4; gate/up of 64 x 2 x 11008 x 4096 18.4 -> 14.2.
 //
-// Structure.  A group of 4 waves (2 x 2) owns a tile of 64 TM x 64 TN; a wave has TM x TN MFMA tiles (row operand =
+// Structure.  A group of 4 waves (2 x 2; block-float, mostly 1 x 4) owns a tile of 64 TM x 64 TN; a wave has TM x TN MFMA tiles (row operand =
 // weights, column operand = tokens, so a lane ends up with groups of 4 consecutive outputs of one token).  One step =
 // 256 channels = NSUB sub-steps of TM TN MFMAs.  Two LDS stages, two register sets per operand:
 //   first sub-steps        write the activations of step s + 1 into the other stage, refill their registers (s + 3)
@@ -41,11 +41,12 @@ enum { GM_ROWS = 0, GM_ANY = 1 };
 template <int FMT, int TM, int TN, int G>
 struct GmFmt {
   static constexpr bool mx = FMT == GM_MX;
-  static_assert(!mx || TM == 1, "block-float tiles are 64 tokens: two waves share a 32-token block row");
-  static constexpr int bm = 64 * TM, bn = 64 * TN;
+  static_assert(!mx || TM <= 2, "block-float tiles are 64 tokens");
+  static constexpr int wn = mx && TM == 2 ? 4 : 2;         // waves across the outputs; the rest across the tokens
+  static constexpr int bm = 32 * (4 / wn) * TM, bn = 32 * wn * TN;
   static constexpr int nsub = mx ? 4 : 8;                  // MFMA sub-steps per step of 256 channels
-  static constexpr int la = (FMT == GM_I8 ? 4 : FMT == GM_I4 ? 2 : 3) * TM;   // 16-byte activation loads per thread and step
-  static constexpr int per_sub = FMT == GM_I4 ? 1 : TM;    // of them written to LDS per sub-step
+  static constexpr int la = (FMT == GM_I8 ? 64 : FMT == GM_I4 ? 32 : 48) * bm / 1024;   // 16-byte activation loads per thread and step
+  static constexpr int per_sub = FMT == GM_I8 ? TM : 1;    // of them written to LDS per sub-step
   static constexpr int stage = mx ? 2 * 6144 : bm * 256;
   static constexpr int shift = FMT == GM_I8 ? 6 : FMT == GM_I4 ? 10 : 0;   // the int8 expansion scales the sums by 2^shift
   static constexpr int tb_row = bn * 2 + 16;               // epilogue: one token's outputs in LDS, padded against conflicts
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(GM_THREADS * G, 2) void gemm_mid_kernel(
   const int tid = threadIdx.x & (GM_THREADS - 1), lane = tid & 63;   // (tid: within the K group)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = G > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = F::wn == 4 ? 0 : wave >> 1, wn = F::wn == 4 ? wave : wave & 1;
   const int l32 = lane & 31, lh = lane >> 5;
   int m0, n0;
   bl_tile_origin((int)blockIdx.x, MT * NTB, MT, NTB, F::bm, F::bn, m0, n0);
@@ -442,8 +443,8 @@ static int gm_go(const void* q, const float* scale, int M, int KT, const void* W
 
 // ---- dispatch rules.  Costs in turns of the chip (tiles over CUs, rounded up).  (The figures below are of repeated calls on one
 // weight matrix; with weights from HBM few tokens take 1 to 2 us more on either side.)
-static int64_t gm_turns(int64_t M, int64_t N, int bm, int bn) {
-  const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), cus = bl_num_cus();
+static int64_t gm_turns(int64_t M, int64_t N, int bm, int bn, int64_t cus = bl_num_cus()) {
+  const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   return (tiles + cus - 1) / cus;
 }
 
@@ -452,10 +453,23 @@ static int64_t gm_turns(int64_t M, int64_t N, int bm, int bn) {
 // 140, 8192 x 3200 x 8640 174 against 180; on the other side 2048 x 4096 x 11008 100 against 71.
 bool bl_gemm_mid_ok(int64_t M, int64_t N) { return 7 * gm_turns(M, N, 256, 256) > 2 * gm_turns(M, N, 128, 128); }
 
-// Block-float codes: a 256 x 256 tile takes 4.8 times as long as a 64 x 128 tile (1.63 against 0.34 us per 256 channels).
-// 1000 x 12288 x 4096: 30.1 us against 36.8; 500 x 9600 x 3200: 23.4 against 16.4; gate and up of 500 x 2 x 8640 x 3200:
-// 23.2 against 24.8; of 200 x 2 x 8640 x 3200: 21.6 against 14.9.  `n_cols` counts the outputs of both matrices.
-bool bl_gemm_mid_mx_ok(int64_t M, int64_t n_cols) { return 24 * gm_turns(M, n_cols, 256, 256) > 5 * gm_turns(M, n_cols, 64, 128); }
+// Block-float codes: 64 x 256 tiles against 256 x 256.  A turn of the large ones takes 3.05 times as long (the first one 2.8) from
+// 2048 channels on, less below (a small tile's start and end weigh more; not so for gate and up, whose large tiles end slowly, and
+// which take 3.1 times as long, the first 2.9, at any K); where the small tiles do not fill their last turn, blocks
+// that share a CU finish sooner, which counts for 0.3 of it.  Product alone, large / small, us: 500 x 12288 x 4096 23.1 / 20.3,
+// 1500 x 12288 x 4096 60.4 / 50.0, 1000 x 12288 x 4096 33.8 / 34.9, 2048 x 12288 x 4096 62.0 / 64.9, 2048 x 9600 x 3200 51.4 / 47.9,
+// 4096 x 9600 x 3200 78.8 / 87.7, 1000 x 6144 x 8192 45.1 / 35.7, 1700 x 3072 x 1024 9.8 / 9.4, 3000 x 3072 x 1024 14.1 / 15.8; gate and up
+// 1000 x 2 x 8640 x 3200 50.6 / 42.2, 1500 x 2 x 11008 x 4096 89.3 / 84.9, 2048 x 2 x 11008 x 4096 95.3 / 105.4, 3000 x 2 x 5460 x 2048
+// 52.4 / 46.0, 3000 x 2 x 2700 x 1024 24.5 / 18.0, 2048 x 2 x 4000 x 1024 15.1 / 16.3.
+bool bl_gemm_mid_mx_ok(int64_t M, int64_t N, int64_t K, bool glu) {
+  const int64_t n_cols = glu ? 2 * N : N;                  // the outputs of both matrices
+  const int64_t cus = bl_num_cus();
+  const double share = (double)(((M + 63) / 64) * ((n_cols + 255) / 256)) / cus;
+  const double KT = (double)(bl_round_up(K, BL_KPAD) >> 8);
+  const double small = 0.7 * (double)gm_turns(M, n_cols, 64, 256, cus) + 0.3 * share, large = (double)gm_turns(M, n_cols, 256, 256, cus);
+  if (glu) return small < 3.1 * large - 0.2;
+  return small < (3.05 * large - 0.25) * (KT < 8.0 ? 0.6 + 0.05 * KT : 1.0);
+}
 
 #define GM_CALL(FMT, OUT, GLU, TM, TN, G) \
   gm_go<FMT, OUT, GLU, TM, TN, G>(q, scale, (int)M, KT, Wp, Wp2, alpha, alpha2, (int)N, Y, ydt, acc_out, s)
@@ -474,16 +488,22 @@ static int gm_int(const void* q, const float* scale, int64_t M, int64_t K, const
   return GM_CALL(FMT, OUT, false, 2, 2, 1);
 }
 
-// Block-float codes: 64 x 128 tiles, with two K groups while they fill one turn (66 x 12288 x 4096: 8.3 us against 9.4;
-// 200 x 9600 x 3200, 300 tiles: 13.2 against 10.8).  Gate and up: one group (66 x 2 x 11008 x 4096: 12.8 against 11.7).
+// Block-float codes.  What bounds a step is the CU's vector loads (about 53 bytes per clock): with the four waves side by side
+// (1 x 4, every wave with all 64 tokens) the weights are fetched once instead of by two waves, 20 KB a step for 64 x 128 instead of
+// 28, and 28 KB for 64 x 256.  So 64 x 256 tiles wherever they save a turn or more (a turn of theirs is 1.4 times as long), else 64 x
+// 128, with two K groups (2 x 2 waves each) where these fill one turn and K is long.  Product alone, weights from HBM, 2 x 2 waves / 64 x 128 / 64 x 256:
+// 200 x 9600 x 3200 13.2 / 12.4 / 10.9, 200 x 6144 x 2048 7.1 / 6.8 / 7.8, 300 x 12288 x 4096 17.2 / 16.7 / 14.2, 700 x 9600 x 3200 25.0 /
+// 25.0 / 21.5; one / two K groups 66 x 12288 x 4096 10.6 / 9.7, 128 x 9600 x 3200 9.6 / 10.4.
 template <int OUT>
 static int gm_mx(const void* q, const float* scale, int64_t M, int64_t K, const void* Wp, const float* alpha, int64_t N,
                  void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s) {
   const int KT = (int)(bl_round_up(K, BL_KPAD) >> 8);
   const void* Wp2 = nullptr;
   const float* alpha2 = nullptr;
-  if (gm_turns(M, N, 64, 128) == 1) return GM_CALL(GM_MX, OUT, false, 1, 2, 2);
-  return GM_CALL(GM_MX, OUT, false, 1, 2, 1);
+  const int64_t cus = bl_num_cus(), t128 = gm_turns(M, N, 64, 128, cus);
+  if (7 * gm_turns(M, N, 64, 256, cus) <= 5 * t128) return GM_CALL(GM_MX, OUT, false, 2, 2, 1);
+  if (t128 == 1 && KT >= 16) return GM_CALL(GM_MX, OUT, false, 1, 2, 2);
+  return GM_CALL(GM_MX, OUT, false, 2, 1, 1);
 }
 
 int bl_launch_gemm_mid(const void* q, const float* scale, bl_act_mode mode, int64_t M, int64_t K, const void* Wp,
@@ -506,7 +526,10 @@ int bl_launch_gemm_mid_mx_glu(const void* q, const float* scale, int64_t M, int6
   const int KT = (int)(bl_round_up(K, BL_KPAD) >> 8);
   const bl_dtype ydt = BL_BF16;
   int32_t* acc_out = nullptr;
-  return GM_CALL(GM_MX, GM_ROWS, true, 1, 2, 1);
+  // 64 outputs of either matrix per block while those blocks fill one turn, else 128 (1 x 4 waves): 128 x 2 x 5460 x 2048 6.6 us /
+  // 7.3; 200 x 2 x 5460 x 2048 9.1 / 7.6, 100 x 2 x 11008 x 4096 15.2 / 12.0, 700 x 2 x 11008 x 4096 51.5 / 40.3
+  if (gm_turns(M, 2 * N, 64, 128) == 1) return GM_CALL(GM_MX, GM_ROWS, true, 1, 2, 1);
+  return GM_CALL(GM_MX, GM_ROWS, true, 2, 2, 1);
 }
 
 // INT4 codes x two BL_W_GEMM matrices (33 to 64 tokens): 64 outputs of either per block, two K groups.
