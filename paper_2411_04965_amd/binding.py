@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libbitlinear.so (the C ABI declared in include/bitlinear.h).
+"""Thin binding of libbitlinear.so (the C ABI declared in include/bitlinear.h): ctypes, and for the three linears that a
+serving loop calls a module that unpacks plain tensors natively.
 
 Argument marshalling only: every function allocates its outputs with torch (device
 memory), passes raw device pointers and the current HIP stream, and checks the status
@@ -6,12 +7,15 @@ code.  No arithmetic of the method happens here, and there is no fallback: if th
 library has not been built, loading fails loudly.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libbitlinear.so")
+MARSHAL_PATH = os.path.join(_HERE, "lib", "bitlinear_marshal.so")
 
 BL_F32, BL_BF16 = 0, 1
 BL_ACT_INT4_ABSMEAN, BL_ACT_TOPK_INT8_ABSMAX, BL_ACT_FP4_E2M1_B32, BL_ACT_INT4_ABSMEAN_MX6 = 0, 1, 2, 3
@@ -82,6 +86,26 @@ def lib():
     return _lib
 
 
+_marshal = None
+
+
+def _native():
+    """The marshalling module (csrc/marshal.cpp), loaded once; False on a torch that it cannot be loaded with."""
+    global _marshal
+    if _marshal is None:
+        lib()
+        if not os.path.exists(MARSHAL_PATH):
+            raise RuntimeError("bitlinear_marshal.so is not built (%s). Run `python -m paper_2411_04965_amd.build`." % MARSHAL_PATH)
+        try:
+            loader = importlib.machinery.ExtensionFileLoader("bitlinear_marshal", MARSHAL_PATH)
+            m = importlib.util.module_from_spec(importlib.util.spec_from_loader("bitlinear_marshal", loader))
+            loader.exec_module(m)
+            _marshal = m
+        except ImportError:
+            _marshal = False
+    return _marshal
+
+
 class BitlinearError(RuntimeError):
     def __init__(self, fn, status):
         self.status = status
@@ -92,6 +116,13 @@ class BitlinearError(RuntimeError):
 def _check(fn, status):
     if status != 0:
         raise BitlinearError(fn, status)
+
+
+def _done(fn, r):
+    """What a call of the marshalling module came to: its output, or a status other than 0."""
+    if type(r) is int:
+        _check(fn, r)
+    return r
 
 
 # torch.cuda.current_stream() builds a Stream object: 2.7 us of the 8.1 us that a one-token linear took on the host.
@@ -190,6 +221,11 @@ def _out(M, N, y_dtype, device, want_acc):
 
 def bitlinear_a4(X, W_packed, alpha, N, eps=DEFAULT_EPS, act_fp4=False, y_dtype=torch.bfloat16,
                  want_acc=False, ws=None, out=None, layout=BL_W_GEMM):
+    m = _marshal or _native()
+    if m and not want_acc:
+        r = m.a4(X, W_packed, alpha, N, eps, act_fp4, y_dtype, ws, out, layout)
+        if r is not None:
+            return _done("bitlinear_a4", r)
     _dev(X)
     M, K = X.shape
     if act_fp4:
@@ -207,6 +243,11 @@ def bitlinear_a4(X, W_packed, alpha, N, eps=DEFAULT_EPS, act_fp4=False, y_dtype=
 
 def bitlinear_a8_sparse(X, topk, W_packed, alpha, N, eps=DEFAULT_EPS, layout=BL_W_GEMM,
                         y_dtype=torch.bfloat16, want_acc=False, ws=None, out=None):
+    m = _marshal or _native()
+    if m and not want_acc:
+        r = m.a8_sparse(X, topk, W_packed, alpha, N, eps, layout, y_dtype, ws, out)
+        if r is not None:
+            return _done("bitlinear_a8_sparse", r)
     _dev(X)
     M, K = X.shape
     if ws is None:
@@ -257,6 +298,11 @@ def bitlinear_a4_gate_up(X, W_gate, alpha_gate, W_up, alpha_up, N, eps=DEFAULT_E
                          want=("G", "U", "H"), gu_dtype=torch.float32, ws=None, out=None):
     """Gate and up projection on one quantized input.  Returns a dict with the tensors named in
     `want` (G, U of gu_dtype; H = bf16(U * max(G, 0)^2)); `out` may bring preallocated ones."""
+    m = _marshal or _native()
+    if m:
+        r = m.gate_up(X, W_gate, alpha_gate, W_up, alpha_up, N, eps, layout, want, ws, out)
+        if r is not None:
+            return _done("bitlinear_a4_gate_up", r)
     _dev(X)
     M, K = X.shape
     out = dict(out or {})

@@ -1,4 +1,5 @@
-"""Build the HIP library (gfx950 only) in-tree: paper_2411_04965_amd/lib/libbitlinear.so."""
+"""Build the HIP library (gfx950 only) in-tree, paper_2411_04965_amd/lib/libbitlinear.so, and the host-only module beside it that
+marshals arguments for the Python binding, bitlinear_marshal.so."""
 import os
 import subprocess
 import sys
@@ -9,6 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIB_DIR, "libbitlinear.so")
+MARSHAL = os.path.join(LIB_DIR, "bitlinear_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -29,6 +31,24 @@ def _compile(src):
     return src, obj, r
 
 
+def _build_marshal():
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL]
+    for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", d]
+    for d in cpp_extension.library_paths() + [LIB_DIR]:
+        cmd += ["-L" + d]
+    cmd += ["-l:libbitlinear.so", "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building bitlinear_marshal failed:\n" + r.stderr)
+
+
 def build(verbose=True, jobs=4):
     os.makedirs(OBJ, exist_ok=True)
     os.makedirs(LIB_DIR, exist_ok=True)
@@ -45,6 +65,7 @@ def build(verbose=True, jobs=4):
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    _build_marshal()
     if verbose:
         print("built", LIB)
     return LIB
