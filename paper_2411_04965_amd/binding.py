@@ -93,13 +93,15 @@ def _native():
     """The marshalling module (csrc/marshal.cpp), loaded once; False on a torch that it cannot be loaded with."""
     global _marshal
     if _marshal is None:
-        lib()
+        L = lib()
         if not os.path.exists(MARSHAL_PATH):
             raise RuntimeError("bitlinear_marshal.so is not built (%s). Run `python -m paper_2411_04965_amd.build`." % MARSHAL_PATH)
         try:
             loader = importlib.machinery.ExtensionFileLoader("bitlinear_marshal", MARSHAL_PATH)
             m = importlib.util.module_from_spec(importlib.util.spec_from_loader("bitlinear_marshal", loader))
             loader.exec_module(m)
+            m.use(*(ctypes.cast(f, _vp).value for f in (L.bitlinear_a4, L.bitlinear_a8_sparse, L.bitlinear_a4_gate_up,
+                                                        L.bitlinear_workspace_bytes, L.bitlinear_gate_up_workspace_bytes)))
             _marshal = m
         except ImportError:
             _marshal = False

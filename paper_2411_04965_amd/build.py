@@ -41,9 +41,9 @@ def _build_marshal():
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL]
     for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
         cmd += ["-isystem", d]
-    for d in cpp_extension.library_paths() + [LIB_DIR]:
+    for d in cpp_extension.library_paths():
         cmd += ["-L" + d]
-    cmd += ["-l:libbitlinear.so", "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-lc10"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("building bitlinear_marshal failed:\n" + r.stderr)

@@ -20,6 +20,15 @@
 
 namespace {
 
+// the library's functions, handed over by the binding that loaded it (so two copies of this package in one process keep apart)
+struct {
+  decltype(&::bitlinear_a4) a4;
+  decltype(&::bitlinear_a8_sparse) a8_sparse;
+  decltype(&::bitlinear_a4_gate_up) gate_up;
+  decltype(&::bitlinear_workspace_bytes) workspace_bytes;
+  decltype(&::bitlinear_gate_up_workspace_bytes) gate_up_workspace_bytes;
+} lib;
+
 PyObject* get_device = nullptr;    // torch._C._cuda_getDevice
 PyObject* get_stream = nullptr;    // torch._C._cuda_getCurrentRawStream
 PyObject* str_H = nullptr;
@@ -161,12 +170,12 @@ PyObject* a4(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (in.M < 1 || N < 1 || N > ((int64_t)1 << 31) || layout < 0 || layout > 4) throw NotPlain();
     const int mode = fp4 ? (mx(layout) ? BL_ACT_FP4_E2M1_B32_MX : BL_ACT_FP4_E2M1_B32)
                          : (mx(layout) ? BL_ACT_INT4_ABSMEAN_MX6 : BL_ACT_INT4_ABSMEAN);
-    Workspace ws(a[7], in, [&] { return bitlinear_workspace_bytes((bl_act_mode)mode, in.M, N, in.K); });
+    Workspace ws(a[7], in, [&] { return lib.workspace_bytes((bl_act_mode)mode, in.M, N, in.K); });
     Output y(a[8], in, N, scalar_type(a[6]));
     void* const s = stream();
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = bitlinear_a4(in.p, (bl_dtype)in.dt, in.M, in.K, w, (bl_w_layout)layout, alpha, N, eps, fp4 ? 1 : 0, y.p,
+    rc = lib.a4(in.p, (bl_dtype)in.dt, in.M, in.K, w, (bl_w_layout)layout, alpha, N, eps, fp4 ? 1 : 0, y.p,
                       (bl_dtype)y.dt, nullptr, ws.p, ws.n, s);
     Py_END_ALLOW_THREADS
     return rc ? PyLong_FromLong(rc) : y.result();
@@ -182,12 +191,12 @@ PyObject* a8_sparse(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const float* const alpha = (const float*)pointer(a[3]);
     const float eps = real(a[5]);
     if (in.M < 1 || N < 1 || N > ((int64_t)1 << 31) || layout < 0 || layout > 4) throw NotPlain();
-    Workspace ws(a[8], in, [&] { return bitlinear_workspace_bytes(BL_ACT_TOPK_INT8_ABSMAX, in.M, N, in.K); });
+    Workspace ws(a[8], in, [&] { return lib.workspace_bytes(BL_ACT_TOPK_INT8_ABSMAX, in.M, N, in.K); });
     Output y(a[9], in, N, scalar_type(a[7]));
     void* const s = stream();
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = bitlinear_a8_sparse(in.p, (bl_dtype)in.dt, in.M, in.K, topk, w, (bl_w_layout)layout, alpha, N, eps, y.p,
+    rc = lib.a8_sparse(in.p, (bl_dtype)in.dt, in.M, in.K, topk, w, (bl_w_layout)layout, alpha, N, eps, y.p,
                              (bl_dtype)y.dt, nullptr, ws.p, ws.n, s);
     Py_END_ALLOW_THREADS
     return rc ? PyLong_FromLong(rc) : y.result();
@@ -215,7 +224,7 @@ PyObject* gate_up(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t N = integer(a[5]), layout = integer(a[7]);
     const float eps = real(a[6]);
     if (in.M < 1 || N < 1 || N > ((int64_t)1 << 31) || layout < 0 || layout > 4) throw NotPlain();
-    Workspace ws(a[9], in, [&] { return bitlinear_gate_up_workspace_bytes(in.M, N, in.K, (bl_w_layout)layout); });
+    Workspace ws(a[9], in, [&] { return lib.gate_up_workspace_bytes(in.M, N, in.K, (bl_w_layout)layout); });
     void* hp;
     at::Tensor own;
     if (h != Py_None) {
@@ -227,7 +236,7 @@ PyObject* gate_up(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* const s = stream();
     int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = bitlinear_a4_gate_up(in.p, (bl_dtype)in.dt, in.M, in.K, wg, ag, wu, au, (bl_w_layout)layout, N, eps, nullptr, nullptr,
+    rc = lib.gate_up(in.p, (bl_dtype)in.dt, in.M, in.K, wg, ag, wu, au, (bl_w_layout)layout, N, eps, nullptr, nullptr,
                               BL_F32, hp, ws.p, ws.n, s);
     Py_END_ALLOW_THREADS
     if (rc) return PyLong_FromLong(rc);
@@ -241,7 +250,27 @@ PyObject* gate_up(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
+// (addresses of bitlinear_a4, bitlinear_a8_sparse, bitlinear_a4_gate_up, bitlinear_workspace_bytes, bitlinear_gate_up_workspace_bytes)
+PyObject* use(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  void* p[5];
+  if (n != 5) {
+    PyErr_SetString(PyExc_TypeError, "five addresses expected");
+    return nullptr;
+  }
+  for (int i = 0; i < 5; ++i) {
+    p[i] = PyLong_AsVoidPtr(a[i]);
+    if (!p[i]) {
+      if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null address");
+      return nullptr;
+    }
+  }
+  lib = {(decltype(lib.a4))p[0], (decltype(lib.a8_sparse))p[1], (decltype(lib.gate_up))p[2], (decltype(lib.workspace_bytes))p[3],
+         (decltype(lib.gate_up_workspace_bytes))p[4]};
+  Py_RETURN_NONE;
+}
+
 PyMethodDef methods[] = {
+    {"use", (PyCFunction)(void (*)(void))use, METH_FASTCALL, "the library's functions, by address; before any other call"},
     {"a4", (PyCFunction)(void (*)(void))a4, METH_FASTCALL, "bitlinear_a4"},
     {"a8_sparse", (PyCFunction)(void (*)(void))a8_sparse, METH_FASTCALL, "bitlinear_a8_sparse"},
     {"gate_up", (PyCFunction)(void (*)(void))gate_up, METH_FASTCALL, "bitlinear_a4_gate_up, H only"},
