@@ -201,8 +201,8 @@ int bl_launch_quantize(const void* X, bl_dtype dt, int64_t M, int64_t K, bl_act_
                        int32_t* sel_idx, hipStream_t s);
 // the same codes in fragment order, for gemm_direct.hip; W, W2 (nullable), w_bytes each: the product's weights
 bool bl_quantize_frag_ok(bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode);
-int bl_launch_quantize_frag(const void* X, int64_t M, int64_t K, bl_act_mode mode, int64_t topk, float eps, void* q,
-                            float* scale, const void* W, const void* W2, size_t w_bytes, hipStream_t s);
+int bl_launch_quantize_frag(const void* X, bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode, int64_t topk, float eps,
+                            void* q, float* scale, const void* W, const void* W2, size_t w_bytes, hipStream_t s);
 bool bl_gemm_direct_ok(int64_t M, int64_t n_cols);
 int bl_launch_gemm_direct(const void* q, const float* scale, bl_act_mode mode, int64_t M, int64_t K, const void* Wp,
                           const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);

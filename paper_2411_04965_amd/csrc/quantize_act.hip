@@ -63,10 +63,10 @@ __device__ __forceinline__ u32 qa_e3m2_of_levelf(float p) {
 // packed nibbles.
 // stat: 0 = eq. 7 (beta = mean |x|), 1 = beta = 2 mean |x|, 2 = absmax with 7 levels (ablation
 // quantizers of Section 4.3)
-template <typename RawT, int VEC, bool MX6>
+template <typename RawT, int VEC, bool MX6, bool FRAG>
 __global__ __launch_bounds__(QA_THREADS) void quant_int4_kernel(
     const RawT* __restrict__ X, int K, int Kp, float eps, u32* __restrict__ q_out,
-    float* __restrict__ scale_out, int32_t* __restrict__ rowsum_out, int stat) {
+    float* __restrict__ scale_out, int32_t* __restrict__ rowsum_out, int stat, int frag_M) {
   extern __shared__ __align__(16) unsigned char qa_smem[];
   RawT* row = reinterpret_cast<RawT*>(qa_smem);
   __shared__ double red[QA_WAVES];
@@ -152,7 +152,8 @@ __global__ __launch_bounds__(QA_THREADS) void quant_int4_kernel(
 #pragma unroll
     for (int b = 0; b < 4; ++b)
       word |= (((u32)q[b] & 15u) | (((u32)q[4 + b] & 15u) << 4)) << (8 * b);
-    out[w] = word;
+    if constexpr (FRAG) q_out[bl_frag_word4(m, bl_frag_rows(m, frag_M), Kp, w >> 1) + (w & 1)] = word;
+    else out[w] = word;
   }
   if (rowsum_out) {
     sum = bl_wave_sum_i32(sum);
@@ -519,7 +520,7 @@ __global__ __launch_bounds__(NT) void quant_topk_int8_kernel(
 template <int NV>
 __global__ __launch_bounds__(64) void quant_topk_int8_f32_wave_kernel(
     const u32* __restrict__ X, int K, int Kp, int topk, float eps, u32* __restrict__ q_out,
-    float* __restrict__ scale_out, int32_t* __restrict__ rowsum_out) {
+    float* __restrict__ scale_out, int32_t* __restrict__ rowsum_out, int frag_M) {
   const int64_t m = blockIdx.x;
   const int lane = threadIdx.x;
   const int n_chunks = Kp / 256;                          // <= NV by dispatch
@@ -591,7 +592,8 @@ __global__ __launch_bounds__(64) void quant_topk_int8_f32_wave_kernel(
 
   const uint64_t lt_mask = (1ull << lane) - 1ull;
   int sum = 0, eq_base = 0;
-  u32* out = q_out + m * (int64_t)(Kp / 4);
+  const int R = frag_M ? bl_frag_rows(m, frag_M) : 1;
+  u32* out = q_out + (frag_M ? bl_frag_word8(m, R, Kp, lane) : m * (int64_t)(Kp / 4) + lane);
 #pragma unroll
   for (int c = 0; c < NV; ++c) {
     if (c >= n_chunks) break;
@@ -627,7 +629,7 @@ __global__ __launch_bounds__(64) void quant_topk_int8_f32_wave_kernel(
       sum += q;
       word |= ((u32)q & 255u) << (8 * j);
     }
-    out[c * 64 + lane] = word;
+    out[c * 64 * R] = word;
   }
   if (rowsum_out) {
     sum = bl_wave_sum_i32(sum);
@@ -1080,10 +1082,40 @@ __global__ __launch_bounds__(QA_THREADS) void unpack_act_kernel(const u32* __res
 }
 
 // ---------------------------------------------------------------- dispatch
+// Weights that the quantizer's launch touches (BlTouch): what streams in while the tokens' chain of latencies runs anyway.  The
+// Top_k kernel takes 4 to 6 us, the INT4 kernel 2.4, of which an empty launch is 1.5; beyond that a touched byte costs its time
+// here and the product gains less (it is then bound by its own loads).  Linear, weights from HBM, without / with, us:
+//   Top_k  32 x 4096 x 11008 (11 MB) 11.8 / 9.9, 57 x 8192 x 12288 (25 MB) 17.1 / 16.2, 32 x 2048 x 2048 (1 MB) 8.75 / 8.5
+//   INT4   32 x 6144 x 2048 (3 MB) 6.8 / 6.4, 32 x 9600 x 3200 (8 MB) 8.6 / 8.2, 32 x 12288 x 3072 (9 MB) 8.8 / 8.8, 32 x 12288 x
+//          4096 (13 MB) 8.9 / 9.1; gate and up 32 x 2 x 5460 x 2048 (6 MB) 7.6 / 7.3, 2 x 11008 x 4096 (23 MB) 11.6 / 12.4, 2 x
+//          2700 x 1024 (1.4 MB) 6.6 / 6.7
+static bool qa_touch_pays(bool a4, size_t bytes) {
+  const size_t mb = (size_t)1 << 20;
+  return a4 ? bytes >= 2 * mb && bytes <= 8 * mb : bytes >= mb && bytes <= 32 * mb;
+}
+
+static BlTouch qa_touch(bool a4, int threads, const void* W, const void* W2, size_t w_bytes) {
+  BlTouch t = {{(const unsigned char*)W, (const unsigned char*)W2}, W2 ? 2 : 1, 0, 0};
+  if (qa_touch_pays(a4, w_bytes * t.n_mat)) {
+    t.lines = (int)(w_bytes >> 7);
+    t.blocks = (int)min((int64_t)512, bl_round_up(((int64_t)t.lines * t.n_mat + threads - 1) / threads, 8));
+  }
+  return t;
+}
+
+static bool qa_f32_wave_ok(int K, int Kp) { return K % 4 == 0 && Kp <= 1024; }
+static int qa_run_topk_f32_wave(const u32* x, int64_t M, int K, int Kp, int topk, float eps, void* q, void* scale, int32_t* rowsum,
+                                int frag_M, hipStream_t s) {
+  if (Kp <= 512) quant_topk_int8_f32_wave_kernel<2><<<(unsigned)M, 64, 0, s>>>(x, K, Kp, topk, eps, (u32*)q, (float*)scale, rowsum, frag_M);
+  else quant_topk_int8_f32_wave_kernel<4><<<(unsigned)M, 64, 0, s>>>(x, K, Kp, topk, eps, (u32*)q, (float*)scale, rowsum, frag_M);
+  BL_HIP_CHECK_LAUNCH();
+  return BL_OK;
+}
+
 template <typename RawT, int VEC>
 static int qa_run_row_kernels(const RawT* X, int64_t M, int K, int Kp, bl_act_mode mode, int topk,
                               float eps, void* q, void* scale, int32_t* rowsum, int32_t* sel,
-                              hipStream_t s) {
+                              hipStream_t s, int frag_M = 0) {
   const size_t smem = (size_t)Kp * sizeof(RawT);
   if (mode == BL_ACT_INT4_ABSMEAN || mode == BL_ACT_INT4_ABSMEAN_MX6 || mode == BL_ACT_INT4_ABSMEAN2 ||
       mode == BL_ACT_INT4_ABSMAX) {
@@ -1091,11 +1123,14 @@ static int qa_run_row_kernels(const RawT* X, int64_t M, int K, int Kp, bl_act_mo
     // (the limit is raised once, to the widest row the library accepts)
     constexpr int max_smem = BL_MAX_K * (int)sizeof(RawT);
     if (mode == BL_ACT_INT4_ABSMEAN_MX6) {
-      BL_SET_MAX_LDS_ONCE((quant_int4_kernel<RawT, VEC, true>), max_smem);
-      quant_int4_kernel<RawT, VEC, true><<<(unsigned)M, QA_THREADS, smem, s>>>(X, K, Kp, eps, (u32*)q, (float*)scale, rowsum, stat);
+      BL_SET_MAX_LDS_ONCE((quant_int4_kernel<RawT, VEC, true, false>), max_smem);
+      quant_int4_kernel<RawT, VEC, true, false><<<(unsigned)M, QA_THREADS, smem, s>>>(X, K, Kp, eps, (u32*)q, (float*)scale, rowsum, stat, 0);
+    } else if (frag_M) {
+      BL_SET_MAX_LDS_ONCE((quant_int4_kernel<RawT, VEC, false, true>), max_smem);
+      quant_int4_kernel<RawT, VEC, false, true><<<(unsigned)M, QA_THREADS, smem, s>>>(X, K, Kp, eps, (u32*)q, (float*)scale, rowsum, stat, frag_M);
     } else {
-      BL_SET_MAX_LDS_ONCE((quant_int4_kernel<RawT, VEC, false>), max_smem);
-      quant_int4_kernel<RawT, VEC, false><<<(unsigned)M, QA_THREADS, smem, s>>>(X, K, Kp, eps, (u32*)q, (float*)scale, rowsum, stat);
+      BL_SET_MAX_LDS_ONCE((quant_int4_kernel<RawT, VEC, false, false>), max_smem);
+      quant_int4_kernel<RawT, VEC, false, false><<<(unsigned)M, QA_THREADS, smem, s>>>(X, K, Kp, eps, (u32*)q, (float*)scale, rowsum, stat, 0);
     }
   } else if (M <= 64) {
     constexpr int max_smem = BL_MAX_K * (int)sizeof(RawT);
@@ -1212,59 +1247,50 @@ int bl_launch_quantize(const void* X, bl_dtype dt, int64_t M, int64_t K64, bl_ac
   }
   const u32* x = (const u32*)X;
   // (index lists stay with the general kernel, which numbers the kept channels)
-  if (mode == BL_ACT_TOPK_INT8_ABSMAX && K % 4 == 0 && Kp <= 1024 && sel_idx == nullptr) {
-    if (Kp <= 512) quant_topk_int8_f32_wave_kernel<2><<<(unsigned)M, 64, 0, s>>>(x, K, Kp, (int)topk, eps, (u32*)q, (float*)scale, rowsum);
-    else quant_topk_int8_f32_wave_kernel<4><<<(unsigned)M, 64, 0, s>>>(x, K, Kp, (int)topk, eps, (u32*)q, (float*)scale, rowsum);
-    BL_HIP_CHECK_LAUNCH();
-    return BL_OK;
-  }
+  if (mode == BL_ACT_TOPK_INT8_ABSMAX && qa_f32_wave_ok(K, Kp) && sel_idx == nullptr)
+    return qa_run_topk_f32_wave(x, M, K, Kp, (int)topk, eps, q, scale, rowsum, 0, s);
   if (K % 4 == 0) return qa_run_row_kernels<u32, 4>(x, M, K, Kp, mode, (int)topk, eps, q, scale, rowsum, sel_idx, s);
   return qa_run_row_kernels<u32, 1>(x, M, K, Kp, mode, (int)topk, eps, q, scale, rowsum, sel_idx, s);
 }
 
-// Weights that the quantizer's launch touches (BlTouch): what streams in while the tokens' chain of latencies runs anyway.  The
-// Top_k kernel takes 4 to 6 us, the INT4 kernel 2.4, of which an empty launch is 1.5; beyond that a touched byte costs its time
-// here and the product gains less (it is then bound by its own loads).  Linear, weights from HBM, without / with, us:
-//   Top_k  32 x 4096 x 11008 (11 MB) 11.8 / 9.9, 57 x 8192 x 12288 (25 MB) 17.1 / 16.2, 32 x 2048 x 2048 (1 MB) 8.75 / 8.5
-//   INT4   32 x 6144 x 2048 (3 MB) 6.8 / 6.4, 32 x 9600 x 3200 (8 MB) 8.6 / 8.2, 32 x 12288 x 3072 (9 MB) 8.8 / 8.8, 32 x 12288 x
-//          4096 (13 MB) 8.9 / 9.1; gate and up 32 x 2 x 5460 x 2048 (6 MB) 7.6 / 7.3, 2 x 11008 x 4096 (23 MB) 11.6 / 12.4, 2 x
-//          2700 x 1024 (1.4 MB) 6.6 / 6.7
-static bool qa_touch_pays(bool a4, size_t bytes) {
-  const size_t mb = (size_t)1 << 20;
-  return a4 ? bytes >= 2 * mb && bytes <= 8 * mb : bytes >= mb && bytes <= 32 * mb;
-}
-
-// Fragment order comes from the register kernels only.
+// Codes in fragment order: INT4 from the register kernel or the general one (K up to 16384), Top_k from the register kernels.
 bool bl_quantize_frag_ok(bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode) {
   const int64_t Kp = bl_round_up(K, BL_KPAD);
-  if (dt != BL_BF16 || M > 256) return false;
-  if (mode == BL_ACT_INT4_ABSMEAN) return K % 8 == 0 && Kp <= 16384;
-  return mode == BL_ACT_TOPK_INT8_ABSMAX && K % 4 == 0 && Kp <= 12288;
+  if (M > 256) return false;
+  // INT4 rows of the general kernel (float32, or K % 8 != 0) gain from it with 16 tokens or 4096 channels, and lose or are level
+  // with few long ones, whose own product streams the weights.  Float32, row order / fragment order, whole linear, us:
+  // 16 x 512 x 8192 13.5 / 12.9, 16 x 4096 x 11008 17.3 / 16.4, 32 x 4096 x 11008 22.9 / 17.2, 1 x 4096 x 4096 8.9 / 8.5; 1 x 512 x
+  // 8192 11.4 / 11.9, 1 x 4096 x 16000 20.2 / 20.8, 8 x 4096 x 11008 15.8 / 16.4; 12 tokens 4096 x 11008 16.3 / 16.5, 512 x 8192
+  // 13.0 / 12.8
+  const bool general = dt != BL_BF16 || K % 8 != 0;
+  if (mode == BL_ACT_INT4_ABSMEAN) return Kp <= 16384 && (!general || M > 8 || Kp <= 4096);
+  if (mode != BL_ACT_TOPK_INT8_ABSMAX) return false;
+  return dt == BL_BF16 ? K % 4 == 0 && Kp <= 12288 : qa_f32_wave_ok((int)K, (int)Kp);
 }
 
-int bl_launch_quantize_frag(const void* X, int64_t M, int64_t K64, bl_act_mode mode, int64_t topk, float eps, void* q,
-                            float* scale, const void* W, const void* W2, size_t w_bytes, hipStream_t s) {
-  if (!bl_quantize_frag_ok(BL_BF16, M, K64, mode)) return BL_EUNSUPPORTED;
-  const int K = (int)K64, Kp = (int)bl_round_up(K64, BL_KPAD);
-  const bool a4 = mode == BL_ACT_INT4_ABSMEAN;
-  const int threads = a4 ? QA_THREADS : 512;
-  BlTouch touch = {{(const unsigned char*)W, (const unsigned char*)W2}, W2 ? 2 : 1, 0, 0};
-  if (qa_touch_pays(a4, w_bytes * touch.n_mat)) {
-    touch.lines = (int)(w_bytes >> 7);
-    touch.blocks = (int)min((int64_t)512, bl_round_up(((int64_t)touch.lines * touch.n_mat + threads - 1) / threads, 8));
+int bl_launch_quantize_frag(const void* X, bl_dtype dt, int64_t M, int64_t K64, bl_act_mode mode, int64_t topk, float eps,
+                            void* q, float* scale, const void* W, const void* W2, size_t w_bytes, hipStream_t s) {
+  if (!bl_quantize_frag_ok(dt, M, K64, mode)) return BL_EUNSUPPORTED;
+  const int K = (int)K64, Kp = (int)bl_round_up(K64, BL_KPAD), frag_M = (int)M;
+  if (mode == BL_ACT_TOPK_INT8_ABSMAX) {
+    if (dt == BL_F32) return qa_run_topk_f32_wave((const u32*)X, M, K, Kp, (int)topk, eps, q, scale, nullptr, frag_M, s);
+    qa_run_topk_regs8(X, M, K, Kp, (int)topk, eps, q, scale, frag_M, qa_touch(false, 512, W, W2, w_bytes), s);
+    BL_HIP_CHECK_LAUNCH();
+    return BL_OK;
   }
-  if (a4) {
-    const int nvv = (Kp / 16 + QA_THREADS - 1) / QA_THREADS;
+#define QA_ROW(T, VEC) qa_run_row_kernels<T, VEC>((const T*)X, M, K, Kp, mode, 0, eps, q, scale, nullptr, nullptr, s, frag_M)
+  if (dt == BL_F32) return K % 4 == 0 ? QA_ROW(u32, 4) : QA_ROW(u32, 1);
+  if (K % 8 != 0) return K % 4 == 0 ? QA_ROW(uint16_t, 4) : QA_ROW(uint16_t, 1);
+#undef QA_ROW
+  const BlTouch touch = qa_touch(true, QA_THREADS, W, W2, w_bytes);
+  const int nvv = (Kp / 16 + QA_THREADS - 1) / QA_THREADS;
 #define QA_I4F(NVV)                                                                                                 \
   quant_int4_regs_kernel<false, NVV><<<(unsigned)(M + touch.blocks), QA_THREADS, 0, s>>>((const uint16_t*)X, M, K, Kp, \
                                                                                           eps, (u32*)q, scale, nullptr, 0, 1, touch)
-    if (nvv <= 1) QA_I4F(1);
-    else if (nvv <= 2) QA_I4F(2);
-    else QA_I4F(4);
+  if (nvv <= 1) QA_I4F(1);
+  else if (nvv <= 2) QA_I4F(2);
+  else QA_I4F(4);
 #undef QA_I4F
-  } else {
-    qa_run_topk_regs8(X, M, K, Kp, (int)topk, eps, q, scale, (int)M, touch, s);
-  }
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
 }

@@ -28,13 +28,19 @@ CASES = [(33, 5269, 200),                         # 1x2 1x2 1x4
          (9, 2049, 2312), (64, 4099, 2056), (40, 24600, 264), (57, 17000, 520), (250, 6300, 300)]
 
 
-@pytest.mark.parametrize("M,N,K", CASES)
-def test_tiles(M, N, K):
+# float32 tokens and rows of any length: the general INT4 quantizer, the one-wave Top_k quantizer of up to 512 and 1024 channels
+OTHER = [(16, 512, 256, torch.float32), (64, 1000, 1000, torch.float32), (33, 130, 1021, torch.float32), (1, 16, 4, torch.float32),
+         (47, 700, 512, torch.float32), (17, 70, 516, torch.float32), (200, 300, 4097, torch.float32), (17, 70, 300, BF16),
+         (9, 100, 262, BF16), (40, 333, 4099, BF16)]
+
+
+@pytest.mark.parametrize("M,N,K,dtype", [c + (BF16,) for c in CASES] + OTHER)
+def test_tiles(M, N, K, dtype):
     """Both linears and the gate/up front: bfloat16 and float32 outputs and accumulators, bit for bit (integer sums below 2^24
     are exact in the float32 reference; the rescale is the same two float32 products)."""
-    print("[case] direct tiles M=%d N=%d K=%d" % (M, N, K), flush=True)
+    print("[case] direct tiles M=%d N=%d K=%d %s" % (M, N, K, dtype), flush=True)
     g = torch.Generator(device="cuda").manual_seed(M + N)
-    X = torch.randn((M, K), generator=g, device="cuda").to(BF16)
+    X = torch.randn((M, K), generator=g, device="cuda").to(dtype)
     W = 0.02 * torch.randn((N, K), generator=g, device="cuda")
     Wu = 0.02 * torch.randn((N, K), generator=g, device="cuda")
     p, a = B.pack_ternary(W)
