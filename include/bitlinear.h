@@ -206,7 +206,7 @@ int quantize_act(const void* X, bl_dtype x_dtype, int64_t M, int64_t K, bl_act_m
  *              packed activations and their scales between the two kernels
  * Kernel choice (BL_W_GEMM) is by M: up to BL_DECODE_MAX_M tokens the weights are streamed once
  * by a skinny (decode) kernel, with the quantizer inside the same launch for up to 8 bfloat16
- * tokens (INT4) or one (Top_k + INT8); above that the tiled MFMA GEMM runs.  Up to 256 bfloat16
+ * tokens (INT4) or one (Top_k + INT8); above that the tiled MFMA GEMM runs.  Up to 256
  * tokens the codes in the workspace are in the order of the product's loads (no public form).  The
  * block-float forms always take the tiled GEMM.
  *
@@ -269,7 +269,7 @@ int bitlinear_gemm(const void* q, const void* scale, bl_act_mode mode, int64_t M
  * Up to 8 bfloat16 tokens with BL_W_GEMM weights (K % 8 == 0, K <= 8192) run as one launch that
  * streams both matrices once and uses no workspace (it may then be NULL); up to 64 tokens with
  * BL_W_GEMM weights and only H asked for run the quantizer and then one launch over both matrices
- * (bfloat16: up to 256 tokens, any K; otherwise K up to 4096 beyond 32 tokens, 8192 beyond 16).  With block-float weights
+ * (up to 256 tokens where M and N are not both large; else K up to 4096 beyond 32 tokens, 8192 beyond 16).  With block-float weights
  * (BL_W_MX4 / BL_W_MX2) and only H asked for, the quantizer is followed by one GEMM over both
  * matrices whose epilogue applies eq. 5 to its accumulators: G and U never reach memory.  Other
  * cases run the quantizer, the two products and the combine as separate kernels. */

@@ -534,14 +534,14 @@ extern "C" int bitlinear_a4_gate_up(const void* X, bl_dtype x_dtype, int64_t M, 
     if (rc) return rc;
     return bl_launch_gemm_direct_glu(codes, (const float*)scales, M, K, W_gate, alpha_gate, W_up, alpha_up, N, H, s);
   }
-  // 9 to 16 tokens (or tokens that are not bfloat16), 2-bit tile weights, only H wanted: the stand-alone
-  // quantizer, then both products and eq. 5 in one launch of the streaming kernel
+  // up to 16 tokens that do not take fragment order (few long rows of the general quantizer, more outputs than its tiles are
+  // for): the stand-alone quantizer, then both products and eq. 5 in one launch of the streaming kernel
   if (layout == BL_W_GEMM && H && !G && !U && bl_gemv_stream_glu_codes_ok(M, N, K)) {
     rc = bl_launch_quantize(X, x_dtype, M, K, mode, 0, eps, codes, scales, nullptr, nullptr, s);
     if (rc) return rc;
     return bl_launch_gemv_stream_glu_codes(codes, (const float*)scales, M, K, W_gate, alpha_gate, W_up, alpha_up, N, H, s);
   }
-  // 17 to 64 tokens, 2-bit tile weights, only H wanted: both products and eq. 5 in one launch
+  // likewise 17 to 64 tokens: both products and eq. 5 in one launch
   if (layout == BL_W_GEMM && H && !G && !U && bl_gemm_decode_glu_ok(M, N, K)) {
     rc = bl_launch_quantize(X, x_dtype, M, K, mode, 0, eps, codes, scales, nullptr, nullptr, s);
     if (rc) return rc;

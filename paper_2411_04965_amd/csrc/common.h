@@ -233,16 +233,8 @@ int bl_launch_gemm_mid_mx_glu(const void* q, const float* scale, int64_t M, int6
                               const void* Wu, const float* au, int64_t N, void* H, hipStream_t s);
 int bl_launch_gemm_mid_a4_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,
                               const void* Wu, const float* au, int64_t N, void* H, hipStream_t s);
-bool bl_gemv_a4_fused_ok(int64_t M, int64_t N, int64_t K);
 int bl_launch_up_gated(const void* X, int64_t M, int64_t K, float eps, const void* Wr, const float* alpha,
                        int64_t N, const void* G, bl_dtype gdt, void* H, hipStream_t s);
-bool bl_gemv_a8_fused_ok(int64_t M, int64_t N, int64_t K);
-int bl_launch_gemv_a8_fused(const void* X, int64_t K, int64_t topk, float eps, const void* Wp,
-                            const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out,
-                            hipStream_t s);
-int bl_launch_gemv_a4_fused(const void* X, int64_t M, int64_t K, float eps, const void* Wp,
-                            const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out,
-                            hipStream_t s);
 // one persistent launch for up to 16 tokens (gemv_stream.hip)
 bool bl_gemv_stream_ok(int64_t M, int64_t N, int64_t K, bool quant_inside);
 bool bl_gemv_stream_pair_ok(int64_t M, int64_t N, int64_t K, bool glu);

@@ -178,7 +178,7 @@ __global__ __launch_bounds__(GD_THREADS) void gemm_decode_kernel(
   }
 }
 
-// One token (the kernel takes up to 4), INT4 activations: eq. 7 inside the same launch.  Every block quantizes the
+// A few tokens, INT4 activations: eq. 7 inside the up projection's launch below.  Every block quantizes the
 // tokens itself (their rows are a few KB and come out of the cache; the statistics and the codes
 // take a few hundred instructions per thread), which saves the quantizer's launch: at these sizes a
 // launch costs as much as streaming the weights.  The arithmetic is that of the stand-alone
@@ -253,73 +253,6 @@ __device__ __forceinline__ void gf_quantize_rows(const uint16_t* __restrict__ X,
   }
   __syncthreads();
 
-}
-
-__global__ __launch_bounds__(GD_THREADS) void gemv_a4_fused_kernel(
-    const uint16_t* __restrict__ X, int M, int K, int Kp, float eps,
-    const unsigned char* __restrict__ Wp, const float* __restrict__ alpha_p, int N,
-    void* __restrict__ Y, int y_bf16, int32_t* __restrict__ acc_out) {
-  extern __shared__ __align__(16) unsigned char gf_smem[];
-  unsigned char* codes = gf_smem;                                  // [M][Kp] int8
-  __shared__ __align__(16) v4i wsum[GD_THREADS / 64][64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int li = lane & 15, lg = lane >> 4;
-  const int KT = Kp >> 8;
-  const int nt = blockIdx.x;                     // grid = tiles of 16 outputs
-  const unsigned char* w_src = Wp + (size_t)nt * KT * 1024 + lane * 16;
-
-  // weights first: tiles wave, wave + 4, ... in groups of 4 (the next group is fetched while one
-  // is multiplied)
-  constexpr int UNR = 4;
-  uint4 wr[UNR];
-  auto load_group = [&](int t) {
-#pragma unroll
-    for (int u = 0; u < UNR; ++u)
-      wr[u] = *reinterpret_cast<const uint4*>(w_src + (size_t)min(t + 4 * u, KT - 1) * 1024);
-  };
-  int t = wave;
-  if (t < KT) load_group(t);
-
-  float dq[4];
-  gf_quantize_rows(X, M, K, Kp, eps, codes, dq);
-
-  // lane (li, lg) holds, for token li, the 64 channels lg * 64 .. of a tile, 16 per MFMA step
-  v4i acc = (v4i){0, 0, 0, 0};
-  const unsigned char* xrow = codes + (size_t)min(li, M - 1) * Kp + lg * 64;
-  while (t < KT) {
-    uint4 wc[UNR];
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) wc[u] = wr[u];
-    const int tn = t + 4 * UNR;
-    if (tn < KT) load_group(tn);
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int tt = t + 4 * u;
-      if (tt < KT) {                             // wave-uniform
-#pragma unroll
-        for (int t4 = 0; t4 < 4; ++t4) {
-          v4i xo = (v4i){0, 0, 0, 0};
-          if (li < M) xo = *reinterpret_cast<const v4i*>(xrow + (size_t)tt * 256 + t4 * 16);
-          const u32 w = t4 == 0 ? wc[u].x : t4 == 1 ? wc[u].y : t4 == 2 ? wc[u].z : wc[u].w;
-          const v4i wo = (v4i){(int)((w << 6) & 0xC0C0C0C0u), (int)((w << 4) & 0xC0C0C0C0u),
-                               (int)((w << 2) & 0xC0C0C0C0u), (int)(w & 0xC0C0C0C0u)};
-          acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wo, xo, acc, 0, 0, 0);
-        }
-      }
-    }
-    t = tn;
-  }
-
-  // add the four waves' sums; wave 0 rescales and stores
-  wsum[wave][lane] = acc;
-  __syncthreads();
-  if (wave != 0) return;
-  v4i sum = wsum[0][lane] + wsum[1][lane] + wsum[2][lane] + wsum[3][lane];
-  const int m = li, n = nt * 16 + 4 * lg;
-  if (m >= M || n >= N) return;
-  const int iv[4] = {sum[0] >> 6, sum[1] >> 6, sum[2] >> 6, sum[3] >> 6};
-  const float d = m == 0 ? dq[0] : m == 1 ? dq[1] : m == 2 ? dq[2] : dq[3];
-  gd_store4(Y, y_bf16, acc_out, (size_t)m * N + n, n, N, iv, d, alpha_p[0]);
 }
 
 // Gate-first up projection for a few tokens: U = INT4 linear of X with row-addressable weights
@@ -434,71 +367,7 @@ __global__ __launch_bounds__(GD_THREADS) void up_gated_kernel(
   }
 }
 
-// One token, top-K + INT8 activations: eq. 1 and eq. 3 inside the same launch, for the same reason.
-// Every block selects and quantizes the token itself with the four-wave register kernel's body
-// (topk_regs.h) while its first weight tiles are on their way, and leaves the int8 codes in LDS.
-template <int CPW>
-__global__ __launch_bounds__(GD_THREADS) void gemv_a8_fused_kernel(
-    const uint16_t* __restrict__ X, int K, int Kp, int topk, float eps,
-    const unsigned char* __restrict__ Wp, const float* __restrict__ alpha_p, int N,
-    void* __restrict__ Y, int y_bf16, int32_t* __restrict__ acc_out) {
-  extern __shared__ __align__(16) unsigned char gf_smem[];         // [Kp] int8
-  __shared__ float dq;
-  __shared__ __align__(16) v4i wsum[GD_THREADS / 64][64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int li = lane & 15, lg = lane >> 4;
-  const int KT = Kp >> 8;
-  const int nt = blockIdx.x;                     // grid = tiles of 16 outputs
-  const unsigned char* w_src = Wp + (size_t)nt * KT * 1024 + lane * 16;
-  constexpr int UNR = 4;
-  uint4 wr[UNR];
-  auto load_group = [&](int t) {
-#pragma unroll
-    for (int u = 0; u < UNR; ++u)
-      wr[u] = *reinterpret_cast<const uint4*>(w_src + (size_t)min(t + 4 * u, KT - 1) * 1024);
-  };
-  int t = wave;
-  if (t < KT) load_group(t);
-
-  qa_topk_row_regs<CPW>(X, nullptr, K, Kp, topk, eps, reinterpret_cast<u32*>(gf_smem), &dq, nullptr);
-  __syncthreads();
-
-  v4i acc = (v4i){0, 0, 0, 0};
-  const unsigned char* xrow = gf_smem + lg * 64;
-  while (t < KT) {
-    uint4 wc[UNR];
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) wc[u] = wr[u];
-    const int tn = t + 4 * UNR;
-    if (tn < KT) load_group(tn);
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int tt = t + 4 * u;
-      if (tt < KT) {                             // wave-uniform
-#pragma unroll
-        for (int t4 = 0; t4 < 4; ++t4) {
-          v4i xo = (v4i){0, 0, 0, 0};
-          if (li == 0) xo = *reinterpret_cast<const v4i*>(xrow + (size_t)tt * 256 + t4 * 16);
-          const u32 w = t4 == 0 ? wc[u].x : t4 == 1 ? wc[u].y : t4 == 2 ? wc[u].z : wc[u].w;
-          const v4i wo = (v4i){(int)((w << 6) & 0xC0C0C0C0u), (int)((w << 4) & 0xC0C0C0C0u),
-                               (int)((w << 2) & 0xC0C0C0C0u), (int)(w & 0xC0C0C0C0u)};
-          acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wo, xo, acc, 0, 0, 0);
-        }
-      }
-    }
-    t = tn;
-  }
-  wsum[wave][lane] = acc;
-  __syncthreads();
-  if (wave != 0) return;
-  v4i sum = wsum[0][lane] + wsum[1][lane] + wsum[2][lane] + wsum[3][lane];
-  const int n = nt * 16 + 4 * lg;
-  if (li != 0 || n >= N) return;
-  const int iv[4] = {sum[0] >> 6, sum[1] >> 6, sum[2] >> 6, sum[3] >> 6};
-  gd_store4(Y, y_bf16, acc_out, (size_t)n, n, N, iv, dq, alpha_p[0]);
-}
-
-// Up to 16 tokens with too few output tiles for the kernel above (written for any number of token
+// Up to 16 tokens with too few output tiles for gemm_decode_kernel (written for any number of token
 // tiles): block = 4 waves = 64 outputs, every wave owns one tile of 16 outputs and walks the block's whole K range (a
 // slice of K when the grid would otherwise be small), so there is no reduction inside the block.
 // The tokens' codes of one K tile (M rows of 128 or 256 bytes, far apart in memory) are fetched
@@ -1046,29 +915,6 @@ int bl_launch_gemm_decode_glu(const void* q, const float* scale, int64_t M, int6
   return bl_launch_gemm_mid_a4_glu(q, scale, M, K, Wg, ag, Wu, au, N, H, s);
 }
 
-// The fused INT4 linear is used for one bfloat16 token when the one-tile-per-block kernel would be
-// (enough output tiles) and the row is 16-byte aligned and at most 8192 channels long.  (The kernel
-// takes up to 4 tokens, but every block quantizes every token: measured per projection at 7B width,
-// HIP-graph replays, fused against two launches: 7.6 / 8.9 us at one token, 9.2 / 9.1 at two,
-// 12.0 / 9.1 at four.)
-bool bl_gemv_a4_fused_ok(int64_t M, int64_t N, int64_t K) {
-  const int64_t Kp = bl_round_up(K, BL_KPAD);
-  return M == 1 && gd_single_tile((int)M, (int)N) && K % 8 == 0 && Kp <= 8 * GD_THREADS * GF_NV;
-}
-
-int bl_launch_gemv_a4_fused(const void* X, int64_t M, int64_t K, float eps, const void* Wp,
-                            const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out,
-                            hipStream_t s) {
-  if (!bl_gemv_a4_fused_ok(M, N, K)) return BL_EUNSUPPORTED;
-  const int Kp = (int)bl_round_up(K, BL_KPAD);
-  const size_t smem = (size_t)M * Kp;            // <= 32 KB
-  gemv_a4_fused_kernel<<<(unsigned)((N + 15) / 16), GD_THREADS, smem, s>>>(
-      (const uint16_t*)X, (int)M, (int)K, Kp, eps, (const unsigned char*)Wp, alpha, (int)N, Y,
-      ydt == BL_BF16 ? 1 : 0, acc_out);
-  BL_HIP_CHECK_LAUNCH();
-  return BL_OK;
-}
-
 int bl_launch_up_gated(const void* X, int64_t M, int64_t K, float eps, const void* Wr, const float* alpha,
                        int64_t N, const void* G, bl_dtype gdt, void* H, hipStream_t s) {
   const int Kp = (int)bl_round_up(K, BL_KPAD);
@@ -1093,31 +939,6 @@ int bl_launch_up_gated(const void* X, int64_t M, int64_t K, float eps, const voi
     else GU_CALL(2, 2);                          // (M * Kp <= 16384: at most 2 tokens here)
   }
 #undef GU_CALL
-  BL_HIP_CHECK_LAUNCH();
-  return BL_OK;
-}
-
-// The fused top-K + INT8 linear: one bfloat16 token whose keys fit the register kernel, enough
-// output tiles for the one-tile-per-block kernel.
-bool bl_gemv_a8_fused_ok(int64_t M, int64_t N, int64_t K) {
-  return M == 1 && gd_single_tile(1, (int)N) && K % 4 == 0 && bl_round_up(K, BL_KPAD) <= 12288;
-}
-
-int bl_launch_gemv_a8_fused(const void* X, int64_t K, int64_t topk, float eps, const void* Wp,
-                            const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out,
-                            hipStream_t s) {
-  if (!bl_gemv_a8_fused_ok(1, N, K)) return BL_EUNSUPPORTED;
-  const int Kp = (int)bl_round_up(K, BL_KPAD);
-  const int cpw = (Kp / 256 + 3) / 4;
-  const unsigned grid = (unsigned)((N + 15) / 16);
-  const int ybf = ydt == BL_BF16 ? 1 : 0;
-#define GF_A8(CPW)                                                                                     \
-  gemv_a8_fused_kernel<CPW><<<grid, GD_THREADS, (size_t)Kp, s>>>(                                      \
-      (const uint16_t*)X, (int)K, Kp, (int)topk, eps, (const unsigned char*)Wp, alpha, (int)N, Y, ybf, acc_out)
-  if (cpw <= 4) GF_A8(4);
-  else if (cpw <= 8) GF_A8(8);
-  else GF_A8(12);
-#undef GF_A8
   BL_HIP_CHECK_LAUNCH();
   return BL_OK;
 }
