@@ -467,7 +467,9 @@ bool bl_gemm_mid_mx_ok(int64_t M, int64_t N, int64_t K, bool glu) {
   const double share = (double)(((M + 63) / 64) * ((n_cols + 255) / 256)) / cus;
   const double KT = (double)(bl_round_up(K, BL_KPAD) >> 8);
   const double small = 0.7 * (double)gm_turns(M, n_cols, 64, 256, cus) + 0.3 * share, large = (double)gm_turns(M, n_cols, 256, 256, cus);
-  if (glu) return small < 3.1 * large - (large > 1.0 ? 0.2 : 0.4);
+  // (at less than 7 % by this count the large ones stay: 1000 x 2 x 11008 x 4096 is 59.0 us large, 56.1 small, 2048 x 2 x 5460 x 2048 37.2 /
+  // 35.2, but the INT8 products after them slow down under the power limit and a layer takes 0.986 to 1.008, 0.990 to 1.024 of the speed)
+  if (glu) return small < 3.1 * large - 0.45;
   return small < (3.05 * large - 0.25) * (KT < 8.0 ? 0.6 + 0.05 * KT : 1.0);
 }
 
