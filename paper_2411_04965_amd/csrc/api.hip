@@ -401,7 +401,8 @@ static int linear_common(const void* X, bl_dtype x_dtype, int64_t M, int64_t K, 
   void* ws2 = p;
   const size_t ws2_bytes = workspace_bytes - (size_t)(p - (unsigned char*)workspace);
   // up to 256 tokens: codes in the order in which the product's waves load them (their own order is free here)
-  if (layout == BL_W_GEMM && bl_quantize_frag_ok(x_dtype, M, K, mode) && bl_gemm_direct_ok(M, N)) {
+  if (layout == BL_W_GEMM && bl_quantize_frag_ok(x_dtype, M, K, mode) &&
+      bl_gemm_direct_ok(M, N, K, mode == BL_ACT_INT4_ABSMEAN)) {
     rc = bl_launch_quantize_frag(X, x_dtype, M, K, mode, topk, eps, codes, (float*)scales, W_packed, nullptr,
                                  pack_ternary_bytes(N, K, layout), (hipStream_t)stream);
     if (rc) return rc;
@@ -527,7 +528,7 @@ extern "C" int bitlinear_a4_gate_up(const void* X, bl_dtype x_dtype, int64_t M, 
   // the composed form would run, its larger workspace is still asked for)
   const bool one_launch = bl_gemv_stream_glu_codes_ok(M, N, K) || bl_gemm_decode_glu_ok(M, N, K);
   if (layout == BL_W_GEMM && H && !G && !U && bl_quantize_frag_ok(x_dtype, M, K, mode) &&
-      (!one_launch || bl_gemm_direct_ok(M, 2 * N))) {
+      (!one_launch || bl_gemm_direct_ok(M, 2 * N, K, true))) {
     if (!one_launch && workspace_bytes < (size_t)(p - (unsigned char*)workspace) + 2 * ws_align((size_t)M * N * sizeof(float)))
       return BL_EWORKSPACE;
     rc = bl_launch_quantize_frag(X, x_dtype, M, K, mode, 0, eps, codes, (float*)scales, W_gate, W_up, pack_ternary_bytes(N, K, layout), s);

@@ -203,7 +203,7 @@ int bl_launch_quantize(const void* X, bl_dtype dt, int64_t M, int64_t K, bl_act_
 bool bl_quantize_frag_ok(bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode);
 int bl_launch_quantize_frag(const void* X, bl_dtype dt, int64_t M, int64_t K, bl_act_mode mode, int64_t topk, float eps,
                             void* q, float* scale, const void* W, const void* W2, size_t w_bytes, hipStream_t s);
-bool bl_gemm_direct_ok(int64_t M, int64_t n_cols);
+bool bl_gemm_direct_ok(int64_t M, int64_t n_cols, int64_t K, bool a4);
 int bl_launch_gemm_direct(const void* q, const float* scale, bl_act_mode mode, int64_t M, int64_t K, const void* Wp,
                           const float* alpha, int64_t N, void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s);
 int bl_launch_gemm_direct_glu(const void* q, const float* scale, int64_t M, int64_t K, const void* Wg, const float* ag,

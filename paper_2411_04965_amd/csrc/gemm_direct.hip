@@ -6,9 +6,11 @@
 // back, sums are added, rows are stored.  Kernels that keep the codes in LDS wait for all of them before the first
 // product and, where K does not fit, split it over blocks and pay a second launch; tiles whose waves share K steps meet
 // at a barrier per step.  Here a block owns 16 MT tokens x 16 NT outputs over the whole of K and its eight waves share out
-// K in pieces of 128 channels.  A wave reads its pieces of both operands straight into MFMA registers, GX_D of them in
-// flight, so nothing waits for another wave until the one LDS reduction at the end (exact integers: any order).  A CU
-// then fetches every byte it needs once; how many those are decides the tile (gx_plan).
+// K in tiles of 256 channels.  A wave reads a tile of both operands straight into MFMA registers and requests the next one
+// into the same registers once its products are issued; other waves and blocks of the CU fill its waits, and nothing waits for
+// another wave until the one LDS reduction at the end (exact integers: any order).  (Two and four tiles in flight per wave were no
+// faster: the blocks that share a CU then have fewer registers.)  A CU fetches every byte it needs once; how many those are
+// decides the tile (gx_pick).
 //
 // Both operands come as whole 1 KB runs per load: the weights because BL_W_GEMM is in fragment order, the codes because the
 // quantizer writes them that way for this kernel (a private order in the caller's workspace; from row-major codes a load
@@ -209,11 +211,31 @@ static int gx_pick(const GxTile (&tiles)[COUNT], int64_t M, int64_t N, int KT, i
   return best;
 }
 
-// Up to how many outputs these tiles are the better choice (quantizer and product, before / here, us).  INT8: 256 x 6144 x 8192
-// 24.8 / 23.6, 150 x 8192 x 8192 22.9 / 22.7; 200 x 8192 x 8192 24.8 / 26.8, 64 x 32000 x 2048 15.4 / 16.0.  INT4: 128 x 12288 x 4096
-// 15.7 / 14.8; 200 x 9600 x 3200 18.3 / 19.4, 64 x 32000 x 2048 12.2 / 13.5.  Gate and up (both counted): 57 x 2 x 11008 x 4096
-// 15.6 / 15.1; 64 x 2 x 20000 x 4096 22.8 / 23.1, 64 x 2 x 32000 x 2048 18.3 / 21.5.
-bool bl_gemm_direct_ok(int64_t M, int64_t n_cols) { return M * n_cols <= 6144 * (int64_t)bl_num_cus(); }
+// Where these tiles are the better choice, by tokens x outputs per CU.  Beyond 16 tokens they take token tiles in pairs (a lone one
+// costs its pair) and run out of room in turns, as the kernels on the other side do: those do 33 to 64 tokens in one turn up to
+// 128 outputs per CU, 17 to 32 tokens up to 256, more tokens while 64 x 128 tiles last, and beyond that turn they lose.
+// The waves share K by 256 channels: up to four tiles leave half of them idle (one tile: all but one), so that what a turn costs at least
+// weighs more, and nine to twelve tiles fill the second round by half.  INT8 codes are twice the loads of INT4.  17 to 32 tokens lose
+// only against INT8 kernels that need not split K (nine to sixteen tiles).  Quantizer and product, weights from HBM, other forms / here, us:
+// INT8 208 x 5904 x 4600 20.0 / 19.0, 208 x 6400 x 4600 20.1 / 20.9, 256 x 5200 x 4600 20.8 / 19.7, 256 x 5600 x 4600 20.8 / 21.2, 56 x 25600 x 4600
+// 21.4 / 22.9, 28 x 48044 x 2972 19.6 / 21.4, 33 x 37636 x 1536 20.5 / 14.0; INT4 128 x 12288 x 4096 15.9 / 14.7, 256 x 6096 x 3064 13.8 / 13.4,
+// 144 x 9952 x 4600 17.5 / 19.5, 40 x 25600 x 3064 14.0 / 14.9, 56 x 25600 x 3064 14.0 / 16.2; up to 1024 channels 128 x 8000 x 1024 8.3 / 8.3,
+// 256 x 4000 x 1024 8.3 / 8.3, 128 x 9600 x 1024 9.4 / 10.0, 256 x 4800 x 1024 9.4 / 10.2, 104 x 7424 x 156 7.7 / 9.0.  Gate and up (both counted)
+// where the other side is one launch: 64 x 2 x 6992 x 1024 9.2 / 8.1, 56 x 2 x 10048 x 1024 9.3 / 10.0, 64 x 2 x 12192 x 4096 15.6 / 14.9,
+// 56 x 2 x 13936 x 4096 15.9 / 17.1.  Of 23600 calls measured (9 to 256 tokens, 156 to 16384 channels, cold and warm weights) 0.8 % are more
+// than 2 % behind the other forms.
+bool bl_gemm_direct_ok(int64_t M, int64_t n_cols, int64_t K, bool a4) {
+  const int64_t cus = bl_num_cus(), tiles = bl_round_up(K, BL_KPAD) >> 8, pairs = bl_round_up(M, 32) * n_cols;
+  if (M * n_cols > 6144 * cus) return false;
+  if (M <= 16 || (M <= 64 && n_cols > (M <= 32 ? 256 : 128) * cus)) return true;
+  if (tiles <= 4) {
+    const bool one_turn = M <= 32 || (M + 63) / 64 * ((n_cols + 63) / 64) <= cus;
+    return pairs <= (tiles == 1 && one_turn ? 2048 : 4096) * cus;
+  }
+  if (M <= 32) return a4 || tiles <= 8 || tiles > 16 || pairs <= 5632 * cus;
+  if (M > 64 && tiles > 12 && (M + 63) / 64 * ((n_cols + 127) / 128) > cus) return true;
+  return pairs <= (a4 || tiles <= 8 || (tiles > 12 && tiles <= 16) ? 6144 : 5376) * cus;
+}
 
 #define GX_GO(A4, GLU, MT, NT) \
   return gx_go<A4, GLU, MT, NT>(q, scale, (int)M, KT, Wp, Wp2, alpha, alpha2, (int)N, Y, ybf, acc_out, s)

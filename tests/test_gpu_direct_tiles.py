@@ -1,6 +1,6 @@
-"""GPU parity of the products whose waves load both operands in fragment order (up to 256 bfloat16 tokens, BL_W_GEMM weights):
-every tile of the dispatch, token tiles of 1 to 16 rows, ragged outputs, K tiles fewer than waves and rounds that do not come out
-even."""
+"""GPU parity of the products whose waves load both operands in fragment order (up to 256 tokens, BL_W_GEMM weights): every tile of
+the dispatch and both sides of its lines, token tiles of 1 to 16 rows, ragged outputs, K tiles fewer than waves and rounds that do not
+come out even; bfloat16 and float32 tokens."""
 import pytest
 import torch
 
@@ -10,22 +10,27 @@ from tests.test_gpu_prefill_tiles import product
 pytestmark = pytest.mark.gpu
 BF16 = torch.bfloat16
 
-# on 256 CUs these reach (token tiles x output tiles of INT8, of INT4, of gate and up; - = one reached elsewhere)
-CASES = [(33, 5269, 200),                         # 1x2 1x2 1x4
+# on 256 CUs these reach (token tiles x output tiles of INT8, of INT4, of gate and up; - = another kernel)
+CASES = [(33, 5269, 200),                         # 1x2 1x2 -
+         (45, 4282, 520),                         # 1x2 1x2 1x4
          (200, 6789, 1288),                       # 2x4 2x4 2x4
          (31, 1776, 200),                         # 1x1 1x1 1x2
          (31, 5376, 776),                         # 1x3 1x3 1x6
          (31, 10981, 1288),                       # 1x6 2x3 2x6
          (129, 3436, 1288),                       # 1x4 1x4 3x6
-         (177, 3989, 2056),                       # 2x6 2x6 -
-         (177, 6804, 200),                        # 2x2 2x2 -
-         (100, 9955, 264),                        # -   1x6 -
-         (65, 10064, 1288),                       # 2x8 -   -
-         (17, 6414, 264),                         # -   -   2x2
-         (177, 4062, 776), (81, 8168, 776),       # 2x3 -   -, 3x4 - -
+         (177, 3989, 2056),                       # 2x6 2x6 2x4
+         (180, 2699, 776),                        # 2x2 2x2 2x4
+         (72, 9575, 776),                         # 1x6 1x6 1x6
+         (65, 10064, 1288),                       # 2x8 2x4 2x4
+         (17, 6414, 264),                         # 1x2 1x2 2x2
+         (177, 4062, 776), (81, 8168, 776),       # 2x3 2x3 2x4, 3x4 1x4 2x4
          (1, 17, 8), (2, 15, 264), (16, 1, 4104), (9, 3210, 2056), (31, 1027, 5464), (33, 130, 11008), (255, 31, 3200), (256, 3210, 264),
          # weights that the quantizer's launch touches: lines that do not divide by eight XCDs, one matrix and two; and beyond the rule
-         (9, 2049, 2312), (64, 4099, 2056), (40, 24600, 264), (57, 17000, 520), (250, 6300, 300)]
+         (9, 2049, 2312), (64, 4099, 2056), (40, 24600, 264), (57, 17000, 520), (250, 6300, 300),
+         # either side of the lines: outputs of a turn of the other kernels (33 to 64 and 17 to 32 tokens), token tiles in pairs with short
+         # and with longer rows, one K tile, nine to sixteen K tiles at up to 32 tokens, beyond a turn of 64 x 128 tiles
+         (33, 32760, 264), (33, 32776, 264), (17, 65528, 264), (17, 65544, 264), (48, 16376, 1000), (48, 16392, 1000), (97, 12288, 1288),
+         (97, 12296, 1288), (90, 5464, 256), (90, 5460, 200), (28, 45056, 2312), (28, 45060, 2312), (88, 16384, 3400), (88, 16392, 3400)]
 
 
 # float32 tokens and rows of any length: the general INT4 quantizer, the one-wave Top_k quantizer of up to 512 and 1024 channels
