@@ -453,24 +453,26 @@ static int64_t gm_turns(int64_t M, int64_t N, int bm, int bn, int64_t cus = bl_n
 // 140, 8192 x 3200 x 8640 174 against 180; on the other side 2048 x 4096 x 11008 100 against 71.
 bool bl_gemm_mid_ok(int64_t M, int64_t N) { return 7 * gm_turns(M, N, 256, 256) > 2 * gm_turns(M, N, 128, 128); }
 
-// Block-float codes: 64 x 256 tiles against 256 x 256.  A turn of the large ones takes 3.05 times as long (the first one 2.8) from
-// 2048 channels on, less below (a small tile's start and end weigh more; not so for gate and up, whose large tiles end slowly, and
-// which take 3.1 times as long, the first 2.9, at any K); where the small tiles do not fill their last turn, blocks
-// that share a CU finish sooner, which counts for 0.3 of it.  Product alone, large / small, us: 500 x 12288 x 4096 23.1 / 20.3,
-// 1500 x 12288 x 4096 60.4 / 50.0, 1000 x 12288 x 4096 33.8 / 34.9, 2048 x 12288 x 4096 62.0 / 64.9, 2048 x 9600 x 3200 51.4 / 47.9,
-// 4096 x 9600 x 3200 78.8 / 87.7, 1000 x 6144 x 8192 45.1 / 35.7, 1700 x 3072 x 1024 9.8 / 9.4, 3000 x 3072 x 1024 14.1 / 15.8; gate and up
-// 1000 x 2 x 8640 x 3200 50.6 / 42.2, 1500 x 2 x 11008 x 4096 89.3 / 84.9, 2048 x 2 x 11008 x 4096 95.3 / 105.4, 3000 x 2 x 5460 x 2048
-// 52.4 / 46.0, 3000 x 2 x 2700 x 1024 24.5 / 18.0, 2048 x 2 x 4000 x 1024 15.1 / 16.3.
+// Block-float codes: 64 x 256 tiles against 256 x 256, in turns of the small ones; where these do not fill their last turn, blocks
+// that share a CU finish sooner, which counts for 0.3 of it.  The lines lie where whole layers (qkv, o, gate and up, down in a row, about
+// 400 sizes of 90 to 10500 tokens, 1024 to 4096 channels) say so as well: the kernel that is the faster one alone may slow down what runs
+// after it, under the power limit.
+// One matrix: a turn of the large tiles is 3.05 small ones, the first one 2.8 from 2048 channels on, less below (a small tile's start and
+// end weigh more).  Product alone, large / small, us: 500 x 12288 x 4096 23.1 / 20.3, 1500 x 12288 x 4096 60.4 / 50.0, 1000 x 12288 x 4096
+// 33.8 / 34.9, 2048 x 12288 x 4096 62.0 / 64.9, 2048 x 9600 x 3200 51.4 / 47.9, 4096 x 9600 x 3200 78.8 / 87.7, 1700 x 3072 x 1024 9.8 / 9.4,
+// 3000 x 3072 x 1024 14.1 / 15.8; two layers: 6000 tokens, 1024 channels 268.8 / 259.1, 1600 tokens, 3200 channels 409.7 / 386.5, 900 tokens,
+// 4096 channels 348.4 / 348.2, 1850 tokens, 4096 channels 566.7 / 573.2.
+// Gate and up: 3.1 small turns, the first 2.65, at any length of rows (the large tiles end slowly).  Two layers, large / small, us:
+// 1106 tokens, 2944 channels, 2 x 7832 outputs 284.7 / 266.4, 1250 tokens, 2944 channels 290.1 / 273.8, 2400 tokens, 2560 channels 400.7 / 380.9;
+// 1000 tokens, 4096 channels 354.2 / 353.7, 2048 tokens, 4096 channels 574.9 / 608.3, 1600 tokens, 2944 channels 351.7 / 356.9.
 bool bl_gemm_mid_mx_ok(int64_t M, int64_t N, int64_t K, bool glu) {
   const int64_t n_cols = glu ? 2 * N : N;                  // the outputs of both matrices
   const int64_t cus = bl_num_cus();
   const double share = (double)(((M + 63) / 64) * ((n_cols + 255) / 256)) / cus;
   const double KT = (double)(bl_round_up(K, BL_KPAD) >> 8);
   const double small = 0.7 * (double)gm_turns(M, n_cols, 64, 256, cus) + 0.3 * share, large = (double)gm_turns(M, n_cols, 256, 256, cus);
-  // (at less than 7 % by this count the large ones stay: 1000 x 2 x 11008 x 4096 is 59.0 us large, 56.1 small, 2048 x 2 x 5460 x 2048 37.2 /
-  // 35.2, but the INT8 products after them slow down under the power limit and a layer takes 0.986 to 1.008, 0.990 to 1.024 of the speed)
   if (glu) return small < 3.1 * large - 0.45;
-  return small < (3.05 * large - 0.25) * (KT < 8.0 ? 0.6 + 0.05 * KT : 1.0);
+  return small < (3.05 * large - 0.25) * (large == 1.0 && KT < 8.0 ? 0.6 + 0.05 * KT : 1.0);
 }
 
 #define GM_CALL(FMT, OUT, GLU, TM, TN, G) \
@@ -493,18 +495,24 @@ static int gm_int(const void* q, const float* scale, int64_t M, int64_t K, const
 // Block-float codes.  What bounds a step is the CU's vector loads (about 53 bytes per clock): with the four waves side by side
 // (1 x 4, every wave with all 64 tokens) the weights are fetched once instead of by two waves, 20 KB a step for 64 x 128 instead of
 // 28, and 28 KB for 64 x 256.  So 64 x 256 tiles wherever they save a turn or more (a turn of theirs is 1.4 times as long), else 64 x
-// 128, with two K groups (2 x 2 waves each) where these fill one turn and K is long.  Product alone, weights from HBM, 2 x 2 waves / 64 x 128 / 64 x 256:
-// 200 x 9600 x 3200 13.2 / 12.4 / 10.9, 200 x 6144 x 2048 7.1 / 6.8 / 7.8, 300 x 12288 x 4096 17.2 / 16.7 / 14.2, 700 x 9600 x 3200 25.0 /
-// 25.0 / 21.5; one / two K groups 66 x 12288 x 4096 10.6 / 9.7, 128 x 9600 x 3200 9.6 / 10.4.
+// 128.  Product alone, weights from HBM, 2 x 2 waves / 64 x 128 / 64 x 256, us: 200 x 9600 x 3200 13.2 / 12.4 / 10.9, 300 x 12288 x 4096 17.2 / 16.7 /
+// 14.2, 700 x 9600 x 3200 25.0 / 25.0 / 21.5.
+// Where 64 x 128 tiles fill no more than one turn, the blocks are few and short: 2 x 2 waves start sooner than 1 x 4, and beyond 3584
+// channels two K groups of them are faster still.  Quantizer and product, mean over 65 to 400 tokens, 2 x 2 / 1 x 4 / two groups: 4608 x 1536 9.3 /
+// 9.4 / 10.5, 9600 x 3200 12.5 / 12.8 / 13.3, 11136 x 3712 13.2 / 13.5 / 13.6; with weights in the last-level cache 8.7 / 8.9 / 9.6, 12.1 / 12.7 /
+// 12.2, 12.8 / 13.4 / 12.2.
+// Where 64 x 256 tiles leave their third turn nearly empty and rows are up to 3072 channels, 64 x 128 are level alone and don't slow
+// down what follows: products alone and two layers, 64 x 128 / 64 x 256: 1400 x 6144 x 2048 19.1 / 20.8 and 236 / 240, 927 x 8832 x 2944 24.3 / 24.1
+// and 247 / 250; longer rows 751 x 12288 x 4096 31.6 / 28.6 and 348 / 341.
 template <int OUT>
 static int gm_mx(const void* q, const float* scale, int64_t M, int64_t K, const void* Wp, const float* alpha, int64_t N,
                  void* Y, bl_dtype ydt, int32_t* acc_out, hipStream_t s) {
   const int KT = (int)(bl_round_up(K, BL_KPAD) >> 8);
   const void* Wp2 = nullptr;
   const float* alpha2 = nullptr;
-  const int64_t cus = bl_num_cus(), t128 = gm_turns(M, N, 64, 128, cus);
-  if (7 * gm_turns(M, N, 64, 256, cus) <= 5 * t128) return GM_CALL(GM_MX, OUT, false, 2, 2, 1);
-  if (t128 == 1 && KT >= 16) return GM_CALL(GM_MX, OUT, false, 1, 2, 2);
+  const int64_t cus = bl_num_cus(), t128 = gm_turns(M, N, 64, 128, cus), t256 = gm_turns(M, N, 64, 256, cus);
+  if (t128 == 1) return KT >= 15 ? GM_CALL(GM_MX, OUT, false, 1, 2, 2) : GM_CALL(GM_MX, OUT, false, 1, 2, 1);
+  if (7 * t256 <= 5 * t128 && !(t256 == 3 && t128 == 5 && KT <= 12)) return GM_CALL(GM_MX, OUT, false, 2, 2, 1);
   return GM_CALL(GM_MX, OUT, false, 2, 1, 1);
 }
 
