@@ -1089,19 +1089,24 @@ __global__ __launch_bounds__(QA_THREADS) void unpack_act_kernel(const u32* __res
 //   INT4   32 x 6144 x 2048 (3 MB) 6.8 / 6.4, 32 x 9600 x 3200 (8 MB) 8.6 / 8.2, 32 x 12288 x 3072 (9 MB) 8.8 / 8.8, 32 x 12288 x
 //          4096 (13 MB) 8.9 / 9.1; gate and up 32 x 2 x 5460 x 2048 (6 MB) 7.6 / 7.3, 2 x 11008 x 4096 (23 MB) 11.6 / 12.4, 2 x
 //          2700 x 1024 (1.4 MB) 6.6 / 6.7
-// INT4 rows of 8192 channels and more have a product of few blocks and long serial chains, which gains from weights at hand:
-//   1 x 512 x 11008 (1.4 MB) 9.2 / 7.8, 1 x 4096 x 11008 (11 MB) 9.8 / 8.5, 32 x 4096 x 14336 (14 MB) 12.5 / 11.1, 1 x 8192 x 11008
-//   (22 MB) 12.1 / 11.1; 1 x 8192 x 14336 (28 MB) 13.9 / 12.9 but 128 tokens 25.9 / 26.7; 32 x 8192 x 16384 (32 MB) 16.4 / 18.3.
-//   Weights that the caches hold already: 1 x 4096 x 11008 7.2 / 7.4, 1 x 4096 x 16384 8.9 / 8.7, 64 x 8192 x 11008 13.1 / 13.9
-static bool qa_touch_pays(bool a4, int Kp, size_t bytes) {
+// INT4 rows of 8192 channels and more have a product of few blocks and long serial chains, which gains from weights at hand: more of
+// them are worth touching the longer the rows, and fewer the more tokens.  Without / with, from HBM: 1 x 4096 x 11008 (11 MB) 9.8 / 8.5,
+// 1 x 512 x 11008 (1.4 MB) 9.2 / 7.8, 32 x 4096 x 14336 (14 MB) 12.5 / 11.1; in per cent gained with 16 / 32 / 64 / 128 tokens: 8192 x 8192
+// (16 MB) 3 / -2 / -2 / 2, 4096 x 14336 (14 MB) 16 / 14 / 5 / 4, 8192 x 11008 (22 MB) 13 / 6 / 1 / 4, 8192 x 12288 (24 MB) 3 / -1 / -4 / 0.
+// Weights that the last-level cache holds already are touched in vain, which a call cannot know: up to 12 MB this costs 0 to 5 % (the
+// smaller matrices gain a little all the same), 14 to 22 MB 4 to 12 %, and with Top_k 16 to 22 MB of 11008 channels 6 to 10 %.  A model's layers in
+// a row come from HBM unless all of them fit 256 MB, so the lines are those of weights from HBM.
+static bool qa_touch_pays(bool a4, int64_t M, int Kp, size_t bytes) {
   const size_t mb = (size_t)1 << 20;
   if (!a4) return bytes >= mb && bytes <= 32 * mb;
-  return Kp < 8192 ? bytes >= 2 * mb && bytes <= 8 * mb : bytes >= mb && bytes <= 24 * mb;
+  if (Kp < 8192) return bytes >= 2 * mb && bytes <= 8 * mb;
+  const size_t most = Kp < 9216 ? (M <= 16 ? 16 : 12) : (M <= 32 ? 22 : 16);
+  return bytes >= mb && bytes <= most * mb;
 }
 
-static BlTouch qa_touch(bool a4, int Kp, int threads, const void* W, const void* W2, size_t w_bytes) {
+static BlTouch qa_touch(bool a4, int64_t M, int Kp, int threads, const void* W, const void* W2, size_t w_bytes) {
   BlTouch t = {{(const unsigned char*)W, (const unsigned char*)W2}, W2 ? 2 : 1, 0, 0};
-  if (qa_touch_pays(a4, Kp, w_bytes * t.n_mat)) {
+  if (qa_touch_pays(a4, M, Kp, w_bytes * t.n_mat)) {
     t.lines = (int)(w_bytes >> 7);
     t.blocks = (int)min((int64_t)512, bl_round_up(((int64_t)t.lines * t.n_mat + threads - 1) / threads, 8));
   }
@@ -1279,7 +1284,7 @@ int bl_launch_quantize_frag(const void* X, bl_dtype dt, int64_t M, int64_t K64, 
   const int K = (int)K64, Kp = (int)bl_round_up(K64, BL_KPAD), frag_M = (int)M;
   if (mode == BL_ACT_TOPK_INT8_ABSMAX) {
     if (dt == BL_F32) return qa_run_topk_f32_wave((const u32*)X, M, K, Kp, (int)topk, eps, q, scale, nullptr, frag_M, s);
-    qa_run_topk_regs8(X, M, K, Kp, (int)topk, eps, q, scale, frag_M, qa_touch(false, Kp, 512, W, W2, w_bytes), s);
+    qa_run_topk_regs8(X, M, K, Kp, (int)topk, eps, q, scale, frag_M, qa_touch(false, M, Kp, 512, W, W2, w_bytes), s);
     BL_HIP_CHECK_LAUNCH();
     return BL_OK;
   }
@@ -1287,7 +1292,7 @@ int bl_launch_quantize_frag(const void* X, bl_dtype dt, int64_t M, int64_t K64, 
   if (dt == BL_F32) return K % 4 == 0 ? QA_ROW(u32, 4) : QA_ROW(u32, 1);
   if (K % 8 != 0) return K % 4 == 0 ? QA_ROW(uint16_t, 4) : QA_ROW(uint16_t, 1);
 #undef QA_ROW
-  const BlTouch touch = qa_touch(true, Kp, QA_THREADS, W, W2, w_bytes);
+  const BlTouch touch = qa_touch(true, M, Kp, QA_THREADS, W, W2, w_bytes);
   const int nvv = (Kp / 16 + QA_THREADS - 1) / QA_THREADS;
 #define QA_I4F(NVV)                                                                                                 \
   quant_int4_regs_kernel<false, NVV><<<(unsigned)(M + touch.blocks), QA_THREADS, 0, s>>>((const uint16_t*)X, M, K, Kp, \
