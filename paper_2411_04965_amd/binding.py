@@ -4,12 +4,13 @@ serving loop calls a module that unpacks plain tensors natively.
 Argument marshalling only: every function allocates its outputs with torch (device
 memory), passes raw device pointers and the current HIP stream, and checks the status
 code.  No arithmetic of the method happens here, and there is no fallback: if the
-library has not been built, loading fails loudly.
+library has not been built, loading fails loudly.  (Without the marshalling module the same calls go through ctypes.)
 """
 import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -90,21 +91,22 @@ _marshal = None
 
 
 def _native():
-    """The marshalling module (csrc/marshal.cpp), loaded once; False on a torch that it cannot be loaded with."""
+    """The marshalling module (csrc/marshal.cpp), loaded once; False where it is absent or cannot be loaded: ctypes does the same."""
     global _marshal
     if _marshal is None:
         L = lib()
-        if not os.path.exists(MARSHAL_PATH):
-            raise RuntimeError("bitlinear_marshal.so is not built (%s). Run `python -m paper_2411_04965_amd.build`." % MARSHAL_PATH)
         try:
+            if not os.path.exists(MARSHAL_PATH):
+                raise ImportError("%s is not built" % MARSHAL_PATH)
             loader = importlib.machinery.ExtensionFileLoader("bitlinear_marshal", MARSHAL_PATH)
             m = importlib.util.module_from_spec(importlib.util.spec_from_loader("bitlinear_marshal", loader))
             loader.exec_module(m)
             m.use(*(ctypes.cast(f, _vp).value for f in (L.bitlinear_a4, L.bitlinear_a8_sparse, L.bitlinear_a4_gate_up,
                                                         L.bitlinear_workspace_bytes, L.bitlinear_gate_up_workspace_bytes)))
             _marshal = m
-        except ImportError:
+        except ImportError as e:
             _marshal = False
+            warnings.warn("calls go through ctypes: %s" % e, RuntimeWarning, stacklevel=3)
     return _marshal
 
 

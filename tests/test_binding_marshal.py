@@ -1,0 +1,24 @@
+"""The binding without its marshalling module: calls go through ctypes, and a build that cannot make the module still makes the library."""
+import warnings
+
+import pytest
+
+from paper_2411_04965_amd import binding as B
+from paper_2411_04965_amd import build
+
+
+def _load(monkeypatch, path):
+    monkeypatch.setattr(B, "_marshal", None)
+    monkeypatch.setattr(B, "MARSHAL_PATH", str(path))
+    return B._native()
+
+
+def test_absent_module(monkeypatch, tmp_path):
+    """No module, or a file that cannot be loaded: ctypes, and one warning that says so."""
+    (tmp_path / "broken.so").write_bytes(b"not a shared object")
+    for name in ("absent.so", "broken.so"):
+        with pytest.warns(RuntimeWarning, match="ctypes"):
+            assert _load(monkeypatch, tmp_path / name) is False
+        with warnings.catch_warnings():
+            warnings.simplefilter("error")
+            assert B._native() is False
