@@ -49,7 +49,7 @@ def _build_marshal():
         raise RuntimeError("building bitlinear_marshal failed:\n" + r.stderr)
 
 
-def build(verbose=True, jobs=4):
+def _build_library(verbose, jobs):
     os.makedirs(OBJ, exist_ok=True)
     os.makedirs(LIB_DIR, exist_ok=True)
     objs = []
@@ -65,7 +65,16 @@ def build(verbose=True, jobs=4):
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
-    _build_marshal()
+
+
+def build(verbose=True, jobs=4):
+    _build_library(verbose, jobs)
+    try:
+        _build_marshal()
+    except Exception as e:                       # (no C++ compiler, no headers: the library needs neither, and the binding has ctypes)
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)
+        print("bitlinear_marshal not built, the binding goes through ctypes: %s" % e, file=sys.stderr)
     if verbose:
         print("built", LIB)
     return LIB

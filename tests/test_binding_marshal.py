@@ -22,3 +22,14 @@ def test_absent_module(monkeypatch, tmp_path):
         with warnings.catch_warnings():
             warnings.simplefilter("error")
             assert B._native() is False
+
+
+def test_build_without_module(monkeypatch, tmp_path, capsys):
+    """No C++ compiler: the library is built all the same, an older module goes."""
+    old = tmp_path / "old.so"
+    old.write_bytes(b"")
+    monkeypatch.setattr(build, "MARSHAL", str(old), raising=False)
+    monkeypatch.setattr(build, "_build_library", lambda verbose, jobs: None, raising=False)
+    monkeypatch.setenv("CXX", str(tmp_path / "no-compiler"))
+    assert build.build(verbose=False) == build.LIB
+    assert not old.exists() and "ctypes" in capsys.readouterr().err
