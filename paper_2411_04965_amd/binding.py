@@ -10,13 +10,21 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import sysconfig
 import warnings
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libbitlinear.so")
-MARSHAL_PATH = os.path.join(_HERE, "lib", "bitlinear_marshal.so")
+
+
+def _marshal_path():
+    """The module reads torch's and Python's object layouts through their headers: one file for each pair of them."""
+    return os.path.join(_HERE, "lib", "bitlinear_marshal.%s.%s.so" % (torch.__version__, sysconfig.get_config_var("SOABI")))
+
+
+MARSHAL_PATH = _marshal_path()
 
 BL_F32, BL_BF16 = 0, 1
 BL_ACT_INT4_ABSMEAN, BL_ACT_TOPK_INT8_ABSMAX, BL_ACT_FP4_E2M1_B32, BL_ACT_INT4_ABSMEAN_MX6 = 0, 1, 2, 3

@@ -1,5 +1,6 @@
 """Build the HIP library (gfx950 only) in-tree, paper_2411_04965_amd/lib/libbitlinear.so, and the host-only module beside it that
-marshals arguments for the Python binding, bitlinear_marshal.so."""
+marshals arguments for the Python binding, bitlinear_marshal.<torch>.<python>.so."""
+import glob
 import os
 import subprocess
 import sys
@@ -10,7 +11,6 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIB_DIR, "libbitlinear.so")
-MARSHAL = os.path.join(LIB_DIR, "bitlinear_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -37,8 +37,10 @@ def _build_marshal():
     import torch
     from torch.utils import cpp_extension
 
+    from .binding import MARSHAL_PATH
+
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH]
     for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
         cmd += ["-isystem", d]
     for d in cpp_extension.library_paths():
@@ -69,11 +71,11 @@ def _build_library(verbose, jobs):
 
 def build(verbose=True, jobs=4):
     _build_library(verbose, jobs)
+    for old in glob.glob(os.path.join(glob.escape(LIB_DIR), "bitlinear_marshal*.so")):
+        os.remove(old)
     try:
         _build_marshal()
     except Exception as e:                       # (no C++ compiler, no headers: the library needs neither, and the binding has ctypes)
-        if os.path.exists(MARSHAL):
-            os.remove(MARSHAL)
         print("bitlinear_marshal not built, the binding goes through ctypes: %s" % e, file=sys.stderr)
     if verbose:
         print("built", LIB)

@@ -2,6 +2,7 @@
 import warnings
 
 import pytest
+import torch
 
 from paper_2411_04965_amd import binding as B
 from paper_2411_04965_amd import build
@@ -26,10 +27,17 @@ def test_absent_module(monkeypatch, tmp_path):
 
 def test_build_without_module(monkeypatch, tmp_path, capsys):
     """No C++ compiler: the library is built all the same, an older module goes."""
-    old = tmp_path / "old.so"
+    old = tmp_path / "bitlinear_marshal.old.so"
     old.write_bytes(b"")
-    monkeypatch.setattr(build, "MARSHAL", str(old), raising=False)
+    monkeypatch.setattr(build, "LIB_DIR", str(tmp_path))
     monkeypatch.setattr(build, "_build_library", lambda verbose, jobs: None, raising=False)
     monkeypatch.setenv("CXX", str(tmp_path / "no-compiler"))
     assert build.build(verbose=False) == build.LIB
     assert not old.exists() and "ctypes" in capsys.readouterr().err
+
+
+def test_one_module_for_each_torch(monkeypatch):
+    """A module that was built with another torch is not taken."""
+    assert B.MARSHAL_PATH == B._marshal_path()
+    monkeypatch.setattr(torch, "__version__", "9.9.9")
+    assert B._marshal_path() != B.MARSHAL_PATH
