@@ -12,6 +12,7 @@
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <torch/csrc/Dtype.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <exception>
@@ -153,8 +154,13 @@ PyObject* guarded(Py_ssize_t n, Py_ssize_t want, F body) {
     Py_RETURN_NONE;
   } catch (const std::exception_ptr&) {
     return nullptr;                                        // (a Python error is set)
+  } catch (python_error& e) {                              // (Python code that torch called, a dispatch mode for instance: its own error)
+    e.restore();
+    if (PyErr_Occurred()) return nullptr;
+    Py_RETURN_NONE;
   } catch (const std::exception&) {                        // (allocation, a tensor without storage: nothing is enqueued yet,
-    Py_RETURN_NONE;                                        //  and the general way meets the same and words it)
+    if (PyErr_Occurred()) return nullptr;                  //  and the general way meets the same and words it)
+    Py_RETURN_NONE;
   }
 }
 

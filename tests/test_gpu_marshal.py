@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 from torch.overrides import TorchFunctionMode
+from torch.utils._python_dispatch import TorchDispatchMode
 
 from paper_2411_04965_amd import binding as B
 
@@ -99,3 +100,23 @@ def test_plain_calls_only():
     torch.cuda.current_stream().wait_stream(s)
     y.record_stream(torch.cuda.current_stream())
     assert torch.equal(y, ref)
+
+
+class Refuses(TorchDispatchMode):
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        raise KeyError("no allocation here")
+
+
+def test_errors_of_a_dispatch_mode(monkeypatch):
+    """What a dispatch mode raises in the allocation of workspace or output reaches the caller as it is."""
+    X = torch.randn((3, 256), device="cuda").to(BF16)
+    p, a = B.pack_ternary(torch.randn((32, 256), device="cuda"))
+    for call in (lambda: B.bitlinear_a4(X, p, a, 32), lambda: B.bitlinear_a8_sparse(X, 8, p, a, 32),
+                 lambda: B.bitlinear_a4_gate_up(X, p, a, p, a, 32, want=("H",))):
+        def inside(call=call):
+            with Refuses():
+                return call()
+        with monkeypatch.context() as mp:
+            n, c = both(mp, inside)
+        assert n == c and n[0] is KeyError, (n, c)
+    assert torch.equal(B.bitlinear_a4(X, p, a, 32), B.bitlinear_a4(X, p, a, 32, want_acc=True)[0])
