@@ -78,3 +78,16 @@ def test_guard_bytes():
         else:
             B.bitlinear_a8_sparse(X, K // 2, p, a, N, ws=ws[:n], out=y[:M * N])
         assert (ws[n:] == 0x5A).all() and (y[M * N:] == 7.0).all()
+
+
+@pytest.mark.parametrize("M", [2, 33])
+@pytest.mark.parametrize("N", [70, 72])
+def test_nan_scale(M, N):
+    """A weight scale that is NaN, of any payload, gives NaN outputs whatever the length of the rows."""
+    print("[case] nan M=%d N=%d" % (M, N), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    X = torch.randn((M, 264), generator=g, device="cuda").to(BF16)
+    p, a = B.pack_ternary(torch.randn((N, 264), generator=g, device="cuda"))
+    for bits in (0x7FC00000, 0x7FFFFFFF, -1):
+        nan = torch.full((1,), bits, dtype=torch.int32, device="cuda").view(torch.float32)
+        assert B.bitlinear_a4(X, p, nan, N).isnan().all() and B.bitlinear_a8_sparse(X, 100, p, nan, N).isnan().all()
