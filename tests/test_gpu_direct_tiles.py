@@ -80,6 +80,48 @@ def test_guard_bytes():
         assert (ws[n:] == 0x5A).all() and (y[M * N:] == 7.0).all()
 
 
+def _special_rows(M, K, seed):
+    """Rows in turn: zeros, one value, few values with ties everywhere, mostly zeros, an infinity, both infinities, NaN, subnormals, largest
+    finite values, ordinary ones."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn((M, K), generator=g, device="cuda")
+    x[0::10] = 0.0
+    x[1::10] = -0.75
+    x[2::10] = torch.round(x[2::10] * 2.0) * 0.5
+    x[3::10] *= torch.rand(x[3::10].shape, generator=g, device="cuda") < 0.1
+    x[4::10, K // 2] = float("inf")
+    x[5::10, 0] = float("inf")
+    x[5::10, K - 1] = float("-inf")
+    x[6::10, K // 3] = float("nan")
+    x[7::10] *= 1e-39
+    x[8::10] = x[8::10].sign() * 3.0e38
+    return x
+
+
+@pytest.mark.parametrize("M", [9, 16, 35, 64, 200, 256])
+@pytest.mark.parametrize("K,dtype", [(520, BF16), (4104, BF16), (5460, BF16), (9000, BF16), (1021, BF16), (516, torch.float32),
+                                     (1024, torch.float32), (2050, torch.float32)])
+def test_special_rows(M, K, dtype):
+    """Codes stored in fragment order against the same quantizers' codes in row order: accumulators, outputs and scales."""
+    print("[case] special rows M=%d K=%d %s" % (M, K, dtype), flush=True)
+    N = 130
+    X = _special_rows(M, K, M + K).to(dtype)
+    p, a = B.pack_ternary(torch.randn((N, K), generator=torch.Generator(device="cuda").manual_seed(K), device="cuda"))
+    for mode, topks in ((B.BL_ACT_INT4_ABSMEAN, (0,)), (B.BL_ACT_TOPK_INT8_ABSMAX, (1, K // 2, K))):
+        for topk in topks:
+            qa = B.quantize_act(X, mode, topk=topk)
+            y_ref, acc_ref = B.bitlinear_gemm(qa["q"], qa["scale"], mode, M, K, p, a, N, y_dtype=torch.float32, want_acc=True)
+            ws = B.workspace(mode, M, N, K, "cuda")
+            if mode == B.BL_ACT_INT4_ABSMEAN:
+                y, acc = B.bitlinear_a4(X, p, a, N, y_dtype=torch.float32, want_acc=True, ws=ws)
+            else:
+                y, acc = B.bitlinear_a8_sparse(X, topk, p, a, N, y_dtype=torch.float32, want_acc=True, ws=ws)
+            assert torch.equal(acc, acc_ref)
+            assert ((y == y_ref) | (y.isnan() & y_ref.isnan())).all()
+            at = (qa["q"].numel() + 255) // 256 * 256
+            assert torch.equal(ws[at:at + 4 * M].view(torch.int32), qa["scale"].view(torch.int32))
+
+
 @pytest.mark.parametrize("M", [2, 33])
 @pytest.mark.parametrize("N", [70, 72])
 def test_nan_scale(M, N):

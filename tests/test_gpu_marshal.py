@@ -78,7 +78,7 @@ def test_same_outputs_and_errors(monkeypatch):
 
 
 def test_plain_calls_only():
-    """Returned outputs are the caller's own; function modes and subclasses take the general way."""
+    """Plain calls are taken by the module itself, returned outputs are the caller's own; function modes and subclasses take the general way."""
     X = torch.randn((3, 256), device="cuda").to(BF16)
     p, a = B.pack_ternary(torch.randn((32, 256), device="cuda"))
     m = B._native()
@@ -88,7 +88,13 @@ def test_plain_calls_only():
     r = B.bitlinear_a4_gate_up(X, p, a, p, a, 32, want=("H",), out=d)
     assert r["H"] is out and r is not d and list(r) == ["H"]
     args = (p, a, 32, 1e-5, False, BF16, None, None, 0)
-    assert m.a4(X, *args) is not None and m.a4(X.as_subclass(Sub), *args) is None and m.a4(X.float().half(), *args) is None
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    for w, o in ((None, None), (ws, out)):
+        for x in (X, X.float(), torch.nn.Parameter(X)):
+            assert torch.is_tensor(m.a4(x, p, a, 32, 1e-5, False, BF16, w, o, 0))
+            assert torch.is_tensor(m.a8_sparse(x, 8, p, a, 32, 1e-5, 0, BF16, w, o))
+            assert type(m.gate_up(x, p, a, p, a, 32, 1e-5, 0, ("H",), w, None if o is None else {"H": o})) is dict
+    assert m.a4(X.as_subclass(Sub), *args) is None and m.a4(X.float().half(), *args) is None
     with Quiet():
         assert m.a4(X, *args) is None
         assert torch.equal(B.bitlinear_a4(X, p, a, 32), B.bitlinear_a4(X, p, a, 32, want_acc=True)[0])
