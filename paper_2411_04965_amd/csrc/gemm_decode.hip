@@ -883,16 +883,15 @@ bool bl_gemm_decode_glu_ok(int64_t M, int64_t N, int64_t K) {
   int MT, NWT, KS, NBn;
   size_t smem;
   if (M > 64 || N > ((int64_t)1 << 27)) return false;
-  // (33 to 64 tokens mostly run in gemm_mid.hip, which takes any K; rows too wide for this plan keep to the composed path, whose
-  // larger workspace their callers already pass)
+  // (33 to 64 tokens run in gemm_mid.hip, which takes any K; rows too wide for this plan keep to the composed path's larger workspace,
+  // which their callers already pass)
   return gr_glu_plan((int)M, (int)N, (int)bl_round_up(K, BL_KPAD), MT, NWT, KS, NBn, smem);
 }
 
-template <int MT>
 static int gr_go_glu(const void* q, const float* scale, int M, int Kp, const void* Wg, const float* ag, const void* Wu,
                      const float* au, int N, void* H, int NWT, int KS, int NBn, size_t smem, hipStream_t s) {
-  BL_SET_MAX_LDS_ONCE((gemm_decode_resident_kernel<MT, true, true>), GR_LDS_MAX);
-  gemm_decode_resident_kernel<MT, true, true><<<(unsigned)NBn, GR_THREADS, smem, s>>>(
+  BL_SET_MAX_LDS_ONCE((gemm_decode_resident_kernel<2, true, true>), GR_LDS_MAX);
+  gemm_decode_resident_kernel<2, true, true><<<(unsigned)NBn, GR_THREADS, smem, s>>>(
       (const unsigned char*)q, scale, M, Kp, (const unsigned char*)Wg, ag, N, H, 1, nullptr, nullptr, NBn, 1, NWT, KS,
       (const unsigned char*)Wu, au);
   BL_HIP_CHECK_LAUNCH();
@@ -906,12 +905,10 @@ int bl_launch_gemm_decode_glu(const void* q, const float* scale, int64_t M, int6
   size_t smem;
   const int Kp = (int)bl_round_up(K, BL_KPAD);
   if (!gr_glu_plan((int)M, (int)N, Kp, MT, NWT, KS, NBn, smem)) return BL_EUNSUPPORTED;
-  if (MT == 2) return gr_go_glu<2>(q, scale, (int)M, Kp, Wg, ag, Wu, au, (int)N, H, NWT, KS, NBn, smem, s);
-  // more than 32 tokens: resident while one tile pair per block covers the outputs (NWT = 2: 4096 outputs on 256 CUs) and K is more
-  // than four steps of 256.  With quantizer, weights from HBM, 64 tokens, here / in gemm_mid.hip: 2 x 3000 x 1152 8.9 us / 9.6, 2 x 4096 x
-  // 1536 9.6 / 10.4, 2 x 1024 x 2688 10.3 / 11.2, 2 x 4096 x 4096 13.1 / 13.2; 2 x 2688 x 1024 8.7 / 8.1; 2 x 4160 x 4096 15.0 / 13.4, 2 x
-  // 5460 x 2048 11.8 / 10.2, 2 x 11008 x 4096 18.4 / 14.2
-  if (NWT == 2 && (Kp >> 8) > 4) return gr_go_glu<4>(q, scale, (int)M, Kp, Wg, ag, Wu, au, (int)N, H, NWT, KS, NBn, smem, s);
+  if (MT == 2) return gr_go_glu(q, scale, (int)M, Kp, Wg, ag, Wu, au, (int)N, H, NWT, KS, NBn, smem, s);
+  // 33 to 64 tokens come here with more outputs than fragment order is for (gemm_direct.hip), where one tile pair per block no longer covers
+  // them and the 64-token tiles are faster than codes kept in LDS: 64 tokens, 2 x 5460 x 2048 10.2 us against 11.8, 2 x 11008 x 4096 14.2
+  // against 18.4
   return bl_launch_gemm_mid_a4_glu(q, scale, M, K, Wg, ag, Wu, au, N, H, s);
 }
 
