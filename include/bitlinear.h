@@ -204,11 +204,14 @@ int quantize_act(const void* X, bl_dtype x_dtype, int64_t M, int64_t K, bl_act_m
  *   acc_out    nullable; device int32[M, N], receives the integer accumulators
  *   workspace  device, >= bitlinear_workspace_bytes(mode, M, N, K) bytes; holds the
  *              packed activations and their scales between the two kernels
- * Kernel choice (BL_W_GEMM) is by M: up to BL_DECODE_MAX_M tokens the weights are streamed once
- * by a skinny (decode) kernel, with the quantizer inside the same launch for up to 8 bfloat16
- * tokens (INT4) or one (Top_k + INT8); above that the tiled MFMA GEMM runs.  Up to 256
- * tokens the codes in the workspace are in the order of the product's loads (no public form).  The
- * block-float forms always take the tiled GEMM.
+ * Kernel choice (BL_W_GEMM).  Up to 8 bfloat16 tokens (INT4; K % 8 == 0, K <= 8192) or one (Top_k +
+ * INT8) run as one launch with the quantizer inside.  Else up to 256 tokens take two launches, with the
+ * codes in the workspace in the order of the product's loads (no public form), while M and N are not
+ * both large (about 4000 to 6000 M x N per compute unit) and the quantizer of that form takes the rows
+ * (INT4: K <= 16384, of float32 or ragged rows 9 tokens or K <= 4096; Top_k: bfloat16 with K % 4 == 0
+ * and K <= 12288, float32 with K % 4 == 0 and K <= 1024).  Else the codes are in row order, as
+ * quantize_act writes them, and the product goes by M as in bitlinear_gemm: skinny kernels up to
+ * BL_DECODE_MAX_M tokens, tiled GEMMs above.  The block-float forms always take tiled GEMMs.
  *
  * bitlinear_a8_sparse (eq. 1): Y = (Q_INT8(X) (.) Top_k(|X|)) . Q_w(W)^T, same
  * accumulation and rescale.  With layout BL_W_KMAJOR (decode, M <= BL_SPARSE_MAX_M; more tokens:
@@ -267,10 +270,9 @@ int bitlinear_gemm(const void* q, const void* scale, bl_act_mode mode, int64_t M
  *   workspace  device, >= bitlinear_gate_up_workspace_bytes(M, N, K, layout) bytes (packed activations,
  *              scales, decode partial sums, and float32 G and U where H is wanted without them)
  * Up to 8 bfloat16 tokens with BL_W_GEMM weights (K % 8 == 0, K <= 8192) run as one launch that
- * streams both matrices once and uses no workspace (it may then be NULL); up to 64 tokens with
- * BL_W_GEMM weights and only H asked for run the quantizer and then one launch over both matrices
- * (up to 256 tokens where M and N are not both large; else K up to 4096 beyond 32 tokens, 8192 beyond 16).  With block-float weights
- * (BL_W_MX4 / BL_W_MX2) and only H asked for, the quantizer is followed by one GEMM over both
+ * streams both matrices once and uses no workspace (it may then be NULL); up to 256 tokens with
+ * BL_W_GEMM weights, K <= 16384 (of up to 8 float32 or ragged rows 4096, more where their codes fit the
+ * LDS) and only H asked for run the quantizer and then one launch over both matrices, for any N.  With block-float weights (BL_W_MX4 / BL_W_MX2) and only H asked for, the quantizer is followed by one GEMM over both
  * matrices whose epilogue applies eq. 5 to its accumulators: G and U never reach memory.  Other
  * cases run the quantizer, the two products and the combine as separate kernels. */
 size_t bitlinear_gate_up_workspace_bytes(int64_t M, int64_t N, int64_t K, bl_w_layout layout);

@@ -1,4 +1,5 @@
-// Decode-shaped linears for up to 16 tokens as ONE persistent launch per call.
+// Decode-shaped linears for up to 16 tokens as ONE persistent launch per call: up to 8 with eq. 7 inside, one with the Top_k quantizer,
+// and up to 16 whose codes come in row order from a caller (the linears themselves use fragment order there: gemm_direct.hip).
 //
 // At these sizes a launch costs as much as streaming the weights (an empty kernel takes 1.6 us
 // between two others, 12 MB of weights at full HBM rate 1.6 us), so the design goal is: one launch,

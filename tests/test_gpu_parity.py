@@ -596,8 +596,8 @@ def test_decode_stream_int4_quantizer_inside(M, N, K):
                                         (16, 11008, 4096, "a4"), (8, 4096, 11008, "a8s"), (5, 2064, 5460, "a8s"),
                                         (3, 1040, 2048, "a4f32"), (16, 300, 8192, "a8s")])
 def test_decode_stream_codes_from_quantizer(M, N, K, kind):
-    """2 to 16 tokens through the stand-alone quantizer and the persistent launch (INT4 nibbles
-    expanded into LDS, INT8 codes copied), float32 inputs included."""
+    """3 to 16 tokens through the stand-alone quantizer and the product on its codes in fragment order, float32 inputs
+    included (the persistent launch on codes in row order: test_gpu_row_order.py)."""
     say("decode stream (codes from the quantizer) M=%d N=%d K=%d %s" % (M, N, K, kind))
     W = S.latent_weights(N, K, S.seed_for(2, 541 + N))
     p, a = pack(W)
@@ -627,8 +627,9 @@ def test_decode_stream_codes_from_quantizer(M, N, K, kind):
 def test_gate_up(M, N, K, layout):
     """Gate and up projection on one quantized input (eq. 5-7): G, U and H = bf16(U * max(G, 0)^2)
     against the oracle's two linears and its GLU, bit for bit -- the one-launch form for up to 8
-    tokens, and the composed form (decode kernels, int8 GEMM, block-float GEMM) for the rest; every
-    combination of outputs the entry point can be asked for."""
+    tokens, the fragment-order and block-float products with eq. 5 in their epilogue where only H is wanted, and the
+    composed form (decode kernels, int8 GEMM, block-float GEMM) for the rest; every combination of outputs the entry
+    point can be asked for."""
     say("gate/up M=%d N=%d K=%d layout=%d" % (M, N, K, layout))
     X = S.heavy(M, K, S.seed_for(2, 800 + M))
     Wg = S.latent_weights(N, K, S.seed_for(2, 801 + N))

@@ -47,7 +47,8 @@ def product(X, W, mode, topk=0):
 
 
 # (tokens, outputs, channels) that reach each tile of the many-token GEMMs on 256 CUs, with ragged edges, one K step (fewer
-# than K groups), odd and even numbers of steps: 64 x 64, 64 x 128 with one and two K groups, 128 x 128, 256 x 256
+# than K groups), odd and even numbers of steps: 64 x 64, 64 x 128 with one and two K groups, 128 x 128, 256 x 256 (integer codes of up to
+# 256 tokens go through the fragment-order products here, and through these tiles in test_gpu_row_order.py)
 TILES = [(65, 63, 200), (191, 1021, 257), (130, 516, 700), (449, 3211, 1025), (833, 2045, 300), (641, 4091, 520), (1153, 2052, 777),
          (4090, 4091, 300), (4097, 4100, 520), (2900, 6141, 256)]
 
@@ -79,7 +80,8 @@ def test_tiles(M, N, K):
     assert torch.equal(h, (u4 * y4.clamp_min(0.0).square()).to(BF16))
 
 
-# both sides of 32 tokens; K of one step and of an odd number; outputs past one turn of the smallest tile and of the next one
+# both sides of 32 tokens; K of one step and of an odd number; outputs past one turn of the smallest tile and of the next one (fragment
+# order, except the two widest; the kernels behind it: test_gpu_row_order.py)
 @pytest.mark.parametrize("M,N,K,mul", [(32, 70, 300, 1.0), (33, 70, 200, 1.0), (33, 1027, 1300, 1e-36), (57, 5460, 2048, 1.0),
                                        (64, 16452, 520, 1.0), (63, 32901, 257, 1.0), (64, 260, 4200, 1.0)])
 def test_decode_tokens(M, N, K, mul):
@@ -107,7 +109,8 @@ def test_decode_tokens(M, N, K, mul):
 
 # more than 32 tokens: both sides of the rule on long K (INT8 codes: from 26 K tiles on, from 29 below 40 tokens, with outputs up
 # to 2048, 512 per K tile beyond 28 or 30, 5120 or 6144; INT4 codes: from 30 on with 512, or 512 per tile beyond 31 and 176 per tile
-# beyond 20), one and two turns of the chip
+# beyond 20), one and two turns of the chip.  The linears take fragment order at most of these; the rule itself is tested on codes in row
+# order (test_gpu_row_order.py)
 @pytest.mark.parametrize("M,N,K", [(40, 70, 6401), (39, 70, 7168), (64, 2048, 6656), (64, 2049, 6500), (33, 2048, 7937), (47, 512, 7600),
                                    (64, 513, 7680), (64, 2560, 9216), (40, 2561, 9000), (64, 5120, 10241), (57, 5121, 9985),
                                    (35, 4916, 20480), (50, 6144, 13500), (33, 333, 32768), (64, 6144, 24577)])
@@ -169,7 +172,7 @@ def test_block_float_outputs(M, N, K, layout):
     assert torch.equal(B.bitlinear_a4(X, p, a, N, layout=layout, act_fp4=True), y.to(BF16))
 
 
-# 33 to 64 tokens: gate and up with the codes resident (one tile pair per block, more than four steps of K) and without
+# 33 to 64 tokens: gate and up, on 256 CUs all through the fragment-order products (other kernels: test_gpu_row_order.py)
 @pytest.mark.parametrize("M,N,K", [(33, 70, 1025), (64, 4096, 1200), (50, 4097, 1200), (64, 4090, 1024), (64, 1021, 4096), (47, 2688, 4001)])
 def test_decode_gate_up(M, N, K):
     """Gate and up with eq. 5 in the same launch, bit for bit."""
