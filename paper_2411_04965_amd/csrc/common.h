@@ -73,11 +73,10 @@ __device__ __forceinline__ void bl_store_tail8(uint16_t* p, v4i v, int n_left) {
 // (nullable); rows whose length is no multiple of 4 by elements.
 __device__ __forceinline__ void bl_store_out4(void* Y, int y_bf16, int32_t* acc_out, size_t o, int n, int N,
                                           const int (&iv)[4], const float (&fv)[4]) {
-  const u32 b01 = bl_pack_bf16(fv[0], fv[1]), b23 = bl_pack_bf16(fv[2], fv[3]);   // (any NaN stays one)
   if ((N & 3) == 0) {
     if (Y) {
       if (y_bf16) {
-        *reinterpret_cast<uint2*>((uint16_t*)Y + o) = make_uint2(b01, b23);
+        *reinterpret_cast<uint2*>((uint16_t*)Y + o) = make_uint2(bl_pack_bf16(fv[0], fv[1]), bl_pack_bf16(fv[2], fv[3]));
       } else {
         *reinterpret_cast<float4*>((float*)Y + o) = make_float4(fv[0], fv[1], fv[2], fv[3]);
       }
@@ -88,7 +87,7 @@ __device__ __forceinline__ void bl_store_out4(void* Y, int y_bf16, int32_t* acc_
     for (int r = 0; r < 4; ++r) {
       if (n + r < N) {
         if (Y) {
-          if (y_bf16) ((uint16_t*)Y)[o + r] = (uint16_t)((r < 2 ? b01 : b23) >> (16 * (r & 1)));
+          if (y_bf16) ((uint16_t*)Y)[o + r] = (uint16_t)bl_pack_bf16(fv[r], fv[r]);   // (any NaN stays one, as above)
           else ((float*)Y)[o + r] = fv[r];
         }
         if (acc_out) acc_out[o + r] = iv[r];
