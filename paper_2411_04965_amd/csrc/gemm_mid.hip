@@ -501,8 +501,8 @@ static int gm_int(const void* q, const float* scale, int64_t M, int64_t K, const
 // channels two K groups of them are faster still.  Quantizer and product, mean over 65 to 400 tokens, 2 x 2 / 1 x 4 / two groups: 4608 x 1536 9.3 /
 // 9.4 / 10.5, 9600 x 3200 12.5 / 12.8 / 13.3, 11136 x 3712 13.2 / 13.5 / 13.6; with weights in the last-level cache 8.7 / 8.9 / 9.6, 12.1 / 12.7 /
 // 12.2, 12.8 / 13.4 / 12.2.
-// Where 64 x 256 tiles leave their third turn nearly empty and rows are up to 3072 channels, 64 x 128 are level alone and don't slow
-// down what follows: products alone and two layers, 64 x 128 / 64 x 256: 1400 x 6144 x 2048 19.1 / 20.8 and 236 / 240, 927 x 8832 x 2944 24.3 / 24.1
+// Where 64 x 256 tiles leave their third turn nearly empty and rows are up to 3072 channels, 64 x 128 are about level and don't slow
+// down what follows: the product inside a layer and two layers, both under the profiler, 64 x 128 / 64 x 256: 1400 x 6144 x 2048 19.1 / 20.8 and 236 / 240, 927 x 8832 x 2944 24.3 / 24.1
 // and 247 / 250; longer rows 751 x 12288 x 4096 31.6 / 28.6 and 348 / 341.
 template <int OUT>
 static int gm_mx(const void* q, const float* scale, int64_t M, int64_t K, const void* Wp, const float* alpha, int64_t N,
